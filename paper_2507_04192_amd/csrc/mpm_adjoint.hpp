@@ -757,13 +757,6 @@ __global__ __launch_bounds__(kAdjBlock) __attribute__((amdgpu_waves_per_eu(2))) 
 // Observation operators and loss (Sec. 3.2, eq:inverse_loss)
 // ---------------------------------------------------------------------------
 
-template <int Unused = 0>
-__global__ void k_inverse_pid(const int32_t* __restrict__ pid, long long N, int32_t* __restrict__ inv)
-{
-    long long s = (long long)blockIdx.x * kBlock + threadIdx.x;
-    if (s < N) inv[pid[s]] = (int32_t)s;
-}
-
 // Lagrangian tracers: Q_l = z of particle l.  Adds m |Q - z_obs|^2 to the
 // loss and, when seed != 0, 2 m (Q - z_obs) to the adjoint of z.
 template <class T, int D>

@@ -1102,6 +1102,25 @@ __global__ void k_fill(T* p, long long n, T v)
 // conversions: F = I + G, J = 1 + dJ, symmetric S <-> full dim x dim.
 enum { CONV_COPY = 0, CONV_ADD_IDENTITY = 1, CONV_ADD_ONE = 2, CONV_SYM = 3, CONV_ISO = 4 };
 
+// Component c of a field in the ABI layout, of the particle in slot s.
+template <class T, int D>
+__device__ __forceinline__ T field_value(const T* __restrict__ src, long long cap, long long s, int c, int conv)
+{
+    const int a = c / D, b = c % D;
+    switch (conv) {
+    case CONV_ADD_IDENTITY: return src[c * cap + s] + ((a == b) ? T(1) : T(0));
+    case CONV_ADD_ONE: return src[s] + T(1);
+    case CONV_SYM: {
+        int q;
+        if (D == 3) q = (a == b) ? a : ((a + b == 1) ? 3 : ((a + b == 2) ? 4 : 5));
+        else q = (a == b) ? a : 2;
+        return src[q * cap + s];
+    }
+    case CONV_ISO: return (a == b) ? src[s] : T(0);
+    default: return src[c * cap + s];
+    }
+}
+
 template <class T, int D>
 __global__ void k_read_field(const T* __restrict__ src, long long cap, const int32_t* __restrict__ pid,
                              long long N, int ncomp, int conv, int by_pid, T* __restrict__ dst)
@@ -1109,24 +1128,44 @@ __global__ void k_read_field(const T* __restrict__ src, long long cap, const int
     long long s = (long long)blockIdx.x * kBlock + threadIdx.x;
     if (s >= N) return;
     long long o = by_pid ? pid[s] : s;
-    for (int c = 0; c < ncomp; ++c) {
-        T v;
-        int a = c / D, b = c % D;
-        switch (conv) {
-        case CONV_ADD_IDENTITY: v = src[c * cap + s] + ((a == b) ? T(1) : T(0)); break;
-        case CONV_ADD_ONE: v = src[s] + T(1); break;
-        case CONV_SYM: {
-            int q;
-            if (D == 3) q = (a == b) ? a : ((a + b == 1) ? 3 : ((a + b == 2) ? 4 : 5));
-            else q = (a == b) ? a : 2;
-            v = src[q * cap + s];
-            break;
-        }
-        case CONV_ISO: v = (a == b) ? src[s] : T(0); break;
-        default: v = src[c * cap + s];
-        }
-        dst[c * N + o] = v;
-    }
+    for (int c = 0; c < ncomp; ++c) dst[c * N + o] = field_value<T, D>(src, cap, s, c, conv);
+}
+
+template <int Unused = 0>
+__global__ void k_inverse_pid(const int32_t* __restrict__ pid, long long N, int32_t* __restrict__ inv)
+{
+    long long s = (long long)blockIdx.x * kBlock + threadIdx.x;
+    if (s < N) inv[pid[s]] = (int32_t)s;
+}
+
+// The same in pid order, gathered through the inverse of pid (several
+// components: the inverse's scatter is paid once).  Scattering the components
+// by pid wrote 8 to 16 bytes of a line at a time from all eight L2s.  Here the
+// writes are whole lines; one component per grid row and one contiguous eighth
+// of the particles per XCD keep the source lines that neighbouring particles
+// share in that XCD's L2.  Cylinder (2,780,000 particles), mean of x, v, C,
+// F and the stress: binary32 87 -> 56 + 12 us for the inverse, binary64
+// 114 -> 80 + 13; one particle per thread 65, bound by the latency of the two
+// dependent loads.
+constexpr int kGatherPer = 4;   // particles per thread, loaded together
+
+template <class T, int D>
+__global__ __launch_bounds__(kBlock) void k_gather_field(const T* __restrict__ src, long long cap,
+                                                         const int32_t* __restrict__ inv, long long N, int conv,
+                                                         T* __restrict__ dst)
+{
+    const long long blk = (long long)(blockIdx.x % 8) * (gridDim.x / 8) + blockIdx.x / 8;
+    const long long o0 = blk * (kBlock * kGatherPer) + threadIdx.x;
+    const int c = blockIdx.y;
+    int at[kGatherPer];
+    T v[kGatherPer];
+#pragma unroll
+    for (int q = 0; q < kGatherPer; ++q) at[q] = o0 + q * kBlock < N ? inv[o0 + q * kBlock] : 0;
+#pragma unroll
+    for (int q = 0; q < kGatherPer; ++q) v[q] = field_value<T, D>(src, cap, at[q], c, conv);
+#pragma unroll
+    for (int q = 0; q < kGatherPer; ++q)
+        if (o0 + q * kBlock < N) dst[c * N + o0 + q * kBlock] = v[q];
 }
 
 template <class T, int D>
@@ -1210,6 +1249,14 @@ __global__ void k_read_grid(Geo g, const T* __restrict__ src, int ncomp, const i
 // ---------------------------------------------------------------------------
 // Host side
 // ---------------------------------------------------------------------------
+
+// Values (particles times components) from which a read in pid order gathers.
+// Below, the second launch costs more than the scattered lines, which then
+// stay in cache: lattice order, 9 components, scatter against gather 6.8 and
+// 10.2 us at 110,592 particles, 10.9 and 10.9 at 262,144, 34.6 and 22.1 at
+// 884,736; 3 components 12.9 and 14.1 at 884,736, 28.0 and 26.3 at 2,097,152
+// (binary32; binary64 crosses at the same sizes).
+constexpr long long kGatherMin = 2500000;
 
 inline unsigned nblocks(long long n) { return (unsigned)((n + kBlock - 1) / kBlock); }
 
@@ -1496,9 +1543,14 @@ struct Solver {
         int ncomp, conv;
         int rc = field_desc(c, field, &src, &ncomp, &conv);
         if (rc) return rc;
-        if (N > 0)
+        if (N > 0 && order == MPM_ORDER_PID && ncomp > 1 && N * ncomp >= kGatherMin) {
+            k_inverse_pid<0><<<nblocks(N), kBlock, 0, st>>>(s.pid, N, c->inv);
+            k_gather_field<T, D><<<dim3((nblocks(N) + 8 * kGatherPer - 1) / (8 * kGatherPer) * 8, ncomp), kBlock, 0, st>>>(src, c->cap, c->inv, N, conv,
+                                                                                          (T*)dst);
+        } else if (N > 0) {
             k_read_field<T, D><<<nblocks(N), kBlock, 0, st>>>(src, c->cap, s.pid, N, ncomp, conv,
                                                              order == MPM_ORDER_PID, (T*)dst);
+        }
         return launch_err(c, "read state");
     }
 
