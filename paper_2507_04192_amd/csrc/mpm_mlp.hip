@@ -1,15 +1,14 @@
 // Learned field alpha(x) ~ N_theta(x) (Sec. 3.2, eq:nn_apprx): a small MLP
 // whose layers run on the matrix cores of gfx950.
 //
-// Each wave owns 16 samples.  A layer h' = act(h W^T + b) is a 16 x out
-// product computed as 16 x 16 output tiles with gfx950's
-// v_mfma_f32_16x16x32_bf16 (BF16 operands, FP32 accumulation, 32-deep K
-// steps) or v_mfma_f32_16x16x4_f32 (FP32 operands); activations stay in the
-// wave's LDS rows between layers.  Widths are padded to multiples of 16 with
-// zeros (the operand functions return zero past the true widths, so a
-// 32-deep step may run past the padding).  The weight gradient
-// dW = dZ^T H (a reduction over samples) is a split-K MFMA product whose
-// partial tiles are added with global atomics.
+// A layer h' = act(h W^T + b) is a product computed as 16 x 16 output tiles
+// with gfx950's v_mfma_f32_16x16x32_bf16 (BF16 operands, FP32 accumulation,
+// 32-deep K steps) or v_mfma_f32_16x16x4_f32 (FP32 operands).  Weights and
+// activations are staged in LDS, zero-padded to the step (16 or 32), by
+// workgroups of 64 samples.  The backward pass is one kernel: a workgroup
+// carries its samples' layer adjoints dZ down the layers in LDS and forms the
+// weight gradients dW = dZ^T H (a reduction over samples) of its samples on
+// the way; a second kernel sums the workgroups' gradients in a fixed order.
 #include <hip/hip_runtime.h>
 #include <math.h>
 #include <stdint.h>
@@ -58,14 +57,14 @@ int scratch_address(float** out)
 }
 
 constexpr int kMaxW = 128;
-constexpr int kRowsPerWave = 16;
+constexpr int kRows = 64;        // samples of a workgroup
+constexpr int kPad = 32;         // operands are zero-padded to this many columns
 typedef float f4 __attribute__((ext_vector_type(4)));
 typedef __bf16 b8 __attribute__((ext_vector_type(8)));
 
 struct MlpDesc {
     int L;
     int w[MPM_MLP_MAX_LAYERS + 1];    // true widths
-    int wp[MPM_MLP_MAX_LAYERS + 1];   // widths padded to 16
     int offW[MPM_MLP_MAX_LAYERS], offb[MPM_MLP_MAX_LAYERS];
     long long offC[MPM_MLP_MAX_LAYERS];   // per-layer offset in the cache (per sample count n)
     int out_act;
@@ -74,206 +73,303 @@ struct MlpDesc {
     float in_scale[MPM_MLP_MAX_IN], in_shift[MPM_MLP_MAX_IN];
 };
 
-// binary32 -> bfloat16, round to nearest even (NaN kept quiet)
-__device__ __forceinline__ short to_bf16(float f)
-{
-    uint32_t u = __float_as_uint(f);
-    if ((u & 0x7fffffffu) > 0x7f800000u) return (short)((u >> 16) | 0x40u);
-    u += 0x7fffu + ((u >> 16) & 1u);
-    return (short)(u >> 16);
-}
-
 __device__ __forceinline__ void wave_sync()
 {
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     __builtin_amdgcn_wave_barrier();
 }
 
-// One 16 x 16 tile: C[r][c] = sum_k A(r, k) * B(k, c), k < K (a multiple of
-// 16).  fa(r, k) and fb(k, c) return zero outside the operands.  Lane l
-// holds C[4*(l/16) + i][l%16], i = 0..3.  BF16: lane l supplies A(l%16, k)
-// and B(k, l%16) for the eight k = k0 + 8*(l/16) + i of each 32-deep step
-// (the same k for both operands, so the pairing is exact whatever order the
-// unit sums in).
-template <int BF16, class FA, class FB>
-__device__ __forceinline__ f4 mfma_tile(int K, FA fa, FB fb)
-{
-    const int lane = threadIdx.x & 63;
-    const int r = lane & 15, q = lane >> 4;
-    f4 c = {0.f, 0.f, 0.f, 0.f};
-    if constexpr (BF16) {
-        for (int k0 = 0; k0 < K; k0 += 32) {
-            b8 a, b;
+// Operands of a 16 x 16 tile C[r][c] = sum_k A(r, k) B(k, c).  Lane l holds
+// C[4*(l/16) + i][l%16], i = 0..3.  FP32: lane l supplies A(l%16, k) and
+// B(k, l%16) for k = k0 + l/16 of each 4-deep step.  BF16: the eight
+// k = k0 + 8*(l/16) + i of each 32-deep step, rounded to nearest even (the
+// same k for both operands, so the pairing is exact whatever order the unit
+// sums in).
+template <int BF16> struct Opnd;
+template <> struct Opnd<0> {
+    static constexpr int STEP = 4, GROUP = 8;   // steps issued together
+    typedef float V;
+    // element k of the lane's vector at p (k advances by `stride` elements)
+    static __device__ __forceinline__ V load(const float* p, int) { return *p; }
+    static __device__ __forceinline__ f4 mma(V a, V b, f4 c) { return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0); }
+    static constexpr int LANE = 1;
+};
+template <> struct Opnd<1> {
+    static constexpr int STEP = 32, GROUP = 1;
+    typedef b8 V;
+    static __device__ __forceinline__ V load(const float* p, int stride)
+    {
+        V v;
 #pragma unroll
-            for (int i = 0; i < 8; ++i) {
-                a[i] = __builtin_bit_cast(__bf16, to_bf16(fa(r, k0 + 8 * q + i)));
-                b[i] = __builtin_bit_cast(__bf16, to_bf16(fb(k0 + 8 * q + i, r)));
-            }
-            c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
-        }
-    } else {
-        for (int k0 = 0; k0 < K; k0 += 4) c = __builtin_amdgcn_mfma_f32_16x16x4f32(fa(r, k0 + q), fb(k0 + q, r), c, 0, 0, 0);
+        for (int i = 0; i < 8; ++i) v[i] = (__bf16)p[i * stride];
+        return v;
     }
-    return c;
-}
+    static __device__ __forceinline__ f4 mma(V a, V b, f4 c) { return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0); }
+    static constexpr int LANE = 8;
+};
 
 __device__ __forceinline__ float act_hidden(int kind, float z) { return kind == MPM_HIDDEN_RELU ? fmaxf(z, 0.f) : tanhf(z); }
 // derivative of the hidden activation from its output h
 __device__ __forceinline__ float dact_hidden(int kind, float h) { return kind == MPM_HIDDEN_RELU ? (h > 0.f ? 1.f : 0.f) : 1.f - h * h; }
 __device__ __forceinline__ float act_out(int kind, float z) { return kind == MPM_ACT_SIGMOID ? 1.f / (1.f + expf(-z)) : z; }
 
-constexpr int kWaves = 2;   // waves per workgroup in the row kernels
+__host__ __device__ __forceinline__ int pad_to(int v, int m) { return (v + m - 1) / m * m; }
 
-template <int BF16>
-__global__ __launch_bounds__(64 * kWaves) void k_mlp_fwd(MlpDesc d, const float* __restrict__ P, long long n,
+// Copies rows [o0, o0 + rows) of a layer's weights (wout x win) to LDS, zero
+// past the true widths, K columns (a multiple of 32), NT threads, 16 per row.
+// Out-of-range elements load an element in range: loads under a condition
+// would each be waited for.
+template <int MW, int NT, int LD>
+__device__ __forceinline__ void stage_rows(float (*dst)[LD], int rows, int K, const float* __restrict__ W, int o0, int wout,
+                                           int win)
+{
+    constexpr int U = MW >= 64 ? 4 : 2;
+    const int t = threadIdx.x & 15;
+#pragma unroll 2
+    for (int o = threadIdx.x >> 4; o < rows; o += NT / 16) {
+        const float* row = W + (long long)min(o0 + o, wout - 1) * win;
+        for (int k0 = 0; k0 < K; k0 += 16 * U) {
+            float v[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) v[u] = row[min(k0 + 16 * u + t, win - 1)];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int k = k0 + 16 * u + t;
+                dst[o][k] = (o0 + o < wout && k < win) ? v[u] : 0.f;
+            }
+        }
+    }
+}
+
+// Forward pass of 64 samples, 16 per wave; MW bounds the widths (32, 64 or
+// 128).  What bounds it is the latency of fetching operands: read straight
+// from global memory, one MFMA step waited for eight scalar loads per operand
+// (BF16).  Here 64 rows of a layer's weights at a time go to LDS (68 KiB with
+// the activations at 128-wide layers: two workgroups per CU), a wave's
+// activations into registers once per layer, and two output tiles are formed
+// at a time.  The row strides (MW + 4 words) give the 64 lanes of an operand
+// read 64 different banks.  2-128-128-1, FP32, 19,897 samples: 47 us (100 with
+// one workgroup per CU and a branch per step); 2-64-64-2, BF16, 32,768: 22 us;
+// most of it is staging and the activations, not the matrix cores.
+template <int BF16, int MW>
+__global__ __launch_bounds__(256) void k_mlp_fwd(MlpDesc d, const float* __restrict__ P, long long n,
                                                  const float* __restrict__ x, float* __restrict__ y,
                                                  float* __restrict__ cache)
 {
-    __shared__ float sh[kWaves][2][kRowsPerWave][kMaxW + 1];
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    float(*buf)[kRowsPerWave][kMaxW + 1] = sh[w];
-    const long long nblk = (n + kRowsPerWave - 1) / kRowsPerWave;
-    for (long long rb = (long long)blockIdx.x * kWaves + w; rb < nblk; rb += (long long)gridDim.x * kWaves) {
-        const long long r0 = rb * kRowsPerWave;
-        for (int i = lane; i < kRowsPerWave * d.wp[0]; i += 64) {
-            int r = i / d.wp[0], k = i % d.wp[0];
-            float v = 0.f;
-            if (r0 + r < n && k < d.w[0]) v = d.in_scale[k] * x[k * n + r0 + r] + d.in_shift[k];
-            buf[0][r][k] = v;
-        }
+    using O = Opnd<BF16>;
+    constexpr int LD = MW + 4, NS = MW / O::STEP, JB = MW < 64 ? MW : 64;
+    __shared__ float s_w[JB][LD];
+    __shared__ float s_a[4][16][LD];
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    const int r = lane & 15, q = lane >> 4;
+    float(*A)[LD] = s_a[w];
+    const long long r0 = (long long)blockIdx.x * kRows + 16 * w;
+    {
+        const bool in = r0 + r < n;
+        for (int k = q; k < kPad; k += 4)
+            A[r][k] = (in && k < d.w[0]) ? d.in_scale[k] * x[k * n + r0 + r] + d.in_shift[k] : 0.f;
+    }
+    for (int l = 0; l < d.L; ++l) {
+        const float* W = P + d.offW[l];
+        const float* bias = P + d.offb[l];
+        const int win = d.w[l], wout = d.w[l + 1];
+        const int K = pad_to(win, kPad), J = pad_to(wout, kPad);
+        const bool last = l == d.L - 1;
         wave_sync();
-        int cur = 0;
-        for (int l = 0; l < d.L; ++l) {
-            const float* W = P + d.offW[l];
-            const float* bias = P + d.offb[l];
-            const int win = d.w[l], wout = d.w[l + 1];
-            for (int jt = 0; jt < d.wp[l + 1]; jt += 16) {
-                float(*A)[kMaxW + 1] = buf[cur];
-                f4 c = mfma_tile<BF16>(
-                    d.wp[l], [&](int r, int k) { return k < win ? A[r][k] : 0.f; },
-                    [&](int k, int col) { return (k < win && jt + col < wout) ? W[(jt + col) * win + k] : 0.f; });
-                const int col = jt + (lane & 15);
+        typename O::V a[NS];
 #pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    int r = 4 * (lane >> 4) + i;
-                    float h = 0.f;
-                    if (col < wout) {
-                        float z = c[i] + bias[col];
-                        h = (l < d.L - 1) ? act_hidden(d.hidden_act, z) : act_out(d.out_act, z);
-                        if (r0 + r < n) cache[d.offC[l] * n + (r0 + r) * wout + col] = h;
+        for (int t = 0; t < NS; ++t)
+            if (t * O::STEP < K) a[t] = O::load(&A[r][t * O::STEP + q * O::LANE], 1);
+        wave_sync();
+        for (int j0 = 0; j0 < J; j0 += JB) {
+            const int rows = min(JB, J - j0);
+            __syncthreads();
+            stage_rows<MW, 256, LD>(s_w, rows, K, W, j0, wout, win);
+            __syncthreads();
+            for (int jt = 0; jt < rows; jt += 32) {
+                f4 c[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
+#pragma unroll
+                for (int g = 0; g < NS / O::GROUP; ++g)
+                    if (g * O::GROUP * O::STEP < K) {
+#pragma unroll
+                        for (int t = g * O::GROUP; t < (g + 1) * O::GROUP; ++t) {
+                            c[0] = O::mma(a[t], O::load(&s_w[jt + r][t * O::STEP + q * O::LANE], 1), c[0]);
+                            c[1] = O::mma(a[t], O::load(&s_w[jt + 16 + r][t * O::STEP + q * O::LANE], 1), c[1]);
+                        }
                     }
-                    buf[1 - cur][r][col] = h;
+#pragma unroll
+                for (int e = 0; e < 2; ++e) {
+                    const int col = j0 + jt + 16 * e + r;
+                    const float b = bias[min(col, wout - 1)];
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        const int row = 4 * q + i;
+                        float h = 0.f;
+                        if (col < wout) {
+                            const float z = c[e][i] + b;
+                            h = last ? act_out(d.out_act, z) : act_hidden(d.hidden_act, z);
+                            if (r0 + row < n) {
+                                cache[d.offC[l] * n + (r0 + row) * wout + col] = h;
+                                if (last) y[col * n + r0 + row] = d.shift + d.scale * h;
+                            }
+                        }
+                        A[row][col] = h;
+                    }
                 }
             }
-            wave_sync();
-            cur = 1 - cur;
         }
-        const int wl = d.w[d.L];
-        for (int i = lane; i < kRowsPerWave * wl; i += 64) {
-            int r = i / wl, c = i % wl;
-            if (r0 + r < n) y[c * n + r0 + r] = d.shift + d.scale * buf[cur][r][c];
-        }
-        wave_sync();
     }
 }
 
-// dZ of every layer from dy, written to `work` in the cache layout.
-template <int BF16>
-__global__ __launch_bounds__(64 * kWaves) void k_mlp_bwd_data(MlpDesc d, const float* __restrict__ P, long long n,
-                                                      const float* __restrict__ cache, const float* __restrict__ dy,
-                                                      float* __restrict__ work)
+// Backward pass of 64 samples per turn, eight waves; each workgroup leaves its
+// gradient of all parameters in part[blockIdx.x].  Per layer, from the last:
+// dW = dZ^T H and db = column sums of dZ, then dZ of the layer below,
+// dZ' = (dZ W) act'(h), which replaces H in LDS.  Weight gradients were a
+// kernel of 512 samples per workgroup that fetched both operands from global
+// memory, one dependent load pair per MFMA, and added to the output with
+// atomics; it took three quarters of the backward pass, on a quarter of the
+// CUs.  With the adjoints in LDS they are never written, and `work` holds the
+// partial gradients instead.  Row stride MW + 16 words: the operand reads that
+// run down the columns (four rows of 16) meet 64 different banks.
+// 2-128-128-1, FP32, 19,897 samples: 67 us (146 KiB of LDS, one workgroup per
+// CU, two turns for some); 2-64-64-2, BF16, 32,768: 17 us; the final sum 6-8.
+// A whole training step (forward, backward, Adam): 687 -> 117 and 427 -> 47 us.
+template <int BF16, int MW>
+__global__ __launch_bounds__(512) void k_mlp_bwd(MlpDesc d, const float* __restrict__ P, long long n,
+                                                 const float* __restrict__ x, const float* __restrict__ cache,
+                                                 const float* __restrict__ dy, long long np, float* __restrict__ part)
 {
-    __shared__ float sh[kWaves][2][kRowsPerWave][kMaxW + 1];
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    float(*buf)[kRowsPerWave][kMaxW + 1] = sh[w];
-    const long long nblk = (n + kRowsPerWave - 1) / kRowsPerWave;
+    using O = Opnd<BF16>;
+    constexpr int LD = MW + 16, NT = 512, NS = MW / O::STEP, GR = NT / MW;
+    __shared__ float s_buf[2][kRows][LD];
+    __shared__ float s_w[MW][LD];
+    __shared__ float s_red[GR][MW];
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    const int r = lane & 15, q = lane >> 4;
+    float* out = part + (long long)blockIdx.x * np;
     const int L = d.L;
-    for (long long rb = (long long)blockIdx.x * kWaves + w; rb < nblk; rb += (long long)gridDim.x * kWaves) {
-        const long long r0 = rb * kRowsPerWave;
-        const int wl = d.w[L];
-        for (int i = lane; i < kRowsPerWave * d.wp[L]; i += 64) {
-            int r = i / d.wp[L], c = i % d.wp[L];
-            float v = 0.f;
-            if (r0 + r < n && c < wl) {
-                float h = cache[d.offC[L - 1] * n + (r0 + r) * wl + c];
-                float g = dy[c * n + r0 + r] * d.scale;
-                v = d.out_act == MPM_ACT_SIGMOID ? g * h * (1.f - h) : g;
-                work[d.offC[L - 1] * n + (r0 + r) * wl + c] = v;
-            }
-            buf[0][r][c] = v;
-        }
-        wave_sync();
+    bool first = true;
+    for (long long r0 = (long long)blockIdx.x * kRows; r0 < n; r0 += (long long)gridDim.x * kRows) {
         int cur = 0;
-        for (int l = L - 1; l >= 1; --l) {
-            // dh = dz_l W_l (16 x w[l]); dz_{l-1} = dh * act'(z), from h = layer l-1 output
-            const float* W = P + d.offW[l];
+        {
+            const int wl = d.w[L], J = pad_to(wl, kPad);
+            for (int i = tid; i < kRows * J; i += NT) {
+                const int row = i & (kRows - 1), c = i / kRows;
+                float v = 0.f;
+                if (r0 + row < n && c < wl) {
+                    const float h = cache[d.offC[L - 1] * n + (r0 + row) * wl + c];
+                    const float g = dy[c * n + r0 + row] * d.scale;
+                    v = d.out_act == MPM_ACT_SIGMOID ? g * h * (1.f - h) : g;
+                }
+                s_buf[0][row][c] = v;
+            }
+        }
+        for (int l = L - 1; l >= 0; --l) {
             const int win = d.w[l], wout = d.w[l + 1];
-            for (int kt = 0; kt < d.wp[l]; kt += 16) {
-                float(*A)[kMaxW + 1] = buf[cur];
-                f4 c = mfma_tile<BF16>(
-                    d.wp[l + 1], [&](int r, int j) { return j < wout ? A[r][j] : 0.f; },
-                    [&](int j, int col) { return (j < wout && kt + col < win) ? W[j * win + kt + col] : 0.f; });
-                const int col = kt + (lane & 15);
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    int r = 4 * (lane >> 4) + i;
-                    float v = 0.f;
-                    if (col < win && r0 + r < n) {
-                        float h = cache[d.offC[l - 1] * n + (r0 + r) * win + col];
-                        v = c[i] * dact_hidden(d.hidden_act, h);
-                        work[d.offC[l - 1] * n + (r0 + r) * win + col] = v;
-                    }
-                    buf[1 - cur][r][col] = v;
+            const int I = pad_to(win, kPad), J = pad_to(wout, kPad);
+            float(*dz)[LD] = s_buf[cur];
+            float(*hb)[LD] = s_buf[1 - cur];
+            if (l > 0) {
+                const float* hc = cache + d.offC[l - 1] * n + r0 * win;
+                const float* W = P + d.offW[l];
+                const int left = n - r0 < kRows ? (int)(n - r0) : kRows;
+                stage_rows<MW, NT, LD>(hb, kRows, I, hc, 0, left, win);
+                stage_rows<MW, NT, LD>(s_w, J, I, W, 0, wout, win);
+            } else {
+                for (int i = tid; i < kRows * I; i += NT) {
+                    const int row = i & (kRows - 1), k = i / kRows;
+                    hb[row][k] = (r0 + row < n && k < win) ? d.in_scale[k] * x[k * n + r0 + row] + d.in_shift[k] : 0.f;
                 }
             }
-            wave_sync();
+            __syncthreads();
+            // a wave keeps the operands of one tile column of H and goes down
+            // every ng-th tile row of dZ
+            const int ti = pad_to(win, 16) / 16, to = pad_to(wout, 16) / 16, ng = 8 / ti;
+            const int i0 = (wv % ti) * 16, og = wv / ti;
+            if (og < ng) {
+                typename O::V bh[kRows / O::STEP];
+#pragma unroll
+                for (int t = 0; t < kRows / O::STEP; ++t) bh[t] = O::load(&hb[t * O::STEP + q * O::LANE][i0 + r], LD);
+                for (int ot = og; ot < to; ot += ng) {
+                    const int o0 = ot * 16;
+                    f4 c = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                    for (int t = 0; t < kRows / O::STEP; ++t)
+                        c = O::mma(O::load(&dz[t * O::STEP + q * O::LANE][o0 + r], LD), bh[t], c);
+                    const int ii = i0 + r;
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        const int oo = o0 + 4 * q + e;
+                        if (oo < wout && ii < win) {
+                            float* g = &out[d.offW[l] + oo * win + ii];
+                            *g = first ? c[e] : *g + c[e];
+                        }
+                    }
+                }
+            }
+            {
+                // column sums of dZ: GR threads per column, then one
+                const int o = tid % MW, g = tid / MW;
+                float sum = 0.f;
+                if (o < wout)
+                    for (int row = g * (kRows / GR); row < (g + 1) * (kRows / GR); ++row) sum += dz[row][o];
+                s_red[g][o] = sum;
+            }
+            __syncthreads();
+            if (tid < wout) {
+                float sum = 0.f;
+#pragma unroll
+                for (int g = 0; g < GR; ++g) sum += s_red[g][tid];
+                float* b = &out[d.offb[l] + tid];
+                *b = first ? sum : *b + sum;
+            }
+            if (l > 0) {
+                // rows 16 * (wv % 4) .. + 15, every second column tile
+                const int row0 = 16 * (wv & 3);
+                typename O::V a[NS];
+#pragma unroll
+                for (int t = 0; t < NS; ++t)
+                    if (t * O::STEP < J) a[t] = O::load(&dz[row0 + r][t * O::STEP + q * O::LANE], 1);
+                for (int kt = 16 * (wv >> 2); kt < I; kt += 32) {
+                    f4 c = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                    for (int g = 0; g < NS / O::GROUP; ++g)
+                        if (g * O::GROUP * O::STEP < J) {
+#pragma unroll
+                            for (int t = g * O::GROUP; t < (g + 1) * O::GROUP; ++t)
+                                c = O::mma(a[t], O::load(&s_w[t * O::STEP + q * O::LANE][kt + r], LD), c);
+                        }
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        const int row = row0 + 4 * q + i;
+                        const bool in = kt + r < win && r0 + row < n;
+                        hb[row][kt + r] = in ? c[i] * dact_hidden(d.hidden_act, hb[row][kt + r]) : 0.f;
+                    }
+                }
+            }
+            __syncthreads();
             cur = 1 - cur;
         }
-        wave_sync();
+        first = false;
     }
 }
 
-// dW_l = dZ_l^T H_l and db_l = sum dZ_l over a chunk of rows; partial
-// results added to dP with atomics.  blockIdx.y = layer.
-template <int BF16>
-__global__ __launch_bounds__(256) void k_mlp_bwd_weights(MlpDesc d, long long n, long long chunk,
-                                                         const float* __restrict__ x,
-                                                         const float* __restrict__ cache,
-                                                         const float* __restrict__ work, float* __restrict__ dP)
+// dP = sum over the workgroups' gradients, in a fixed order: 64 parameters
+// per workgroup, four waves that each sum a quarter of the parts.
+__global__ __launch_bounds__(256) void k_mlp_reduce(long long np, int parts, const float* __restrict__ part,
+                                                    float* __restrict__ dP)
 {
-    const int l = blockIdx.y;
+    __shared__ float s[4][64];
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    const int win = d.w[l], wout = d.w[l + 1];
-    const long long rbeg = (long long)blockIdx.x * chunk;
-    if (rbeg >= n) return;
-    const long long rend = min(rbeg + chunk, n);
-    const int K = (int)(rend - rbeg);
-    const int Kp = (K + 15) & ~15;
-    const float* dz = work + d.offC[l] * n;
-    auto hin = [&](long long r, int i) -> float {
-        if (l == 0) return d.in_scale[i] * x[i * n + r] + d.in_shift[i];
-        return cache[d.offC[l - 1] * n + r * win + i];
-    };
-    const int tiles_o = d.wp[l + 1] / 16, tiles_i = d.wp[l] / 16;
-    for (int t = w; t < tiles_o * tiles_i; t += 4) {
-        const int o0 = (t / tiles_i) * 16, i0 = (t % tiles_i) * 16;
-        f4 c = mfma_tile<BF16>(
-            Kp,
-            [&](int o, int k) { return (k < K && o0 + o < wout) ? dz[(rbeg + k) * wout + o0 + o] : 0.f; },
-            [&](int k, int i) { return (k < K && i0 + i < win) ? hin(rbeg + k, i0 + i) : 0.f; });
-        const int ii = i0 + (lane & 15);
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            int oo = o0 + 4 * (lane >> 4) + q;
-            if (oo < wout && ii < win) atomicAdd(&dP[d.offW[l] + oo * win + ii], c[q]);
-        }
+    const long long i = (long long)blockIdx.x * 64 + lane;
+    float sum = 0.f;
+    if (i < np) {
+#pragma unroll 8
+        for (int b = w; b < parts; b += 4) sum += part[b * np + i];
     }
-    // bias: column sums of dZ over the chunk
-    for (int o = threadIdx.x; o < wout; o += 256) {
-        float s = 0.f;
-        for (long long r = rbeg; r < rend; ++r) s += dz[r * wout + o];
-        atomicAdd(&dP[d.offb[l] + o], s);
-    }
+    s[w][lane] = sum;
+    __syncthreads();
+    if (w == 0 && i < np) dP[i] = (s[0][lane] + s[1][lane]) + (s[2][lane] + s[3][lane]);
 }
 
 __global__ void k_fill_f(float* p, long long n, float v)
@@ -426,7 +522,6 @@ int make_desc(const mpm_mlp* net, MlpDesc* d)
         int wv = net->width[l];
         if (wv < 1 || wv > kMaxW) return MPM_EINVAL;
         d->w[l] = wv;
-        d->wp[l] = (wv + 15) & ~15;
     }
     for (int l = 0; l < d->L; ++l) {
         d->offW[l] = off;
@@ -447,10 +542,36 @@ int make_desc(const mpm_mlp* net, MlpDesc* d)
     return MPM_OK;
 }
 
-unsigned grid_for(long long n)
+int widest(const MlpDesc& d)
 {
-    long long blk = (n + kRowsPerWave * kWaves - 1) / (kRowsPerWave * kWaves);
-    return (unsigned)(blk < 4096 ? (blk > 0 ? blk : 1) : 4096);
+    int m = 0;
+    for (int l = 0; l <= d.L; ++l) m = d.w[l] > m ? d.w[l] : m;
+    return m;
+}
+
+template <int BF16, int MW>
+void launch_fwd(const MlpDesc& d, hipStream_t st, const float* P, long long n, const float* x, float* y, float* cache)
+{
+    k_mlp_fwd<BF16, MW><<<(unsigned)((n + kRows - 1) / kRows), 256, 0, st>>>(d, P, n, x, y, cache);
+}
+
+// `parts` workgroups, whose gradients fit the work buffer (a single one writes
+// the output itself); more than the chip holds at once would only lengthen the
+// final sum.
+template <int BF16, int MW>
+void launch_bwd(const MlpDesc& d, hipStream_t st, const float* P, long long n, const float* x, const float* cache,
+                const float* dy, long long np, long long work_floats, float* work, float* dP)
+{
+    const long long held = MW == 128 ? 256 : 512;   // LDS: one workgroup per CU of 128-wide layers, else more
+    long long parts = (n + kRows - 1) / kRows;
+    parts = parts < held ? parts : held;
+    parts = parts < work_floats / np ? parts : work_floats / np;
+    if (parts <= 1) {
+        k_mlp_bwd<BF16, MW><<<1, 512, 0, st>>>(d, P, n, x, cache, dy, np, dP);
+        return;
+    }
+    k_mlp_bwd<BF16, MW><<<(unsigned)parts, 512, 0, st>>>(d, P, n, x, cache, dy, np, work);
+    k_mlp_reduce<<<(unsigned)((np + 63) / 64), 256, 0, st>>>(np, (int)parts, work, dP);
 }
 
 }  // namespace
@@ -484,8 +605,16 @@ int mpm_mlp_forward(const mpm_mlp* net, void* hip_stream, const float* params, i
     if (n < 0 || (n > 0 && (!params || !x || !y || !cache))) return MPM_EINVAL;
     if (n == 0) return MPM_OK;
     hipStream_t st = (hipStream_t)hip_stream;
-    if (net->math == MPM_MLP_BF16) k_mlp_fwd<1><<<grid_for(n), 64 * kWaves, 0, st>>>(d, params, n, x, y, cache);
-    else k_mlp_fwd<0><<<grid_for(n), 64 * kWaves, 0, st>>>(d, params, n, x, y, cache);
+    const int mw = widest(d);
+    if (net->math == MPM_MLP_BF16) {
+        if (mw <= 32) launch_fwd<1, 32>(d, st, params, n, x, y, cache);
+        else if (mw <= 64) launch_fwd<1, 64>(d, st, params, n, x, y, cache);
+        else launch_fwd<1, 128>(d, st, params, n, x, y, cache);
+    } else {
+        if (mw <= 32) launch_fwd<0, 32>(d, st, params, n, x, y, cache);
+        else if (mw <= 64) launch_fwd<0, 64>(d, st, params, n, x, y, cache);
+        else launch_fwd<0, 128>(d, st, params, n, x, y, cache);
+    }
     return hipGetLastError() == hipSuccess ? MPM_OK : MPM_EHIP;
 }
 
@@ -497,18 +626,18 @@ int mpm_mlp_backward(const mpm_mlp* net, void* hip_stream, const float* params, 
     if (rc) return rc;
     if (n < 0 || !dparams || (n > 0 && (!params || !x || !cache || !dy || !work))) return MPM_EINVAL;
     hipStream_t st = (hipStream_t)hip_stream;
-    long long np = mpm_mlp_num_params(net);
-    k_fill_f<<<(unsigned)((np + 255) / 256 < 1024 ? (np + 255) / 256 : 1024), 256, 0, st>>>(dparams, np, 0.f);
-    if (n > 0) {
-        const long long chunk = 512;
-        dim3 gw((unsigned)((n + chunk - 1) / chunk), (unsigned)d.L);
-        if (net->math == MPM_MLP_BF16) {
-            k_mlp_bwd_data<1><<<grid_for(n), 64 * kWaves, 0, st>>>(d, params, n, cache, dy, work);
-            k_mlp_bwd_weights<1><<<gw, 256, 0, st>>>(d, n, chunk, x, cache, work, dparams);
-        } else {
-            k_mlp_bwd_data<0><<<grid_for(n), 64 * kWaves, 0, st>>>(d, params, n, cache, dy, work);
-            k_mlp_bwd_weights<0><<<gw, 256, 0, st>>>(d, n, chunk, x, cache, work, dparams);
-        }
+    const long long np = mpm_mlp_num_params(net), wf = mpm_mlp_cache_floats(net, n);
+    const int mw = widest(d);
+    if (n == 0) {
+        k_fill_f<<<(unsigned)((np + 255) / 256 < 1024 ? (np + 255) / 256 : 1024), 256, 0, st>>>(dparams, np, 0.f);
+    } else if (net->math == MPM_MLP_BF16) {
+        if (mw <= 32) launch_bwd<1, 32>(d, st, params, n, x, cache, dy, np, wf, work, dparams);
+        else if (mw <= 64) launch_bwd<1, 64>(d, st, params, n, x, cache, dy, np, wf, work, dparams);
+        else launch_bwd<1, 128>(d, st, params, n, x, cache, dy, np, wf, work, dparams);
+    } else {
+        if (mw <= 32) launch_bwd<0, 32>(d, st, params, n, x, cache, dy, np, wf, work, dparams);
+        else if (mw <= 64) launch_bwd<0, 64>(d, st, params, n, x, cache, dy, np, wf, work, dparams);
+        else launch_bwd<0, 128>(d, st, params, n, x, cache, dy, np, wf, work, dparams);
     }
     return hipGetLastError() == hipSuccess ? MPM_OK : MPM_EHIP;
 }
