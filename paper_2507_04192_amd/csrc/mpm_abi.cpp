@@ -135,7 +135,7 @@ Geo make_geo(const mpm_config& c)
 }
 
 struct Layout {
-    size_t st[2], pid[2], eps[2], key, perm, tmp, tmpk, count, tile_off, tile_slot, active, part, meta, status;
+    size_t st[2], pid[2], eps[2], key, perm, tmp, tmpk, count[2], range[2], tile_perm, tile_key, tile_off, tile_slot, active, part, meta, status;
     size_t part_grid, gv, gmass, gvo;
     size_t inv, loss, box_sum, box_cnt, box_coef;
     size_t ckpt, ckpt_pid, tape, tape_pid, adj[2], mid, gtape, amu;
@@ -172,7 +172,12 @@ Layout make_layout(const mpm_config& c, const Geo& g, int64_t cap, int tape_step
     L.perm = take(ucap * 4);
     L.tmp = take(ucap * 4);
     L.tmpk = take(ucap * 4);
-    L.count = take((size_t)g.ntiles * 4);
+    // 2-D steps alternate between two sets of counts and of the tiles' ranges
+    for (int b = 0; b < 2; ++b) L.count[b] = (b == 0 || c.dim == 2) ? take((size_t)g.ntiles * 4) : 0;
+    for (int b = 0; b < 2; ++b) L.range[b] = c.dim == 2 ? take((size_t)g.ntiles * 8) : 0;
+    const bool rows = c.dim == 2 && g.ntiles <= kSmallTiles;
+    L.tile_perm = rows ? take((size_t)g.ntiles * kTileRow * 4) : 0;
+    L.tile_key = rows ? take((size_t)g.ntiles * kTileRow * 4) : 0;
     L.tile_off = take((size_t)g.ntiles * 4);
     L.tile_slot = take((size_t)g.ntiles * 4);
     L.active = take((size_t)g.ntiles * sizeof(ActiveTile));
@@ -338,7 +343,15 @@ int mpm_bind_workspace(mpm_ctx* c, void* dev_ptr, size_t bytes, int64_t n_partic
     c->perm = (int32_t*)(b + L.perm);
     c->tmp = (int32_t*)(b + L.tmp);
     c->tmpk = (int32_t*)(b + L.tmpk);
-    c->count = (int32_t*)(b + L.count);
+    for (int i = 0; i < 2; ++i) {
+        c->count[i] = (int32_t*)(b + L.count[i]);
+        c->range[i] = (int2*)(b + L.range[i]);
+    }
+    const bool rows = c->cfg.dim == 2 && c->geo.ntiles <= kSmallTiles;
+    c->tile_perm = rows ? (int32_t*)(b + L.tile_perm) : nullptr;
+    c->tile_key = rows ? (int32_t*)(b + L.tile_key) : nullptr;
+    c->turn = 0;
+    c->ranges_known = false;
     c->tile_off = (int32_t*)(b + L.tile_off);
     c->tile_slot = (int32_t*)(b + L.tile_slot);
     c->active = (ActiveTile*)(b + L.active);

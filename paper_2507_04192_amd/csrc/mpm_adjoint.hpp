@@ -939,14 +939,6 @@ struct Adjoint {
         return MPM_OK;
     }
 
-    static void keys_of(mpm_ctx* c, const PView<T>& v)
-    {
-        hipStream_t st = c->stream;
-        k_fill<int><<<std::min<long long>(nblocks(c->geo.ntiles), 4096), kBlock, 0, st>>>(c->count, c->geo.ntiles, 0);
-        Phys<T> P = make_phys<T>(c, 0.0);
-        k_keys<T, D><<<nblocks(c->N), kBlock, 0, st>>>(c->geo, P, v, c->N, c->key, c->count);
-    }
-
     // The grid-tape record of step i of the segment in tape slot q.
     static typename S::StepBufs rec_bufs(const mpm_ctx* c, int q, int i)
     {
@@ -1141,7 +1133,7 @@ struct Adjoint {
             if (!on_tape) {
                 int rc = copy_state(c, tape(c, 0, 0), ckpt(c, seg));
                 if (rc) return rc;
-                keys_of(c, tape(c, 0, 0));
+                S::new_keys(c, tape(c, 0, 0));
                 for (int t = t0; t < t1; ++t)
                     S::template step_views<MAT, XF>(c, Pk, tape(c, 0, t - t0), tape(c, 0, t - t0 + 1),
                                                     rec_bufs(c, 0, t - t0));

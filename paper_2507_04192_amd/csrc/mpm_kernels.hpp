@@ -16,6 +16,8 @@
 //                               APIC C, velocity gradient, position, then the
 //                               constitutive update; writes the state in the
 //                               new sorted order and counts the next keys
+// In 2-D, 1 to 3 are one kernel (sort_p2g2) wherever the previous step's
+// layout is known and the grid is small, and 4 is done by g2p.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -41,8 +43,8 @@ constexpr int kSortCap = 1024;   // particles per tile sorted in LDS (larger: in
 // force): binary32 then uses four waves per tile.
 template <class T, bool FL = false> constexpr int kP2GBlock = sizeof(T) == 4 ? (FL ? 256 : 128) : 64;
 template <class T, bool FL = false> constexpr int kP2GWGs = kTileWGs * kBlock / kP2GBlock<T, FL>;
-// threads of a G2P workgroup (binary64: smaller groups, measured faster)
-template <class T> constexpr int kG2PBlock = sizeof(T) == 8 ? 128 : 256;
+// threads of a G2P workgroup (3-D binary64: smaller groups, measured faster)
+template <class T, int D> constexpr int kG2PBlock = sizeof(T) == 8 && D == 3 ? 128 : 256;
 // G2P loads the next tile's node block while it works on the current one
 // (binary64: measured faster; binary32: slower)
 template <class T> constexpr bool kG2PPrefetch = sizeof(T) == 8;
@@ -131,7 +133,8 @@ template <int Unused = 0>
 __global__ __launch_bounds__(kBlock) void k_scan_down(const int* __restrict__ count, int ntiles,
                                                       const int* __restrict__ part,
                                                       int* __restrict__ tile_off, int* __restrict__ tile_slot,
-                                                      ActiveTile* __restrict__ active, int* __restrict__ meta)
+                                                      ActiveTile* __restrict__ active, int* __restrict__ meta,
+                                                     int2* __restrict__ range, int* __restrict__ count_next)
 {
     // prefix of the earlier chunks
     int ps = 0, pa = 0;
@@ -160,6 +163,8 @@ __global__ __launch_bounds__(kBlock) void k_scan_down(const int* __restrict__ co
         int t = t0 + k;
         if (t < ntiles) {
             tile_off[t] = off;
+            if (range) range[t] = make_int2(off, c[k]);
+            if (count_next) count_next[t] = 0;
             if (c[k] > 0) {
                 tile_slot[t] = slot;
                 ActiveTile e;
@@ -224,6 +229,7 @@ __global__ __launch_bounds__(kBlock) void k_keys(Geo g, Phys<T> P, PView<T> cur,
 {
     long long j = (long long)blockIdx.x * kBlock + threadIdx.x;
     bool valid = j < N;
+
     int k = 0;
     if (valid) {
         T xp[D];
@@ -685,6 +691,345 @@ __global__ __launch_bounds__((kP2GBlock<T, FL>)) __attribute__((amdgpu_waves_per
 }
 
 // ---------------------------------------------------------------------------
+// 2-D: the sort and P2G of a tile in one kernel
+//
+// A 2-D step is short of work, not of bandwidth: 8,192 particles are 40 tiles
+// on 256 CUs, and a step was five launches (scan, bucket, P2G, grid, G2P), each
+// a chain of dependent memory round trips of about a microsecond.  Two launches
+// remain: this kernel, and G2P, which forms its tile's nodal velocities itself.
+//
+// Where the previous step's layout is known (GATHER), a tile's particles are
+// found without a scan and a scatter over the grid.  The previous G2P left the
+// particles of every tile in one range of slots and their new keys beside them,
+// and a particle moves at most to a neighbouring tile (a cell is the limit of a
+// step, a tile is eight), so a workgroup reads the keys of the nine ranges
+// around its tile and picks its own; its offset is the sum of the counts of
+// the tiles before it, at most kSmallTiles of them.  The first keys of a range
+// are also kept in a row per tile, whose place is known without the range, so
+// counts, ranges and keys come in one round trip (G2P likewise finds its
+// particles in a row of perm).  A workgroup that finds
+// fewer than its tile's count (a particle moved further, in a step beyond the
+// CFL limit) reads all keys.  The order inside the tile is by cell and previous
+// slot, whatever order they were found in, so both ways of finding give the
+// same permutation and, from there, the same bits.
+// ---------------------------------------------------------------------------
+
+// Threads per tile where tiles are many and waves, not latency, are short
+// (524,288 particles, binary64: 256 threads 74.7 us a step, 128 68.8, 64 68.7;
+// 131,072: 37.8, 36.1, 38.6).
+constexpr int kSortMany2 = 128;
+
+// The previous step's layout and this step's, for kernels that gather.
+struct Ranges2 {
+    const int* count;        // particles per tile, by the current keys
+    int* count_next;         // cleared here for this step's G2P
+    const int2* range;       // previous sort: first slot and number of each tile's particles
+    int2* range_next;        // this sort
+    const int* key;
+    const int* tile_key;     // the first kTileRow keys of every tile's range, a row per tile
+    int* tile_perm;          // the same of perm (null: not kept)
+    long long N;
+};
+
+// Tile of a workgroup when there is one per tile: a contiguous chunk of tiles
+// on each XCD (workgroup b runs on XCD b % 8).  -1 past the end.
+__device__ __forceinline__ int tile_of_block(int ntiles)
+{
+    const int chunk = (ntiles + 7) / 8;
+    const int lb = blockIdx.x / 8, t = (blockIdx.x % 8) * chunk + lb;
+    return lb < chunk && t < ntiles ? t : -1;
+}
+
+// One tile per workgroup of NW waves (four; two where tiles are many).  After
+// the sort, wave w takes the particles of rank w, w + NW, ... of every cell,
+// lane = cell: a lane sums its
+// particles in registers (they all hit the same nine nodes), then adds to its
+// wave's own copy of the tile's node block, lanes on distinct nodes per offset;
+// the copies are summed in a fixed order.  With four particles per cell a wave
+// of four has one round, where one wave (binary64, LDS atomics) had four.
+// A step of the 2-D dam-break, 8,192 / 32,768 / 73,728 particles: binary32
+// 24.1 / 25.6 / 28.5 -> 13.8 / 17.6 / 18.6 us, binary64 28.8 / 31.0 / 35.1 ->
+// 15.1 / 20.2 / 22.6.  This kernel takes 7.7 us of it at 8,192 particles and
+// G2P 6.2; what bounds both is the chain of launch, two memory round trips,
+// LDS phases and the drain of the stores.
+template <class T, int MAT, bool FL, bool GATHER, int NT>
+__global__ __launch_bounds__(NT) void k_sort_p2g2(Geo g, Phys<T> P, Ranges2 rg, int* __restrict__ meta,
+                                                           ActiveTile* __restrict__ active, int* __restrict__ tile_slot,
+                                                           int* __restrict__ tmp, int* __restrict__ tmpk, PView<T> cur,
+                                                           int* __restrict__ perm, T* __restrict__ part)
+{
+    constexpr int D = 2, TE = TileShape<D>::TE, NB = TileShape<D>::NB, NW = NT / 64;
+    constexpr int NV = FL ? 2 * D + 1 : D + 1;   // node values per block node
+    constexpr int NK = 9;
+    __shared__ T s_node[NW][NV][NB];
+    __shared__ int s_cnt[64], s_off[64], s_cur[64], s_roff[64];
+    __shared__ unsigned long long s_rmask[64];
+    __shared__ int s_unord[kSortCap], s_sorted[kSortCap];
+    __shared__ unsigned char s_ucell[kSortCap];
+    __shared__ int s_sum[2][NW], s_first[9], s_num[9], s_found;
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    const int n_active = GATHER ? 0 : meta[0];
+    constexpr int U = GATHER ? 9 : (kSortCap + NT - 1) / NT;
+    static_assert(!GATHER || kTileRow == NT, "a thread holds one entry of each tile's row");
+    for (int it = 0;; ++it) {
+        ActiveTile at;
+        int cj[U], cc[U];   // candidates: slot, and key, then cell or -1
+        if (tid < 64) {
+            s_cnt[tid] = 0;
+            s_cur[tid] = 0;
+        }
+        if constexpr (GATHER) {
+            const int t = it == 0 ? tile_of_block(g.ntiles) : -1;
+            if (t < 0) break;
+            const int own = rg.count[t];
+            const int ty = t / g.ntile[0], tx = t - ty * g.ntile[0];
+            // the row of a neighbour outside the grid is read as the tile's own and not used
+#pragma unroll
+            for (int q = 0; q < U; ++q) {
+                const int nx = tx + q % 3 - 1, ny = ty + q / 3 - 1;
+                const bool in = nx >= 0 && ny >= 0 && nx < g.ntile[0] && ny < g.ntile[1];
+                cc[q] = rg.tile_key[(in ? ny * g.ntile[0] + nx : t) * kTileRow + tid];
+            }
+            if (tid < 9) {
+                const int nx = tx + tid % 3 - 1, ny = ty + tid / 3 - 1;
+                const bool in = nx >= 0 && ny >= 0 && nx < g.ntile[0] && ny < g.ntile[1];
+                const int2 r = in ? rg.range[ny * g.ntile[0] + nx] : make_int2(0, 0);
+                s_first[tid] = r.x;
+                s_num[tid] = r.y;
+            }
+            int s = 0, a = 0;
+            for (int i = tid; i < t; i += NT) {
+                const int c = rg.count[i];
+                s += c;
+                a += c > 0;
+            }
+#pragma unroll
+            for (int o = 32; o > 0; o >>= 1) {
+                s += __shfl_xor(s, o);
+                a += __shfl_xor(a, o);
+            }
+            if (lane == 0) {
+                s_sum[0][w] = s;
+                s_sum[1][w] = a;
+            }
+            __syncthreads();
+            s = a = 0;
+#pragma unroll
+            for (int i = 0; i < NW; ++i) {
+                s += s_sum[0][i];
+                a += s_sum[1][i];
+            }
+            at.tile = t;
+            at.off = s;
+            at.cnt = own;
+            at.pad = 0;
+            if (tid == 0) {
+                tile_slot[t] = own > 0 ? a : -1;
+                if (own > 0) active[a] = at;
+                rg.range_next[t] = make_int2(s, own);
+                rg.count_next[t] = 0;
+                if (t == g.ntiles - 1) {
+                    meta[0] = a + (own > 0);
+                    meta[1] = s + own;
+                }
+            }
+            if (own == 0) break;
+        } else {
+            const int e = tile_entry(it, n_active);
+            if (e < 0) break;
+            at = active[e];
+            __syncthreads();
+        }
+        const bool in_lds = at.cnt <= kSortCap;
+        // Candidates: the keys of the nine ranges (or all keys), or the tile's
+        // bucketed entries.  A batch is U per thread, loaded together (of each
+        // range kTileRow); where one batch holds them all it stays in registers
+        // from the histogram to the placement.
+        bool all = false;
+        auto batch = [&](int u0) {
+            if constexpr (GATHER) {
+#pragma unroll
+                for (int q = 0; q < U; ++q) {
+                    const int u = all ? u0 * U + q * NT + tid : u0 + tid;
+                    cj[q] = all ? (u < (int)rg.N ? u : -1) : (u < s_num[q] ? s_first[q] + u : -1);
+                }
+                if (u0 > 0 || all)
+#pragma unroll
+                    for (int q = 0; q < U; ++q) cc[q] = cj[q] >= 0 ? rg.key[cj[q]] : -1;
+#pragma unroll
+                for (int q = 0; q < U; ++q) cc[q] = cj[q] >= 0 && (cc[q] >> 6) == at.tile ? cc[q] & 63 : -1;
+            } else {
+#pragma unroll
+                for (int q = 0; q < U; ++q) {
+                    const int u = u0 * U + q * NT + tid;
+                    cc[q] = u < at.cnt ? tmpk[at.off + u] & 63 : -1;
+                    cj[q] = u < at.cnt ? tmp[at.off + u] : -1;
+                }
+            }
+        };
+        // entries to go through, in units of U
+        int total = (at.cnt + U - 1) / U;
+        if constexpr (GATHER) {
+            total = 0;
+#pragma unroll
+            for (int b = 0; b < 9; ++b) total = max(total, s_num[b]);
+        }
+        for (;;) {
+            for (int u0 = 0; u0 < total; u0 += NT) {
+                batch(u0);
+#pragma unroll
+                for (int q = 0; q < U; ++q)
+                    if (cc[q] >= 0) atomicAdd(&s_cnt[cc[q]], 1);
+            }
+            __syncthreads();
+            if (w == 0) {
+                const int v = s_cnt[lane];
+                int inc = v;
+#pragma unroll
+                for (int o = 1; o < 64; o <<= 1) {
+                    const int t = __shfl_up(inc, o);
+                    if (lane >= o) inc += t;
+                }
+                s_off[lane] = inc - v;
+                if (lane == 63) s_found = inc;
+                // rank table: cells with more than q particles, earlier ranks' count
+                int run = 0;
+                for (int q = 0; q < 64; ++q) {
+                    const unsigned long long m = __ballot(v > q);
+                    if (!m) break;
+                    if (lane == 0) {
+                        s_rmask[q] = m;
+                        s_roff[q] = run;
+                    }
+                    run += __popcll(m);
+                }
+            }
+            __syncthreads();
+            if (!GATHER || all || s_found == at.cnt) break;
+            __syncthreads();
+            if (tid < 64) s_cnt[tid] = 0;
+            all = true;
+            total = (int)((rg.N + U - 1) / U);
+            __syncthreads();
+        }
+        // cell-major placement, then the rank inside the cell by previous slot
+        int* unord = perm + at.off;   // crowded tiles
+        for (int u0 = 0; u0 < total; u0 += NT) {
+            if (total > NT) {
+                if (GATHER && u0 == 0 && !all)
+#pragma unroll
+                    for (int q = 0; q < U; ++q) cc[q] = u0 + tid < s_num[q] ? rg.key[s_first[q] + tid] : -1;
+                batch(u0);
+            }
+#pragma unroll
+            for (int q = 0; q < U; ++q)
+                if (cc[q] >= 0) {
+                    const int u = s_off[cc[q]] + atomicAdd(&s_cur[cc[q]], 1);
+                    if (in_lds) {
+                        s_unord[u] = cj[q];
+                        s_ucell[u] = (unsigned char)cc[q];
+                    } else {
+                        unord[u] = cj[q];
+                    }
+                }
+        }
+        if (in_lds) {
+            __syncthreads();
+            for (int u = tid; u < at.cnt; u += NT) {
+                const int c = s_ucell[u], j = s_unord[u];
+                const int o = s_off[c], n = s_cnt[c], last = o + n - 1;
+                int rank = 0;
+                for (int q = 0; q < n; q += 4) {
+                    int e[4];
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) e[i] = s_unord[min(o + q + i, last)];
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) rank += (q + i < n && e[i] < j) ? 1 : 0;
+                }
+                s_sorted[rank_major_pos(c, rank, s_rmask, s_roff, s_cnt)] = j;
+            }
+            __syncthreads();
+            for (int k = tid; k < at.cnt; k += NT) perm[at.off + k] = s_sorted[k];
+            if (rg.tile_perm && tid < at.cnt) rg.tile_perm[at.tile * kTileRow + tid] = s_sorted[tid];   // NT = a row
+        } else {
+            __threadfence_block();
+            __syncthreads();
+            for (int k = tid; k < at.cnt; k += NT) {
+                int lo = 0;
+#pragma unroll
+                for (int step = 32; step >= 1; step >>= 1)
+                    if (lo + step < 64 && s_off[lo + step] <= k) lo += step;
+                const int j = unord[k], o = s_off[lo], n = s_cnt[lo];
+                int rank = 0;
+                for (int q = 0; q < n; ++q) rank += unord[o + q] < j;
+                tmp[at.off + rank_major_pos(lo, rank, s_rmask, s_roff, s_cnt)] = j;
+            }
+            __threadfence_block();
+            __syncthreads();
+            const volatile int* rm = tmp + at.off;
+            for (int k = tid; k < at.cnt; k += NT) unord[k] = rm[k];
+            if (rg.tile_perm) rg.tile_perm[at.tile * kTileRow + tid] = rm[tid];   // crowded: more than a row
+            __threadfence_block();
+            __syncthreads();
+        }
+        const int* sorted = in_lds ? s_sorted : (perm + at.off);
+        int tc[3];
+        tile_coords(g, at.tile, tc);
+        // opaque to the compiler for this tile, so that what is derived from the
+        // cell is not hoisted out of the tile loop into registers
+        int cl = lane;
+        asm volatile("" : "+v"(cl));
+        const int lb[3] = {cl % TE, cl / TE, 0};
+        const int gb[3] = {tc[0] * TE + lb[0] - g.G, tc[1] * TE + lb[1] - g.G, 0};
+        const int mycnt = s_cnt[cl];
+        T acc[NK][NV];
+#pragma unroll
+        for (int k = 0; k < NK; ++k)
+#pragma unroll
+            for (int q = 0; q < NV; ++q) acc[k][q] = T(0);
+        P2GIn<T, D, MAT> nx;
+        if (w < mycnt) nx.load(cur, sorted[rank_major_pos(cl, w, s_rmask, s_roff, s_cnt)]);
+        T(*node)[NB] = s_node[w];
+        for (int i = lane; i < NV * NB; i += 64) (&node[0][0])[i] = T(0);
+        for (int r = w; r < mycnt; r += NW) {
+            const P2GIn<T, D, MAT> in = nx;
+            if (r + NW < mycnt) nx.load(cur, sorted[rank_major_pos(cl, r + NW, s_rmask, s_roff, s_cnt)]);
+            p2g_particle<T, D, MAT, 0, D>(P, in, lb, gb,
+                                          [&](int k, int, const T* fx, T mw, const T* U, const T* V, const T* W,
+                                              const T* Uq) {
+                acc[k][0] = fma(fx[0], mw, acc[k][0]);
+#pragma unroll
+                for (int a = 0; a < D; ++a) {
+                    acc[k][1 + a] = fma(fx[2], W[a], fma(fx[1], V[a], fma(fx[0], U[a], acc[k][1 + a])));
+                    if constexpr (FL) acc[k][1 + D + a] = fma(fx[1], V[a], fma(fx[0], Uq[a], acc[k][1 + D + a]));
+                }
+            });
+        }
+        wave_sync();
+#pragma unroll
+        for (int k = 0; k < NK; ++k) {
+            const int n = block_node<D>(lb, k);
+            T cv[NV];
+#pragma unroll
+            for (int q = 0; q < NV; ++q) cv[q] = node[q][n];
+#pragma unroll
+            for (int q = 0; q < NV; ++q) node[q][n] = cv[q] + acc[k][q];
+            wave_sync();
+        }
+        __syncthreads();
+        T* dst = part + (long long)at.tile * NV * NB;
+        for (int i = tid; i < NV * NB; i += NT) {
+            T s = (&s_node[0][0][0])[i];
+#pragma unroll
+            for (int k = 1; k < NW; ++k) s += (&s_node[k][0][0])[i];
+            dst[i] = s;
+        }
+        if constexpr (GATHER) break;
+        __syncthreads();
+    }
+}
+
+// ---------------------------------------------------------------------------
 // Grid update over the node blocks of the active tiles.  A node shared by
 // several blocks is handled by exactly one of them: the first active tile
 // among its candidates, own tile first.  Its mass and momentum are the sum of
@@ -727,10 +1072,39 @@ __device__ __forceinline__ int node_blocks(const Geo& g, const int I[3], const i
     return des;
 }
 
+// Velocity of a node of mass m > 0 and momentum p after the grid update, the
+// walls and the resting obstacles (Sec. 4.2.1); vt: before the walls.
+template <class T, int D>
+__device__ __forceinline__ void node_velocity(const Geo& g, const Phys<T>& P, const int I[3], T m, const T p[D], T v[D],
+                                              T vt[D])
+{
+#pragma unroll
+    for (int a = 0; a < D; ++a) vt[a] = v[a] = p[a] / m + P.dt * P.g[a];
+#pragma unroll
+    for (int a = 0; a < D; ++a) {
+        int ip = I[a] - g.G;
+        if (ip <= 0) {
+            T mu = P.wall_mu[2 * a];
+            if (a == D - 1 && P.floor_mu) {
+                int fx = min(I[0], g.box[0] - 1);
+                int fi = (D == 3) ? min(I[1], g.box[1] - 1) * P.floor_stride + fx : fx;
+                mu = P.floor_mu[fi];
+            }
+            wall_node<T, D>(P.wall_mode[2 * a], mu, a, T(-1), v);
+        }
+        if (ip >= g.n[a]) wall_node<T, D>(P.wall_mode[2 * a + 1], P.wall_mu[2 * a + 1], a, T(1), v);
+    }
+    if (P.n_obst > 0) {
+        double xi[D];
+#pragma unroll
+        for (int a = 0; a < D; ++a) xi[a] = double(I[a] - g.G) * P.obst_h;
+        obstacle_node<T, D>(P, xi, v);
+    }
+}
+
 // With FL (FLIP) the partial blocks also hold the momentum without the
 // internal force, and gvo receives the velocity before the update,
-// v_i^n = that / m_i (0 where m_i = 0).  Resting obstacles (Sec. 4.2.1) act
-// after the walls.
+// v_i^n = that / m_i (0 where m_i = 0).
 template <class T, int D, bool FL>
 __global__ __launch_bounds__(kGridBlock) void k_grid(Geo g, Phys<T> P, const int* __restrict__ meta,
                                                  const ActiveTile* __restrict__ active,
@@ -781,39 +1155,13 @@ __global__ __launch_bounds__(kGridBlock) void k_grid(Geo g, Phys<T> P, const int
             }
             if (des != tile) continue;
             long long node = node_index(g, I[0], I[1], I[2]);
-            T v[D];
+            T v[D], vt[D];
 #pragma unroll
-            for (int a = 0; a < D; ++a) v[a] = T(0);
-            if (m > T(0)) {
+            for (int a = 0; a < D; ++a) v[a] = vt[a] = T(0);
+            if (m > T(0)) node_velocity<T, D>(g, P, I, m, p, v, vt);
+            if (gvt)
 #pragma unroll
-                for (int a = 0; a < D; ++a) v[a] = p[a] / m + P.dt * P.g[a];
-                if (gvt)
-#pragma unroll
-                    for (int a = 0; a < D; ++a) gvt[a * g.NN + node] = v[a];
-#pragma unroll
-                for (int a = 0; a < D; ++a) {
-                    int ip = I[a] - g.G;
-                    if (ip <= 0) {
-                        T mu = P.wall_mu[2 * a];
-                        if (a == D - 1 && P.floor_mu) {
-                            int fx = min(I[0], g.box[0] - 1);
-                            int fi = (D == 3) ? min(I[1], g.box[1] - 1) * P.floor_stride + fx : fx;
-                            mu = P.floor_mu[fi];
-                        }
-                        wall_node<T, D>(P.wall_mode[2 * a], mu, a, T(-1), v);
-                    }
-                    if (ip >= g.n[a]) wall_node<T, D>(P.wall_mode[2 * a + 1], P.wall_mu[2 * a + 1], a, T(1), v);
-                }
-                if (P.n_obst > 0) {
-                    double xi[D];
-#pragma unroll
-                    for (int a = 0; a < D; ++a) xi[a] = double(I[a] - g.G) * P.obst_h;
-                    obstacle_node<T, D>(P, xi, v);
-                }
-            } else if (gvt) {
-#pragma unroll
-                for (int a = 0; a < D; ++a) gvt[a * g.NN + node] = T(0);
-            }
+                for (int a = 0; a < D; ++a) gvt[a * g.NN + node] = vt[a];
 #pragma unroll
             for (int a = 0; a < D; ++a) gv[a * g.NN + node] = v[a];
             if constexpr (FL)
@@ -849,56 +1197,165 @@ __device__ __forceinline__ void g2p_block_load(const Geo& g, const T* __restrict
     }
 }
 
+// 2-D: what G2P needs to form its tile's nodal velocities from P2G's partial
+// blocks, and where they are kept.
+template <class T>
+struct Nodes2 {
+    const T* part;          // partial block of each tile (indexed by tile)
+    const int* tile_slot;
+    const int2* range;      // one workgroup per tile where given, else over the active list
+    const int* tile_perm;   // with range: the first kTileRow entries of each tile's perm
+    int* tile_key;          // with range: the same of the new keys
+    T *gv, *gmass, *gvt, *gvo;
+};
+
+// The node update of k_grid for the 100 nodes of one tile's block, one per
+// thread, into LDS.  A node shared by several tiles is formed by each of them
+// from the same sums in the same order (1.56 updates per node); its owner
+// stores it.  Partial blocks are loaded before it is known which tiles are
+// active: one round trip.
+template <class T, bool FL>
+__device__ __forceinline__ void node_block2(const Geo& g, const Phys<T>& P, const Nodes2<T>& nd, int tile, int tid,
+                                            T (&s_v)[2][TileShape<2>::NB], T (*s_vo)[FL ? TileShape<2>::NB : 1])
+{
+    constexpr int D = 2, TE = TileShape<D>::TE, BE = TileShape<D>::BE, NB = TileShape<D>::NB, NC = 4;
+    constexpr int NV = FL ? 2 * D + 1 : D + 1;
+    if (tid >= NB) return;
+    int tc[3];
+    tile_coords(g, tile, tc);
+    const int l[2] = {tid % BE, tid / BE};
+    int I[3] = {0, 0, 0}, own[2];
+    bool down[2];
+#pragma unroll
+    for (int a = 0; a < D; ++a) {
+        I[a] = tc[a] * TE + l[a];
+        own[a] = I[a] / TE;
+        down[a] = (I[a] % TE < 2) && own[a] >= 1;
+    }
+    int tl[NC], slot[NC];
+    T val[NC][NV];
+#pragma unroll
+    for (int msk = 0; msk < NC; ++msk) {
+        const int cx = own[0] - (msk & 1), cy = own[1] - (msk >> 1);
+        const bool ok = (!(msk & 1) || down[0]) && (!(msk >> 1) || down[1]) && cx < g.ntile[0] && cy < g.ntile[1];
+        tl[msk] = ok ? cy * g.ntile[0] + cx : -1;
+        const int src = ok ? tl[msk] : tile;
+        const int li = ok ? (I[1] - cy * TE) * BE + I[0] - cx * TE : 0;
+        slot[msk] = nd.tile_slot[src];
+        const T* p = nd.part + (long long)src * NV * NB + li;
+#pragma unroll
+        for (int q = 0; q < NV; ++q) val[msk][q] = p[q * NB];
+    }
+    int des = -1;
+    T sum[NV];
+#pragma unroll
+    for (int q = 0; q < NV; ++q) sum[q] = T(0);
+#pragma unroll
+    for (int msk = 0; msk < NC; ++msk)
+        if (tl[msk] >= 0 && slot[msk] >= 0) {
+            if (des < 0) des = tl[msk];
+#pragma unroll
+            for (int q = 0; q < NV; ++q) sum[q] += val[msk][q];
+        }
+    const T m = sum[0];
+    T v[D] = {T(0), T(0)}, vt[D] = {T(0), T(0)};
+    if (m > T(0)) node_velocity<T, D>(g, P, I, m, &sum[1], v, vt);
+    const long long node = node_index(g, I[0], I[1], 0);
+    const bool keep = des == tile;
+#pragma unroll
+    for (int a = 0; a < D; ++a) {
+        s_v[a][tid] = v[a];
+        if (keep) {
+            nd.gv[a * g.NN + node] = v[a];
+            if (nd.gvt) nd.gvt[a * g.NN + node] = vt[a];
+        }
+        if constexpr (FL) {
+            const T vo = m > T(0) ? sum[1 + D + a] / m : T(0);
+            s_vo[a][tid] = vo;
+            if (keep) nd.gvo[a * g.NN + node] = vo;
+        }
+    }
+    if (keep && P.keep_grid) nd.gmass[node] = m;
+}
+
 // The transfer (App. B) sets the new velocity and the carried matrix C:
 // APIC C = (4/h^2) sum phi v_i (x_i - x_p)^T, TPIC C = the velocity gradient,
 // PIC and FLIP C = 0; FLIP (FL) also gathers the grid velocity before the
 // update, gvo, and blends: v' = sum phi v_i + alpha (v_p - sum phi v_i^n).
 template <class T, int D, int MAT, int XF>
-__global__ __launch_bounds__(kG2PBlock<T>) void k_g2p(Geo g, Phys<T> P, const int* __restrict__ meta,
+__global__ __launch_bounds__((kG2PBlock<T, D>)) void k_g2p(Geo g, Phys<T> P, const int* __restrict__ meta,
                                                 const ActiveTile* __restrict__ active, const int* __restrict__ perm,
                                                 PView<T> cur, PView<T> nxt, const T* __restrict__ gv,
                                                 const T* __restrict__ gvo,
                                                 int* __restrict__ key_out, int* __restrict__ count,
                                                 int* __restrict__ status, const T* __restrict__ eps_in,
-                                                T* __restrict__ eps_out)
+                                                T* __restrict__ eps_out, Nodes2<T> nd)
 {
     constexpr int TE = TileShape<D>::TE, BE = TileShape<D>::BE, NB = TileShape<D>::NB;
     constexpr int NS = D * (D + 1) / 2;
-    constexpr int NPT = (NB + kG2PBlock<T> - 1) / kG2PBlock<T>;   // block nodes per thread
+    constexpr int NPT = (NB + kG2PBlock<T, D> - 1) / kG2PBlock<T, D>;   // block nodes per thread
     constexpr bool FL = XF == XF_FLIP;
     __shared__ T s_v[D][NB];
     __shared__ T s_vo[FL ? D : 1][FL ? NB : 1];
-    const int n_active = meta[0];
+    const bool by_tile = D == 2 && nd.range;
+    const int n_active = by_tile ? 0 : meta[0];
     const int tid = threadIdx.x;
     const long long cap = cur.cap;
     // With kG2PPrefetch, the next tile's node velocities are loaded into
     // registers while this tile's particles are processed (and its
     // active-list entry one tile earlier still); otherwise each tile loads its
     // own block at its top.
-    constexpr bool PF = kG2PPrefetch<T> && !FL;
-    int e = __builtin_amdgcn_readfirstlane(tile_entry(0, n_active));
+    constexpr bool PF = kG2PPrefetch<T> && !FL && D == 3;
+    int e = __builtin_amdgcn_readfirstlane(by_tile ? tile_of_block(g.ntiles) : tile_entry(0, n_active));
     if (e < 0) return;
-    ActiveTile at = active[e];
+    ActiveTile at;
+    int j_row = 0;
+    if (by_tile) {
+        const int2 r = nd.range[e];
+        j_row = nd.tile_perm[e * kTileRow + tid];
+        at.tile = e;
+        at.off = r.x;
+        at.cnt = r.y;
+        if (at.cnt == 0) return;
+    } else {
+        at = active[e];
+    }
     T pre[D][NPT];
-    if (PF) g2p_block_load<T, D, NPT, kG2PBlock<T>>(g, gv, at.tile, tid, pre);
-    int en = __builtin_amdgcn_readfirstlane(tile_entry(1, n_active));
+    if (PF) g2p_block_load<T, D, NPT, kG2PBlock<T, D>>(g, gv, at.tile, tid, pre);
+    int en = by_tile ? -1 : __builtin_amdgcn_readfirstlane(tile_entry(1, n_active));
     int next_tile = (PF && en >= 0) ? active[en].tile : 0;
     for (int it = 0; e >= 0; ++it) {
-        if (!PF) g2p_block_load<T, D, NPT, kG2PBlock<T>>(g, gv, at.tile, tid, pre);
-        if constexpr (FL) {
+        // 2-D: a thread's first particle is on its way while the nodes are formed
+        constexpr int NG = mat_has_F(MAT) ? D * D : 1;
+        int j_first = 0, pid_first = 0;
+        T x_first[D], g_first[NG];
+        if constexpr (D == 2) {
+            if (tid < at.cnt) {
+                j_first = by_tile ? j_row : ld_once(&perm[at.off + tid]);
+#pragma unroll
+                for (int a = 0; a < D; ++a) x_first[a] = ld_once(&cur.x[a * cap + j_first]);
+#pragma unroll
+                for (int q = 0; q < NG; ++q) g_first[q] = ld_once(&cur.G[q * cap + j_first]);
+                pid_first = ld_once(&cur.pid[j_first]);
+            }
+            node_block2<T, FL>(g, P, nd, at.tile, tid, s_v, s_vo);
+        }
+        if (!PF && D == 3) g2p_block_load<T, D, NPT, kG2PBlock<T, D>>(g, gv, at.tile, tid, pre);
+        if constexpr (FL && D == 3) {
             T preo[D][NPT];
-            g2p_block_load<T, D, NPT, kG2PBlock<T>>(g, gvo, at.tile, tid, preo);
+            g2p_block_load<T, D, NPT, kG2PBlock<T, D>>(g, gvo, at.tile, tid, preo);
 #pragma unroll
             for (int p = 0; p < NPT; ++p) {
-                const int i = tid + p * kG2PBlock<T>;
+                const int i = tid + p * kG2PBlock<T, D>;
                 if (i < NB)
 #pragma unroll
                     for (int a = 0; a < D; ++a) s_vo[a][i] = preo[a][p];
             }
         }
+        if constexpr (D == 3)
 #pragma unroll
         for (int p = 0; p < NPT; ++p) {
-            const int i = tid + p * kG2PBlock<T>;
+            const int i = tid + p * kG2PBlock<T, D>;
             if (i < NB)
 #pragma unroll
                 for (int a = 0; a < D; ++a) s_v[a][i] = pre[a][p];
@@ -906,26 +1363,27 @@ __global__ __launch_bounds__(kG2PBlock<T>) void k_g2p(Geo g, Phys<T> P, const in
         __syncthreads();
         int enn = -1, next2_tile = 0;
         if (!PF) {
-            enn = __builtin_amdgcn_readfirstlane(tile_entry(it + 2, n_active));
+            enn = by_tile ? -1 : __builtin_amdgcn_readfirstlane(tile_entry(it + 2, n_active));
         } else if (en >= 0) {
-            g2p_block_load<T, D, NPT, kG2PBlock<T>>(g, gv, next_tile, tid, pre);
+            g2p_block_load<T, D, NPT, kG2PBlock<T, D>>(g, gv, next_tile, tid, pre);
             enn = __builtin_amdgcn_readfirstlane(tile_entry(it + 2, n_active));
             if (enn >= 0) next2_tile = active[enn].tile;
         }
         int tc[3];
         tile_coords(g, at.tile, tc);
-        for (int k0 = 0; k0 < at.cnt; k0 += kG2PBlock<T>) {
+        for (int k0 = 0; k0 < at.cnt; k0 += kG2PBlock<T, D>) {
             int k = k0 + tid;
             bool valid = k < at.cnt;
             int newkey = 0;
             if (valid) {
                 long long s = at.off + k;
-                int j = ld_once(&perm[s]);
+                const bool mine_first = D == 2 && k0 == 0;
+                int j = mine_first ? j_first : ld_once(&perm[s]);
                 T xp[D], w[D][3], dw[D][3], dd[D][3];
                 int lb[3] = {0, 0, 0};
 #pragma unroll
                 for (int a = 0; a < D; ++a) {
-                    xp[a] = ld_once(&cur.x[a * cap + j]);
+                    xp[a] = mine_first ? x_first[a] : ld_once(&cur.x[a * cap + j]);
                     int b;
                     T f;
                     stencil_axis(xp[a], P.inv, b, f, w[a], dw[a]);
@@ -1012,13 +1470,13 @@ __global__ __launch_bounds__(kG2PBlock<T>) void k_g2p(Geo g, Phys<T> P, const in
                     }
                 }
                 if constexpr (MAT == MAT_FLUID) {
-                    T dJ = ld_once(&cur.G[j]), si;
+                    T dJ = mine_first ? g_first[0] : ld_once(&cur.G[j]), si;
                     fluid_update<T, D>(P, Lm, dJ, si);
                     bad |= !finite(si) || !finite(dJ);
                     st_late(dJ, &nxt.G[s]);
                     nxt.S[s] = si;
                 } else if constexpr (MAT == MAT_VFLUID || MAT == MAT_JAUMANN) {
-                    T dJ = ld_once(&cur.G[j]), Sv[NS];
+                    T dJ = mine_first ? g_first[0] : ld_once(&cur.G[j]), Sv[NS];
                     if constexpr (MAT == MAT_JAUMANN)   // the viscous fluid's stress is a function of J and L
 #pragma unroll
                         for (int q = 0; q < NS; ++q) Sv[q] = cur.S[q * cap + j];
@@ -1041,7 +1499,8 @@ __global__ __launch_bounds__(kG2PBlock<T>) void k_g2p(Geo g, Phys<T> P, const in
 #pragma unroll
                     for (int a = 0; a < D; ++a)
 #pragma unroll
-                        for (int b = 0; b < D; ++b) Gm[a][b] = ld_once(&cur.G[(a * D + b) * cap + j]);
+                        for (int b = 0; b < D; ++b)
+                            Gm[a][b] = mine_first ? g_first[NG > 1 ? a * D + b : 0] : ld_once(&cur.G[(a * D + b) * cap + j]);
                     T dgam;
                     noconv = !hencky_update<T, D>(P, MAT == MAT_SAND, Lm, Gm, Sv, &dgam);
                     // equivalent plastic strain (when carried): sqrt(2/3) |dE_p|
@@ -1056,7 +1515,7 @@ __global__ __launch_bounds__(kG2PBlock<T>) void k_g2p(Geo g, Phys<T> P, const in
                         nxt.S[q * cap + s] = Sv[q];
                     }
                 }
-                int pid = ld_once(&cur.pid[j]);
+                int pid = mine_first ? pid_first : ld_once(&cur.pid[j]);
                 st_late(pid, &nxt.pid[s]);
                 if (bad) {
                     atomicOr(&status[0], 1);
@@ -1072,6 +1531,8 @@ __global__ __launch_bounds__(kG2PBlock<T>) void k_g2p(Geo g, Phys<T> P, const in
                 }
                 newkey = cell_key<T, D>(g, xn, P.inv);
                 key_out[s] = newkey;
+                if constexpr (D == 2)
+                    if (by_tile && k < kTileRow) nd.tile_key[at.tile * kTileRow + k] = newkey;
             }
             int head, len, rank;
             wave_runs(valid ? (newkey >> 6) : -1, valid, head, len, rank);
@@ -1374,13 +1835,28 @@ struct Solver {
 
     static int recompute_keys(mpm_ctx* c)
     {
+        new_keys(c, view<T>(c, c->cur));
+        return launch_err(c, "keys");
+    }
+
+    // Keys and tile counts of a state whose layout no sort of this step's
+    // predecessor describes.
+    static void new_keys(mpm_ctx* c, const PView<T>& v)
+    {
         hipStream_t st = c->stream;
-        k_fill<int><<<std::min<long long>(nblocks(c->geo.ntiles), 4096), kBlock, 0, st>>>(c->count, c->geo.ntiles, 0);
+        int* count = c->count[c->turn];
+        k_fill<int><<<std::min<long long>(nblocks(c->geo.ntiles), 4096), kBlock, 0, st>>>(count, c->geo.ntiles, 0);
+        // no tile finds its particles in the rows of the last sort (a captured
+        // step that gathers then reads all keys)
+        if (c->tile_key) {
+            const long long nr = (long long)c->geo.ntiles * kTileRow;
+            k_fill<int><<<std::min<long long>(nblocks(nr), 4096), kBlock, 0, st>>>(c->tile_key, nr, -1);
+        }
+        c->ranges_known = false;
         if (c->N > 0) {
             Phys<T> P = make_phys<T>(c, 0.0);
-            k_keys<T, D><<<nblocks(c->N), kBlock, 0, st>>>(c->geo, P, view<T>(c, c->cur), c->N, c->key, c->count);
+            k_keys<T, D><<<nblocks(c->N), kBlock, 0, st>>>(c->geo, P, v, c->N, c->key, count);
         }
-        return launch_err(c, "keys");
     }
 
     static int clear_grid(mpm_ctx* c)
@@ -1435,21 +1911,76 @@ struct Solver {
         prof_mark(c, -1);
         // one chunk has no earlier chunks to sum: the down-sweep alone (a
         // launch fewer for the small grids, whose steps are launch-bound)
-        if (nsb > 1) k_scan_reduce<0><<<nsb, kBlock, 0, st>>>(c->count, g.ntiles, c->part);
-        k_scan_down<0><<<nsb, kBlock, 0, st>>>(c->count, g.ntiles, c->part, c->tile_off, b.tile_slot, b.active, b.meta);
-        prof_mark(c, MPM_PROF_SCAN);
-        k_bucket<0><<<(unsigned)((c->N + kBlock * kBucketPer - 1) / (kBlock * kBucketPer)), kBlock, 0, st>>>(
-            c->N, c->key, c->count, c->tile_off, c->tmp, c->tmpk);
-        prof_mark(c, MPM_PROF_BUCKET);
+        if constexpr (D == 2) {
+            step_views2<MAT, XF>(c, P, cur, nxt, b, nsb);
+            return;
+        } else {
+        int* count = c->count[0];
+        sort_tiles(c, nsb, count, b, nullptr, nullptr);
         k_p2g<T, D, PM, FL><<<kP2GWGs<T, FL>, kP2GBlock<T, FL>, 0, st>>>(g, P, b.meta, b.active, c->tmp, c->tmpk, cur,
                                                                         b.perm, (T*)c->part_grid);
         prof_mark(c, MPM_PROF_P2G);
         k_grid<T, D, FL><<<kTileWGs * kBlock / kGridBlock, kGridBlock, 0, st>>>(g, P, b.meta, b.active, b.tile_slot, (const T*)c->part_grid,
                                                   b.gv, b.gmass, b.gvt, b.gvo);
         prof_mark(c, MPM_PROF_GRID);
-        k_g2p<T, D, MAT, XF><<<kTileWGs * kBlock / kG2PBlock<T>, kG2PBlock<T>, 0, st>>>(g, P, b.meta, b.active, b.perm, cur, nxt, (const T*)b.gv,
-                                                      (const T*)b.gvo, c->key, c->count, c->status, b.eps_in, b.eps_out);
+        k_g2p<T, D, MAT, XF><<<kTileWGs * kBlock / kG2PBlock<T, D>, kG2PBlock<T, D>, 0, st>>>(g, P, b.meta, b.active, b.perm, cur, nxt, (const T*)b.gv,
+                                                      (const T*)b.gvo, c->key, count, c->status, b.eps_in, b.eps_out, Nodes2<T>{});
         prof_mark(c, MPM_PROF_G2P);
+        }
+    }
+
+    // The scan over the tiles' counts and the scatter of the particles into
+    // their tiles' ranges.
+    static void sort_tiles(mpm_ctx* c, unsigned nsb, int* count, const StepBufs& b, int2* range, int* count_next)
+    {
+        hipStream_t st = c->stream;
+        // one chunk has no earlier chunks to sum: the down-sweep alone
+        if (nsb > 1) k_scan_reduce<0><<<nsb, kBlock, 0, st>>>(count, c->geo.ntiles, c->part);
+        k_scan_down<0><<<nsb, kBlock, 0, st>>>(count, c->geo.ntiles, c->part, c->tile_off, b.tile_slot, b.active, b.meta,
+                                               range, count_next);
+        prof_mark(c, MPM_PROF_SCAN);
+        k_bucket<0><<<(unsigned)((c->N + kBlock * kBucketPer - 1) / (kBlock * kBucketPer)), kBlock, 0, st>>>(
+            c->N, c->key, count, c->tile_off, c->tmp, c->tmpk);
+        prof_mark(c, MPM_PROF_BUCKET);
+    }
+
+    // The step in 2-D: two launches where the last sort's layout is known and
+    // the tiles are few enough that a workgroup can sum all earlier counts
+    // itself (one scan chunk: 8 loads per thread), else the scan and the
+    // scatter before them.  Everything that alternates between steps does so on
+    // every step, so that an even number of captured steps can be replayed.
+    template <int MAT, int XF>
+    static void step_views2(mpm_ctx* c, const Phys<T>& P, const PView<T>& cur, const PView<T>& nxt, const StepBufs& b,
+                            unsigned nsb)
+    {
+        constexpr bool FL = XF == XF_FLIP;
+        constexpr int PM = mat_iso_stress(MAT) ? MAT_FLUID : MAT_SAND;
+        hipStream_t st = c->stream;
+        const Geo& g = c->geo;
+        const bool small = g.ntiles <= kSmallTiles;
+        const int o = c->turn, n = small ? 1 - o : o;
+        const unsigned wgs = small ? (unsigned)((g.ntiles + 7) / 8 * 8) : (unsigned)kTileWGs;
+        const Ranges2 r{c->count[o], c->count[n], c->range[o], c->range[n], c->key, c->tile_key,
+                          small ? c->tile_perm : nullptr, (long long)c->N};
+        if (small && c->ranges_known && c->N < (1ll << 30)) {   // key positions plus a batch stay in int32
+            k_sort_p2g2<T, PM, FL, true, 256><<<wgs, 256, 0, st>>>(g, P, r, b.meta, b.active, b.tile_slot, c->tmp, c->tmpk,
+                                                                      cur, b.perm, (T*)c->part_grid);
+        } else {
+            sort_tiles(c, nsb, c->count[o], b, small ? c->range[n] : nullptr, small ? c->count[n] : nullptr);
+            if (small)
+                k_sort_p2g2<T, PM, FL, false, 256><<<wgs, 256, 0, st>>>(g, P, r, b.meta, b.active, b.tile_slot, c->tmp,
+                                                                        c->tmpk, cur, b.perm, (T*)c->part_grid);
+            else
+                k_sort_p2g2<T, PM, FL, false, kSortMany2><<<kTileWGs * kBlock / kSortMany2, kSortMany2, 0, st>>>(
+                    g, P, r, b.meta, b.active, b.tile_slot, c->tmp, c->tmpk, cur, b.perm, (T*)c->part_grid);
+        }
+        prof_mark(c, MPM_PROF_P2G);
+        const Nodes2<T> nd{(const T*)c->part_grid, b.tile_slot, small ? c->range[n] : nullptr, c->tile_perm, c->tile_key, b.gv, b.gmass, b.gvt, b.gvo};
+        k_g2p<T, D, MAT, XF><<<wgs, kG2PBlock<T, D>, 0, st>>>(g, P, b.meta, b.active, b.perm, cur, nxt, nullptr, nullptr, c->key,
+                                                              c->count[n], c->status, b.eps_in, b.eps_out, nd);
+        prof_mark(c, MPM_PROF_G2P);
+        c->turn = n;
+        c->ranges_known = small;
     }
 
     template <int MAT, int XF = XF_APIC>

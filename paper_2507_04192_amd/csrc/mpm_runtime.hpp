@@ -19,6 +19,8 @@ namespace mpm {
 constexpr int kBlock = 256;        // threads per workgroup (4 waves)
 constexpr int kScanChunk = 2048;   // tiles per scan workgroup
 constexpr int kTileWGs = 2048;     // workgroups of the per-tile kernels (8 XCDs x 256)
+constexpr int kSmallTiles = kScanChunk;   // 2-D: tiles up to which a workgroup sums all earlier counts itself
+constexpr int kTileRow = 256;      // 2-D: entries of a tile's row of perm and of its keys, one per thread
 constexpr int kMaxBoxes = MPM_MAX_BOXES;   // Eulerian observation regions
 
 struct Ops;
@@ -61,7 +63,12 @@ struct mpm_ctx {
     int32_t* perm = nullptr;
     int32_t* tmp = nullptr;
     int32_t* tmpk = nullptr;       // key of each bucketed particle
-    int32_t* count = nullptr;
+    int32_t* count[2] = {nullptr, nullptr};  // particles per tile; 2-D steps alternate, 3-D uses the first
+    int2* range[2] = {nullptr, nullptr};     // 2-D: first slot and number of each tile's particles, by turn
+    int32_t* tile_perm = nullptr;  // 2-D, few tiles: row per tile of the first entries of perm
+    int32_t* tile_key = nullptr;   // and of the keys after the step, else null
+    int turn = 0;                  // 2-D: buffer that describes the current state
+    bool ranges_known = false;     // 2-D: range[turn] is the layout of the current state
     int32_t* tile_off = nullptr;
     int32_t* tile_slot = nullptr;
     mpm::ActiveTile* active = nullptr;
