@@ -12,6 +12,7 @@
 //   g2p_adj   per particle: reverse of the constitutive update and of G2P;
 //             node adjoints accumulated in LDS and written per tile
 //   grid_adj  per node: reverse of the walls (dL/dmu) and of v = P/m + dt g
+//             (2-D: inside p2g_adj)
 //   p2g_adj   per particle: reverse of P2G, then the sort is undone by
 //             writing each particle's adjoint at its slot before the step.
 #pragma once
@@ -21,7 +22,8 @@
 
 namespace mpm {
 
-constexpr int kAdjBlock = 128;   // threads of the reverse per-tile kernels
+// threads of the reverse per-tile kernels (2-D: a tile's particles at once)
+template <int D> constexpr int kAdjBlock = D == 2 ? 256 : 128;
 
 // Per-slot intermediate of the reverse sweep (mid), component-major with
 // stride cap, written by k_g2p_adj and read by k_p2g_adj:
@@ -51,7 +53,7 @@ template <int D> struct MidLayout {
 // an adjoint to the position, and alpha times the adjoint of v' goes to mid
 // as the direct adjoint of v_p.
 template <class T, int D, int MAT, bool FL>
-__global__ __launch_bounds__(kAdjBlock) void k_g2p_adj(Geo g, Phys<T> P, const int* __restrict__ meta,
+__global__ __launch_bounds__((kAdjBlock<D>)) void k_g2p_adj(Geo g, Phys<T> P, const int* __restrict__ meta,
                                                     const ActiveTile* __restrict__ active,
                                                     const int* __restrict__ perm, PView<T> st, PView<T> aout,
                                                     const T* __restrict__ gv, const T* __restrict__ gvo,
@@ -75,7 +77,7 @@ __global__ __launch_bounds__(kAdjBlock) void k_g2p_adj(Geo g, Phys<T> P, const i
         ActiveTile at = active[e];
         int tc[3];
         tile_coords(g, at.tile, tc);
-        for (int i = tid; i < NB; i += kAdjBlock) {
+        for (int i = tid; i < NB; i += kAdjBlock<D>) {
             int l0 = i % BE, l1 = (i / BE) % BE, l2 = (D == 3) ? i / (BE * BE) : 0;
             long long node = node_index(g, tc[0] * TE + l0, tc[1] * TE + l1, (D == 3) ? tc[2] * TE + l2 : 0);
 #pragma unroll
@@ -89,7 +91,7 @@ __global__ __launch_bounds__(kAdjBlock) void k_g2p_adj(Geo g, Phys<T> P, const i
             }
         }
         __syncthreads();
-        for (int k = tid; k < at.cnt; k += kAdjBlock) {
+        for (int k = tid; k < at.cnt; k += kAdjBlock<D>) {
             long long s = at.off + k;
             int j = perm[s];
             T xbar_c[D], vt_c[D], Lb_c[D][D], vob_c[FL ? D : 1];
@@ -329,16 +331,96 @@ __global__ __launch_bounds__(kAdjBlock) void k_g2p_adj(Geo g, Phys<T> P, const i
             }
         }
         __syncthreads();
-        T* dst = part + (long long)e * NVA * NB;
-        for (int i = tid; i < D * NB; i += kAdjBlock) dst[i] = (T)(&s_b[0][0])[i];
+        // 2-D: by tile, so that the next kernel need not look the block up
+        T* dst = part + (long long)(D == 2 ? at.tile : e) * NVA * NB;
+        for (int i = tid; i < D * NB; i += kAdjBlock<D>) dst[i] = (T)(&s_b[0][0])[i];
         if constexpr (FL)
-            for (int i = tid; i < D * NB; i += kAdjBlock) dst[D * NB + i] = (T)(&s_bo[0][0])[i];
+            for (int i = tid; i < D * NB; i += kAdjBlock<D>) dst[D * NB + i] = (T)(&s_bo[0][0])[i];
         __syncthreads();
     }
 }
 
-template <class T, int D>
-__global__ __launch_bounds__(kAdjBlock) void k_grid_adj(Geo g, Phys<T> P, const int* __restrict__ meta,
+// Reverse of a node's update (walls, obstacles, v = P/m + dt g) from the
+// adjoint vb of its velocity (overwritten): pb the adjoint of its momentum, mb
+// of its mass m.  vt: the velocity before the walls; FLIP (FL): vob, the
+// adjoint of the velocity before the update, v^n = Q / m = vo, whose Q gets
+// qb.  amu (null: not added): dL/dmu per floor node.
+template <class T, int D, bool FL>
+__device__ __forceinline__ void node_adjoint(const Geo& g, const Phys<T>& P, const int I[3], T m, const T vt[D], T vb[D],
+                                             const T* vo, const T* vob, double* __restrict__ amu, T pb[D], T& mb, T* qb)
+{
+    mb = T(0);
+#pragma unroll
+    for (int a = 0; a < D; ++a) pb[a] = T(0);
+    if constexpr (FL)
+#pragma unroll
+        for (int a = 0; a < D; ++a) qb[a] = T(0);
+    if (!(m > T(0))) return;
+    T vin[2 * D][D], vel[D];
+    int nf = 0, fc[2 * D];
+    T fmu[2 * D];
+#pragma unroll
+    for (int a = 0; a < D; ++a) vel[a] = vt[a];
+    for (int a = 0; a < D; ++a) {
+        int ip = I[a] - g.G;
+        for (int side = 0; side < 2; ++side) {
+            bool beyond = side == 0 ? (ip <= 0) : (ip >= g.n[a]);
+            if (!beyond) continue;
+            int face = 2 * a + side;
+            T mu = P.wall_mu[face];
+            if (face == 2 * (D - 1) && P.floor_mu) {
+                int fx = min(I[0], g.box[0] - 1);
+                int fi = (D == 3) ? min(I[1], g.box[1] - 1) * P.floor_stride + fx : fx;
+                mu = P.floor_mu[fi];
+            }
+#pragma unroll
+            for (int q = 0; q < D; ++q) vin[nf][q] = vel[q];
+            fc[nf] = face;
+            fmu[nf] = mu;
+            ++nf;
+            wall_node<T, D>(P.wall_mode[face], mu, a, side == 0 ? T(-1) : T(1), vel);
+        }
+    }
+    // resting obstacles after the walls (Sec. 4.2.1): a component that one of
+    // them removed passes no adjoint back
+    if (P.n_obst > 0) {
+        double xi[D];
+#pragma unroll
+        for (int a = 0; a < D; ++a) xi[a] = double(I[a] - g.G) * P.obst_h;
+        int cut[kMaxObstacles];
+        for (int o = 0; o < P.n_obst; ++o) {
+            cut[o] = obstacle_component<T, D>(P, o, xi, vel);
+            if (cut[o] >= 0) vel[cut[o]] = T(0);
+        }
+        for (int o = P.n_obst - 1; o >= 0; --o)
+            for (int a = 0; a < D; ++a)
+                if (cut[o] == a) vb[a] = T(0);
+    }
+    for (int f = nf - 1; f >= 0; --f) {
+        int face = fc[f], a = face / 2;
+        T sign = (face % 2 == 0) ? T(-1) : T(1);
+        T mub = wall_node_vjp<T, D>(P.wall_mode[face], fmu[f], a, sign, vin[f], vb);
+        if (amu && face == 2 * (D - 1) && P.floor_mu && mub != T(0)) {
+            int fx = min(I[0], g.box[0] - 1);
+            int fi = (D == 3) ? min(I[1], g.box[1] - 1) * P.floor_stride + fx : fx;
+            atomicAdd(&amu[fi], (double)mub);
+        }
+    }
+    T dot = T(0);
+#pragma unroll
+    for (int a = 0; a < D; ++a) {
+        pb[a] = vb[a] / m;
+        dot += vb[a] * (vt[a] - P.dt * P.g[a]);
+        if constexpr (FL) {
+            dot += vob[a] * vo[a];
+            qb[a] = vob[a] / m;
+        }
+    }
+    mb = -dot / m;
+}
+
+template <class T, int D, bool FL>
+__global__ __launch_bounds__((kAdjBlock<D>)) void k_grid_adj(Geo g, Phys<T> P, const int* __restrict__ meta,
                                                      const ActiveTile* __restrict__ active,
                                                      const int* __restrict__ tile_slot, const T* __restrict__ part,
                                                      T* __restrict__ gmass, const T* __restrict__ gvt,
@@ -353,7 +435,7 @@ __global__ __launch_bounds__(kAdjBlock) void k_grid_adj(Geo g, Phys<T> P, const 
         int tile = active[e].tile;
         int tc[3];
         tile_coords(g, tile, tc);
-        for (int i = threadIdx.x; i < NB; i += kAdjBlock) {
+        for (int i = threadIdx.x; i < NB; i += kAdjBlock<D>) {
             int l[3] = {i % BE, (i / BE) % BE, (D == 3) ? i / (BE * BE) : 0};
             int I[3], own[3];
             bool down[3];
@@ -366,100 +448,88 @@ __global__ __launch_bounds__(kAdjBlock) void k_grid_adj(Geo g, Phys<T> P, const 
             constexpr int NC = 1 << D;
             int slot[NC], li[NC];
             const int des = node_blocks<D>(g, I, own, down, tile_slot, slot, li);
-            // FLIP (gvo given): the partial blocks also carry the adjoint of
-            // the velocity before the update, v^n = Q / m, after the first D
-            const int nva = gvo ? 2 * D + 1 : D + 1;
+            if (des != tile) continue;
+            // FLIP: the partial blocks also carry the adjoint of the velocity
+            // before the update, after the first D
+            constexpr int NVA = FL ? 2 * D + 1 : D + 1;
             T vb[D], vob[D];
 #pragma unroll
             for (int a = 0; a < D; ++a) {
                 vb[a] = T(0);
                 vob[a] = T(0);
             }
-            if (des == tile) {
 #pragma unroll
-                for (int msk = 0; msk < NC; ++msk) {
-                    if (slot[msk] < 0) continue;
-                    const T* src = part + (long long)slot[msk] * nva * NB;
+            for (int msk = 0; msk < NC; ++msk) {
+                if (slot[msk] < 0) continue;
+                const T* src = part + (long long)slot[msk] * NVA * NB;
 #pragma unroll
-                    for (int a = 0; a < D; ++a) vb[a] += src[a * NB + li[msk]];
-                    if (gvo)
+                for (int a = 0; a < D; ++a) vb[a] += src[a * NB + li[msk]];
+                if constexpr (FL)
 #pragma unroll
-                        for (int a = 0; a < D; ++a) vob[a] += src[(D + a) * NB + li[msk]];
-                }
+                    for (int a = 0; a < D; ++a) vob[a] += src[(D + a) * NB + li[msk]];
             }
-            if (des != tile) continue;
             long long node = node_index(g, I[0], I[1], I[2]);
-            T m = gmass[node];
-            T pb[D], mb = T(0);
+            const T m = gmass[node];
+            T vt[D], vo[D], pb[D], qb[D], mb;
 #pragma unroll
-            for (int a = 0; a < D; ++a) pb[a] = T(0);
-            if (m > T(0)) {
-                T vin[2 * D][D], vel[D];
-                int nf = 0, fc[2 * D];
-                T fmu[2 * D];
-#pragma unroll
-                for (int a = 0; a < D; ++a) vel[a] = gvt[a * g.NN + node];
-                for (int a = 0; a < D; ++a) {
-                    int ip = I[a] - g.G;
-                    for (int side = 0; side < 2; ++side) {
-                        bool beyond = side == 0 ? (ip <= 0) : (ip >= g.n[a]);
-                        if (!beyond) continue;
-                        int face = 2 * a + side;
-                        T mu = P.wall_mu[face];
-                        if (face == 2 * (D - 1) && P.floor_mu) {
-                            int fx = min(I[0], g.box[0] - 1);
-                            int fi = (D == 3) ? min(I[1], g.box[1] - 1) * P.floor_stride + fx : fx;
-                            mu = P.floor_mu[fi];
-                        }
-#pragma unroll
-                        for (int q = 0; q < D; ++q) vin[nf][q] = vel[q];
-                        fc[nf] = face;
-                        fmu[nf] = mu;
-                        ++nf;
-                        wall_node<T, D>(P.wall_mode[face], mu, a, side == 0 ? T(-1) : T(1), vel);
-                    }
-                }
-                // resting obstacles after the walls (Sec. 4.2.1): a component
-                // that one of them removed passes no adjoint back
-                if (P.n_obst > 0) {
-                    double xi[D];
-#pragma unroll
-                    for (int a = 0; a < D; ++a) xi[a] = double(I[a] - g.G) * P.obst_h;
-                    int cut[kMaxObstacles];
-                    for (int o = 0; o < P.n_obst; ++o) {
-                        cut[o] = obstacle_component<T, D>(P, o, xi, vel);
-                        if (cut[o] >= 0) vel[cut[o]] = T(0);
-                    }
-                    for (int o = P.n_obst - 1; o >= 0; --o)
-                        for (int a = 0; a < D; ++a)
-                            if (cut[o] == a) vb[a] = T(0);
-                }
-                for (int f = nf - 1; f >= 0; --f) {
-                    int face = fc[f], a = face / 2;
-                    T sign = (face % 2 == 0) ? T(-1) : T(1);
-                    T mub = wall_node_vjp<T, D>(P.wall_mode[face], fmu[f], a, sign, vin[f], vb);
-                    if (amu && face == 2 * (D - 1) && P.floor_mu && mub != T(0)) {
-                        int fx = min(I[0], g.box[0] - 1);
-                        int fi = (D == 3) ? min(I[1], g.box[1] - 1) * P.floor_stride + fx : fx;
-                        atomicAdd(&amu[fi], (double)mub);
-                    }
-                }
-                T dot = T(0);
-#pragma unroll
-                for (int a = 0; a < D; ++a) {
-                    pb[a] = vb[a] / m;
-                    dot += vb[a] * (gvt[a * g.NN + node] - P.dt * P.g[a]);
-                    if (gvo) dot += vob[a] * gvo[a * g.NN + node];
-                }
-                mb = -dot / m;
+            for (int a = 0; a < D; ++a) {
+                vt[a] = gvt[a * g.NN + node];
+                if constexpr (FL) vo[a] = gvo[a * g.NN + node];
             }
+            node_adjoint<T, D, FL>(g, P, I, m, vt, vb, vo, vob, amu, pb, mb, qb);
 #pragma unroll
             for (int a = 0; a < D; ++a) gv[a * g.NN + node] = pb[a];
             gmass[node] = mb;
             // FLIP: the adjoint of Q replaces v^n in the record
-            if (gvo)
+            if constexpr (FL)
 #pragma unroll
-                for (int a = 0; a < D; ++a) gvo[a * g.NN + node] = m > T(0) ? vob[a] / m : T(0);
+                for (int a = 0; a < D; ++a) gvo[a * g.NN + node] = qb[a];
+        }
+    }
+}
+
+// 2-D: what the reverse of P2G needs to form its tile's node adjoints itself
+// (as k_grid_adj, 1.56 times per node, the owner adding to dL/dmu): a launch
+// and its chain of round trips less in a step that is nothing but those.
+// 6,000 particles, binary64, per reverse step: g2p_adj 10.3, grid_adj 5.0,
+// p2g_adj 6.2 us -> 7.3 (256 threads per tile) and 7.2.
+template <class T>
+struct NodesAdj2 {
+    const T* part;
+    const int* tile_slot;
+    const T *gmass, *gvt, *gvo;
+    double* amu;
+};
+
+template <class T, bool FL>
+__device__ __forceinline__ void node_adj_block2(const Geo& g, const Phys<T>& P, const NodesAdj2<T>& nd, int tile, int tid,
+                                                T (&s_p)[2][TileShape<2>::NB], T (*s_f)[FL ? TileShape<2>::NB : 1], T* s_m)
+{
+    constexpr int D = 2, NB = TileShape<D>::NB, NV = FL ? 2 * D : D, NS = FL ? 2 * D + 1 : D + 1;
+    if (tid >= NB) return;
+    int tc[3];
+    tile_coords(g, tile, tc);
+    const long long node = node_index(g, tc[0] * TileShape<D>::TE + tid % TileShape<D>::BE,
+                                      tc[1] * TileShape<D>::TE + tid / TileShape<D>::BE, 0);
+    const T m = nd.gmass[node];
+    T vt[D], vo[D] = {T(0), T(0)};
+#pragma unroll
+    for (int a = 0; a < D; ++a) {
+        vt[a] = nd.gvt[a * g.NN + node];
+        if constexpr (FL) vo[a] = nd.gvo[a * g.NN + node];
+    }
+    int I[3];
+    T sum[NV], pb[D], qb[D], mb;
+    const int des = block_sum2<T, NV, NS>(g, nd.tile_slot, nd.part, tile, tid, I, sum);
+    node_adjoint<T, D, FL>(g, P, I, m, vt, sum, vo, &sum[FL ? D : 0], des == tile ? nd.amu : nullptr, pb, mb, qb);
+    s_m[tid] = mb;
+#pragma unroll
+    for (int a = 0; a < D; ++a) {
+        if constexpr (FL) {
+            s_f[a][tid] = pb[a];
+            s_p[a][tid] = pb[a] + qb[a];
+        } else {
+            s_p[a][tid] = pb[a];
         }
     }
 }
@@ -470,12 +540,12 @@ __global__ __launch_bounds__(kAdjBlock) void k_grid_adj(Geo g, Phys<T> P, const 
 // part, so the affine gathers take p + q (q the adjoint of Q, gqb) and the
 // force's gathers p alone; the direct adjoint of v_p comes from mid.
 template <class T, int D, int MAT, bool FL>
-__global__ __launch_bounds__(kAdjBlock) __attribute__((amdgpu_waves_per_eu(2))) void k_p2g_adj(Geo g, Phys<T> P, const int* __restrict__ meta,
+__global__ __launch_bounds__((kAdjBlock<D>)) __attribute__((amdgpu_waves_per_eu(2))) void k_p2g_adj(Geo g, Phys<T> P, const int* __restrict__ meta,
                                                     const ActiveTile* __restrict__ active,
                                                     const int* __restrict__ perm, PView<T> st,
                                                     const T* __restrict__ gpb, const T* __restrict__ gmb,
                                                     const T* __restrict__ gqb,
-                                                    const T* __restrict__ mid, PView<T> ain)
+                                                    const T* __restrict__ mid, PView<T> ain, NodesAdj2<T> nd)
 {
     constexpr int TE = TileShape<D>::TE, BE = TileShape<D>::BE, NB = TileShape<D>::NB;
     using ML = MidLayout<D>;
@@ -492,7 +562,9 @@ __global__ __launch_bounds__(kAdjBlock) __attribute__((amdgpu_waves_per_eu(2))) 
         ActiveTile at = active[e];
         int tc[3];
         tile_coords(g, at.tile, tc);
-        for (int i = tid; i < NB; i += kAdjBlock) {
+        if constexpr (D == 2) node_adj_block2<T, FL>(g, P, nd, at.tile, tid, s_p, s_f, s_m);
+        else
+        for (int i = tid; i < NB; i += kAdjBlock<D>) {
             int l0 = i % BE, l1 = (i / BE) % BE, l2 = (D == 3) ? i / (BE * BE) : 0;
             long long node = node_index(g, tc[0] * TE + l0, tc[1] * TE + l1, (D == 3) ? tc[2] * TE + l2 : 0);
             s_m[i] = gmb[node];
@@ -508,7 +580,7 @@ __global__ __launch_bounds__(kAdjBlock) __attribute__((amdgpu_waves_per_eu(2))) 
             }
         }
         __syncthreads();
-        for (int k = tid; k < at.cnt; k += kAdjBlock) {
+        for (int k = tid; k < at.cnt; k += kAdjBlock<D>) {
             long long s = at.off + k;
             int j = perm[s];
             T w[D][3], dw[D][3], dd[D][3], vp[D], Cp[D][D], Sp[D][D];
@@ -951,7 +1023,7 @@ struct Adjoint {
     // Reverse of one step whose sort and grid are in record rb (written by
     // the segment's forward recomputation): aout holds the adjoint of the
     // step's output state, ain receives that of its input state st_in.  The
-    // record's nodal velocity and mass are overwritten by their adjoints.
+    // record's nodal velocity and mass are overwritten by their adjoints (3-D).
     template <int MAT>
     static void adjoint_step(mpm_ctx* c, const Phys<T>& P, const PView<T>& st_in, const PView<T>& aout,
                              const PView<T>& ain, const typename S::StepBufs& rb)
@@ -961,26 +1033,35 @@ struct Adjoint {
         prof_mark(c, -1);
         const bool flip = c->xfer == XF_FLIP;
         if (flip)
-            k_g2p_adj<T, D, MAT, true><<<kTileWGs * kBlock / kAdjBlock, kAdjBlock, 0, st>>>(
+            k_g2p_adj<T, D, MAT, true><<<tile_wgs(c, kAdjBlock<D>), kAdjBlock<D>, 0, st>>>(
                 g, P, rb.meta, rb.active, rb.perm, st_in, aout, (const T*)rb.gv, (const T*)rb.gvo, (T*)c->part_grid,
                 (T*)c->mid);
         else
-            k_g2p_adj<T, D, MAT, false><<<kTileWGs * kBlock / kAdjBlock, kAdjBlock, 0, st>>>(
+            k_g2p_adj<T, D, MAT, false><<<tile_wgs(c, kAdjBlock<D>), kAdjBlock<D>, 0, st>>>(
                 g, P, rb.meta, rb.active, rb.perm, st_in, aout, (const T*)rb.gv, nullptr, (T*)c->part_grid,
                 (T*)c->mid);
         prof_mark(c, MPM_PROF_G2P_ADJ);
-        k_grid_adj<T, D><<<kTileWGs * kBlock / kAdjBlock, kAdjBlock, 0, st>>>(g, P, rb.meta, rb.active, rb.tile_slot,
-                                                      (const T*)c->part_grid, rb.gmass, (const T*)rb.gvt, rb.gv,
-                                                      flip ? rb.gvo : nullptr, c->floor_mu ? c->amu : nullptr);
-        prof_mark(c, MPM_PROF_GRID_ADJ);
+        double* amu = c->floor_mu ? c->amu : nullptr;
+        NodesAdj2<T> nd{};
+        if constexpr (D == 2) {
+            nd = {(const T*)c->part_grid, rb.tile_slot, rb.gmass, rb.gvt, rb.gvo, amu};
+        } else {
+            if (flip)
+                k_grid_adj<T, D, true><<<tile_wgs(c, kAdjBlock<D>), kAdjBlock<D>, 0, st>>>(
+                    g, P, rb.meta, rb.active, rb.tile_slot, (const T*)c->part_grid, rb.gmass, (const T*)rb.gvt, rb.gv, rb.gvo, amu);
+            else
+                k_grid_adj<T, D, false><<<tile_wgs(c, kAdjBlock<D>), kAdjBlock<D>, 0, st>>>(
+                    g, P, rb.meta, rb.active, rb.tile_slot, (const T*)c->part_grid, rb.gmass, (const T*)rb.gvt, rb.gv, nullptr, amu);
+            prof_mark(c, MPM_PROF_GRID_ADJ);
+        }
         if (flip)
-            k_p2g_adj<T, D, MAT, true><<<kTileWGs * kBlock / kAdjBlock, kAdjBlock, 0, st>>>(
+            k_p2g_adj<T, D, MAT, true><<<tile_wgs(c, kAdjBlock<D>), kAdjBlock<D>, 0, st>>>(
                 g, P, rb.meta, rb.active, rb.perm, st_in, (const T*)rb.gv, (const T*)rb.gmass, (const T*)rb.gvo,
-                (const T*)c->mid, ain);
+                (const T*)c->mid, ain, nd);
         else
-            k_p2g_adj<T, D, MAT, false><<<kTileWGs * kBlock / kAdjBlock, kAdjBlock, 0, st>>>(
+            k_p2g_adj<T, D, MAT, false><<<tile_wgs(c, kAdjBlock<D>), kAdjBlock<D>, 0, st>>>(
                 g, P, rb.meta, rb.active, rb.perm, st_in, (const T*)rb.gv, (const T*)rb.gmass, nullptr,
-                (const T*)c->mid, ain);
+                (const T*)c->mid, ain, nd);
         prof_mark(c, MPM_PROF_P2G_ADJ);
     }
 

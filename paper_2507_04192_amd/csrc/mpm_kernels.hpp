@@ -42,7 +42,6 @@ constexpr int kSortCap = 1024;   // particles per tile sorted in LDS (larger: in
 // With FLIP the node values double (momentum with and without the internal
 // force): binary32 then uses four waves per tile.
 template <class T, bool FL = false> constexpr int kP2GBlock = sizeof(T) == 4 ? (FL ? 256 : 128) : 64;
-template <class T, bool FL = false> constexpr int kP2GWGs = kTileWGs * kBlock / kP2GBlock<T, FL>;
 // threads of a G2P workgroup (3-D binary64: smaller groups, measured faster)
 template <class T, int D> constexpr int kG2PBlock = sizeof(T) == 8 && D == 3 ? 128 : 256;
 // G2P loads the next tile's node block while it works on the current one
@@ -1209,23 +1208,22 @@ struct Nodes2 {
     T *gv, *gmass, *gvt, *gvo;
 };
 
-// The node update of k_grid for the 100 nodes of one tile's block, one per
-// thread, into LDS.  A node shared by several tiles is formed by each of them
-// from the same sums in the same order (1.56 updates per node); its owner
-// stores it.  Partial blocks are loaded before it is known which tiles are
-// active: one round trip.
-template <class T, bool FL>
-__device__ __forceinline__ void node_block2(const Geo& g, const Phys<T>& P, const Nodes2<T>& nd, int tile, int tid,
-                                            T (&s_v)[2][TileShape<2>::NB], T (*s_vo)[FL ? TileShape<2>::NB : 1])
+// Sum of NV values over the partial blocks (one per tile, stride NS values per
+// node) that cover node `tid` of a tile's block, in the order of node_blocks:
+// own tile first.  I: the node; returns its owner, the first active tile that
+// covers it.  Blocks are loaded before it is known which tiles are active: one
+// round trip.
+template <class T, int NV, int NS>
+__device__ __forceinline__ int block_sum2(const Geo& g, const int* __restrict__ tile_slot, const T* __restrict__ part, int tile,
+                                          int tid, int I[3], T sum[NV])
 {
     constexpr int D = 2, TE = TileShape<D>::TE, BE = TileShape<D>::BE, NB = TileShape<D>::NB, NC = 4;
-    constexpr int NV = FL ? 2 * D + 1 : D + 1;
-    if (tid >= NB) return;
     int tc[3];
     tile_coords(g, tile, tc);
     const int l[2] = {tid % BE, tid / BE};
-    int I[3] = {0, 0, 0}, own[2];
+    int own[2];
     bool down[2];
+    I[2] = 0;
 #pragma unroll
     for (int a = 0; a < D; ++a) {
         I[a] = tc[a] * TE + l[a];
@@ -1241,13 +1239,12 @@ __device__ __forceinline__ void node_block2(const Geo& g, const Phys<T>& P, cons
         tl[msk] = ok ? cy * g.ntile[0] + cx : -1;
         const int src = ok ? tl[msk] : tile;
         const int li = ok ? (I[1] - cy * TE) * BE + I[0] - cx * TE : 0;
-        slot[msk] = nd.tile_slot[src];
-        const T* p = nd.part + (long long)src * NV * NB + li;
+        slot[msk] = tile_slot[src];
+        const T* p = part + (long long)src * NS * NB + li;
 #pragma unroll
         for (int q = 0; q < NV; ++q) val[msk][q] = p[q * NB];
     }
     int des = -1;
-    T sum[NV];
 #pragma unroll
     for (int q = 0; q < NV; ++q) sum[q] = T(0);
 #pragma unroll
@@ -1257,6 +1254,22 @@ __device__ __forceinline__ void node_block2(const Geo& g, const Phys<T>& P, cons
 #pragma unroll
             for (int q = 0; q < NV; ++q) sum[q] += val[msk][q];
         }
+    return des;
+}
+
+// The node update of k_grid for the 100 nodes of one tile's block, one per
+// thread, into LDS.  A node shared by several tiles is formed by each of them
+// from the same sums in the same order (1.56 updates per node); its owner
+// stores it.
+template <class T, bool FL>
+__device__ __forceinline__ void node_block2(const Geo& g, const Phys<T>& P, const Nodes2<T>& nd, int tile, int tid,
+                                            T (&s_v)[2][TileShape<2>::NB], T (*s_vo)[FL ? TileShape<2>::NB : 1])
+{
+    constexpr int D = 2, NB = TileShape<D>::NB, NV = FL ? 2 * D + 1 : D + 1;
+    if (tid >= NB) return;
+    int I[3];
+    T sum[NV];
+    const int des = block_sum2<T, NV, NV>(g, nd.tile_slot, nd.part, tile, tid, I, sum);
     const T m = sum[0];
     T v[D] = {T(0), T(0)}, vt[D] = {T(0), T(0)};
     if (m > T(0)) node_velocity<T, D>(g, P, I, m, &sum[1], v, vt);
@@ -1810,6 +1823,15 @@ PView<T> view(const mpm_ctx* c, int which)
     return v;
 }
 
+// Workgroups of a per-tile launch with `block` threads each: enough to fill the
+// chip, and not more than the grid has tiles (a small grid's launch was 2048
+// workgroups for a few dozen tiles).  A multiple of 8, one share per XCD.
+inline unsigned tile_wgs(const mpm_ctx* c, int block)
+{
+    const long long full = (long long)kTileWGs * kBlock / block, tiles = (c->geo.ntiles + 7) / 8 * 8;
+    return (unsigned)std::min(full, (long long)tiles);
+}
+
 template <class T, int D>
 struct Solver {
     static int launch_err(mpm_ctx* c, const char* what) { return hip_check(c, hipGetLastError(), what); }
@@ -1917,13 +1939,13 @@ struct Solver {
         } else {
         int* count = c->count[0];
         sort_tiles(c, nsb, count, b, nullptr, nullptr);
-        k_p2g<T, D, PM, FL><<<kP2GWGs<T, FL>, kP2GBlock<T, FL>, 0, st>>>(g, P, b.meta, b.active, c->tmp, c->tmpk, cur,
+        k_p2g<T, D, PM, FL><<<tile_wgs(c, kP2GBlock<T, FL>), kP2GBlock<T, FL>, 0, st>>>(g, P, b.meta, b.active, c->tmp, c->tmpk, cur,
                                                                         b.perm, (T*)c->part_grid);
         prof_mark(c, MPM_PROF_P2G);
-        k_grid<T, D, FL><<<kTileWGs * kBlock / kGridBlock, kGridBlock, 0, st>>>(g, P, b.meta, b.active, b.tile_slot, (const T*)c->part_grid,
+        k_grid<T, D, FL><<<tile_wgs(c, kGridBlock), kGridBlock, 0, st>>>(g, P, b.meta, b.active, b.tile_slot, (const T*)c->part_grid,
                                                   b.gv, b.gmass, b.gvt, b.gvo);
         prof_mark(c, MPM_PROF_GRID);
-        k_g2p<T, D, MAT, XF><<<kTileWGs * kBlock / kG2PBlock<T, D>, kG2PBlock<T, D>, 0, st>>>(g, P, b.meta, b.active, b.perm, cur, nxt, (const T*)b.gv,
+        k_g2p<T, D, MAT, XF><<<tile_wgs(c, kG2PBlock<T, D>), kG2PBlock<T, D>, 0, st>>>(g, P, b.meta, b.active, b.perm, cur, nxt, (const T*)b.gv,
                                                       (const T*)b.gvo, c->key, count, c->status, b.eps_in, b.eps_out, Nodes2<T>{});
         prof_mark(c, MPM_PROF_G2P);
         }
@@ -1971,7 +1993,7 @@ struct Solver {
                 k_sort_p2g2<T, PM, FL, false, 256><<<wgs, 256, 0, st>>>(g, P, r, b.meta, b.active, b.tile_slot, c->tmp,
                                                                         c->tmpk, cur, b.perm, (T*)c->part_grid);
             else
-                k_sort_p2g2<T, PM, FL, false, kSortMany2><<<kTileWGs * kBlock / kSortMany2, kSortMany2, 0, st>>>(
+                k_sort_p2g2<T, PM, FL, false, kSortMany2><<<tile_wgs(c, kSortMany2), kSortMany2, 0, st>>>(
                     g, P, r, b.meta, b.active, b.tile_slot, c->tmp, c->tmpk, cur, b.perm, (T*)c->part_grid);
         }
         prof_mark(c, MPM_PROF_P2G);

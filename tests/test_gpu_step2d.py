@@ -120,3 +120,31 @@ def test_captured_steps_replay():
     st.synchronize()
     a.close()
     b.close()
+
+
+# one tile, ragged tiles, particles of many tiles in the corner nodes, and a grid
+# past the tiles that a workgroup counts itself; with floor friction
+@pytest.mark.parametrize("cells,n,transfer", [((3, 3, 1), 30, W.APIC), ((13, 9, 1), 400, W.FLIP), ((59, 44, 1), 4000, W.APIC),
+                                              ((363, 355, 1), 3000, W.APIC)])
+def test_gradient_over_tiles_matches_oracle(orc, cells, n, transfer):
+    from paper_2507_04192_amd.native import Solver
+    from tests.helpers import rel_l2
+    cfg = _config(cells, W.FLUID, transfer, dt=5e-5).replace(wall_mode=(W.SLIP, W.SLIP, W.COULOMB, W.SLIP, W.SLIP, W.SLIP))
+    print(f"[case] 2-D gradient {cells} {n} {transfer}", flush=True)
+    rng = np.random.default_rng(n)
+    x = rng.uniform(0.0, 1.0, size=(2, n)) * np.array([[cells[0] * 0.01], [min(cells[1], 20) * 0.01]])
+    v = rng.normal(0.0, 1.0, size=(2, n)) - np.array([[0.0], [0.5]])
+    mu = rng.uniform(0.1, 0.5, size=cfg.floor_nodes())
+    frames, tr = [3, 6, 8], W.pick_tracers(n, 20, 3)
+    tgt = x[:, tr][None] + rng.normal(0.0, 1e-3, size=(3, 2, 20))
+    loss_o, gv_o, gmu_o = orc.rollout_grad(cfg, x, v, 8, cfg.dt, mu, orc.Observations(frames, tr, "x", tgt))
+    s = Solver(cfg, "f64", capacity=n, tape_steps=8, ckpt_every=3)
+    s.mpm_init_particles(x, v)
+    s.mpm_set_floor_mu(mu)
+    s.mpm_set_observations(frames, tracer_pid=tr, lag_field="x", lag_target=tgt)
+    loss = s.mpm_forward_loss(8)
+    gv, gmu = (t.cpu().numpy() for t in s.mpm_backward())
+    s.close()
+    # binary64 to the bounds of the other gradient tests
+    assert abs(loss - loss_o) <= 1e-10 * loss_o
+    assert rel_l2(gv, gv_o) <= 1e-8 and rel_l2(gmu, gmu_o) <= 1e-8
