@@ -298,27 +298,26 @@ __host__ __device__ constexpr int sym_index(int a, int b)
 }
 
 // One particle's P2G contribution (eq:update_m, the momentum with the APIC
-// affine term of App. B, and the internal force -dt V_p sigma_p grad phi).
-// Every weight factors over the axes, so per node line along x the terms
-// that do not depend on x are formed once.  With wyz = w_y w_z (2-D: w_y),
-// the values at node (kx, line) are
-//   mass  w_x mw,                              mw  = m_p wyz,
-//   P_a   w_x U_a + (w_x dd_x) V_a + dw_x W_a,
-//   U_a = wyz (m v_a + sum_{b>0} mC_ab dd_b) + sum_{b>0} fs_ab (grad phi_b / w_x),
-//   V_a = wyz mC_a0,  W_a = wyz fs_a0.
-// For each of the 3^D stencil nodes, sink(k, n, fx, mw, U, V, W, Uq)
-// receives the offset index k, the node's index n in the tile's LDS block,
-// the x factors fx = (w_x, w_x dd_x, dw_x) and the line terms of the
-// momentum components [A0, A1); Uq = wyz (m v_a + ...) is U without the
-// force, so the momentum without the internal force is w_x Uq + (w_x dd_x) V
-// (FLIP's v_i^n); p2g_node_values forms the D+1 values from them when the
-// range is all of them.
-template <class T, int D, int MAT, int A0, int A1, class Sink>
+// affine term of App. B, and the internal force -dt V_p sigma_p grad phi) in
+// the momentum components [A0, A1).  Weights, x_i - x_p and grad phi factor over
+// the axes, and so do the affine term and the force of each axis: with
+//   E^b_a(k) = (w dd)_b(k) m C_ab + dw_b(k) fs_ab,  fs = -dt V_p sigma_p,
+// the value at node (kx, ky, kz) is
+//   P_a = w_x w_y w_z m v_a + E^x_a w_y w_z + w_x E^y_a w_z + w_x w_y E^z_a
+//       = w_x U_a + (w_y w_z) E^x_a,
+//   U_a = w_z (w_y m v_a + E^y_a) + w_y E^z_a  (2-D: without the z factors),
+// two multiply-adds per node and two per line along x: 93 per component, where
+// one term each for velocity, affine part and force per node was 144.
+// Without FORCE (FLIP's v_i^n) fs = 0.  For each of the 3^D stencil nodes,
+// sink(k, n, wx, mw, wyz, U, Ex) receives the offset index k, the node's index n
+// in the tile's LDS block, the factors of the mass w_x mw and of P_a = w_x U_a +
+// wyz Ex_a.
+template <class T, int D, int MAT, int A0, int A1, bool FORCE, class Sink>
 __device__ __forceinline__ void p2g_particle(const Phys<T>& P, const P2GIn<T, D, MAT, A0, A1>& in, const int lb[3],
                                              const int gb[3], Sink&& sink)
 {
     constexpr int BE = TileShape<D>::BE, NA = A1 - A0;
-    T w[D][3], dw[D][3], dd[D][3];
+    T w[D][3], dw[D][3], wd[D][3];
 #pragma unroll
     for (int a = 0; a < D; ++a) {
         T x = in.x[a];
@@ -326,70 +325,55 @@ __device__ __forceinline__ void p2g_particle(const Phys<T>& P, const P2GIn<T, D,
         T f = t - T(gb[a]);
         weights_from_f(f, P.inv, w[a], dw[a]);
 #pragma unroll
-        for (int k = 0; k < 3; ++k) dd[a][k] = (T(k) - f) * P.h;
+        for (int k = 0; k < 3; ++k) wd[a][k] = w[a][k] * ((T(k) - f) * P.h);
     }
-    // rows A0..A1-1 of m v, m C and fs = -dt V sigma
-    T mv[NA], mC[NA][D], fs[NA][D];
+    // rows A0..A1-1 of m v and of the axis terms
+    T mv[NA], E[D][3][NA];
 #pragma unroll
     for (int a = 0; a < NA; ++a) {
         mv[a] = P.mass * in.v[a];
 #pragma unroll
         for (int b = 0; b < D; ++b) {
-            mC[a][b] = P.mass * in.C[a * D + b];
-            if constexpr (mat_iso_stress(MAT)) fs[a][b] = (A0 + a == b) ? -P.dt * in.S[0] : T(0);
-            else fs[a][b] = -P.dt * in.S[sym_index<D>(A0 + a, b)];
+            const T mC = P.mass * in.C[a * D + b];
+#pragma unroll
+            for (int k = 0; k < 3; ++k) {
+                E[b][k][a] = wd[b][k] * mC;
+                if constexpr (!FORCE) continue;
+                if (mat_iso_stress(MAT)) {
+                    if (A0 + a == b) E[b][k][a] = fma(dw[b][k], -P.dt * in.S[0], E[b][k][a]);
+                } else {
+                    E[b][k][a] = fma(dw[b][k], -P.dt * in.S[mat_iso_stress(MAT) ? 0 : sym_index<D>(A0 + a, b)], E[b][k][a]);
+                }
+            }
         }
     }
-    T fx[3][3];
+    // along y
 #pragma unroll
-    for (int q = 0; q < 3; ++q) {
-        fx[q][0] = w[0][q];
-        fx[q][1] = w[0][q] * dd[0][q];
-        fx[q][2] = dw[0][q];
-    }
+    for (int k = 0; k < 3; ++k)
+#pragma unroll
+        for (int a = 0; a < NA; ++a) E[1][k][a] = fma(w[1][k], mv[a], E[1][k][a]);
     constexpr int KZ = (D == 3) ? 3 : 1;
 #pragma unroll
     for (int kz = 0; kz < KZ; ++kz) {
-        T mvz[NA];   // m v_a + mC_a2 dd_z: the part of the affine term fixed on a z plane
-#pragma unroll
-        for (int a = 0; a < NA; ++a) mvz[a] = (D == 3) ? mv[a] + mC[a][D - 1] * dd[D - 1][kz] : mv[a];
 #pragma unroll
         for (int ky = 0; ky < 3; ++ky) {
-            T wyz = (D == 3) ? w[1][ky] * w[2][kz] : w[1][ky];
-            T g1 = (D == 3) ? dw[1][ky] * w[2][kz] : dw[1][ky];
-            T g2 = (D == 3) ? w[1][ky] * dw[2][kz] : T(0);
-            T U[NA], V[NA], Wf[NA], Uq[NA];
+            T wyz = w[1][ky], U[NA];
+            if constexpr (D == 3) wyz *= w[D - 1][kz];
 #pragma unroll
             for (int a = 0; a < NA; ++a) {
-                T aff = mvz[a] + mC[a][1] * dd[1][ky];
-                Uq[a] = wyz * aff;
-                T u = Uq[a] + fs[a][1] * g1;
-                if constexpr (D == 3) u += fs[a][2] * g2;
-                U[a] = u;
-                V[a] = wyz * mC[a][0];
-                Wf[a] = wyz * fs[a][0];
+                U[a] = E[1][ky][a];
+                if constexpr (D == 3) U[a] = fma(w[D - 1][kz], U[a], w[1][ky] * E[D - 1][kz][a]);
             }
-            T mw = P.mass * wyz;
+            const T mw = P.mass * wyz;
 #pragma unroll
             for (int kx = 0; kx < 3; ++kx) {
                 int n;
                 if constexpr (D == 3) n = ((lb[2] + kz) * BE + lb[1] + ky) * BE + lb[0] + kx;
                 else n = (lb[1] + ky) * BE + lb[0] + kx;
-                sink((kz * 3 + ky) * 3 + kx, n, fx[kx], mw, U, V, Wf, Uq);
+                sink((kz * 3 + ky) * 3 + kx, n, w[0][kx], mw, wyz, U, E[0][kx]);
             }
         }
     }
-}
-
-// The D+1 values (mass, momentum) a particle adds at one node, from the
-// factors p2g_particle hands to its sink.
-template <class T, int D>
-__device__ __forceinline__ void p2g_node_values(const T fx[3], T mw, const T U[D], const T V[D], const T W[D],
-                                                T add[D + 1])
-{
-    add[0] = fx[0] * mw;
-#pragma unroll
-    for (int a = 0; a < D; ++a) add[1 + a] = fx[0] * U[a] + fx[1] * V[a] + fx[2] * W[a];
 }
 
 // Node index in the tile's LDS block of stencil offset k for a lane whose
@@ -455,15 +439,10 @@ __device__ __forceinline__ void p2g_lane_sums(const Phys<T>& P, const PView<T>& 
         const P2GIn<T, D, MAT, A0, A1> in = nx;
         if (r + 1 < mycnt) nx.load(cur, sorted[rank_major_pos(lane, r + 1, s_rmask, s_roff, s_cnt)]);
         // the products go straight into the sums (one FMA each)
-        p2g_particle<T, D, MAT, A0, A1>(P, in, lb, gb,
-                                        [&](int k, int, const T* fx, T mw, const T* U, const T* V, const T* W,
-                                            const T* Uq) {
-            if constexpr (MASS) acc[k][0] = fma(fx[0], mw, acc[k][0]);
+        p2g_particle<T, D, MAT, A0, A1, !QV>(P, in, lb, gb, [&](int k, int, T wx, T mw, T wyz, const T* U, const T* Ex) {
+            if constexpr (MASS) acc[k][0] = fma(wx, mw, acc[k][0]);
 #pragma unroll
-            for (int a = 0; a < A1 - A0; ++a) {
-                if constexpr (QV) acc[k][M + a] = fma(fx[1], V[a], fma(fx[0], Uq[a], acc[k][M + a]));
-                else acc[k][M + a] = fma(fx[2], W[a], fma(fx[1], V[a], fma(fx[0], U[a], acc[k][M + a])));
-            }
+            for (int a = 0; a < A1 - A0; ++a) acc[k][M + a] = fma(wyz, Ex[a], fma(wx, U[a], acc[k][M + a]));
         });
     }
     if (mycnt > 0) {
@@ -668,17 +647,18 @@ __global__ __launch_bounds__((kP2GBlock<T, FL>)) __attribute__((amdgpu_waves_per
                 if (r < mycnt) {
                     P2GIn<T, D, MAT> in;
                     in.load(cur, sorted[rank_major_pos(cl, r, s_rmask, s_roff, s_cnt)]);
-                    p2g_particle<T, D, MAT>(P, in, lb, gb,
-                                            [&](int, int n, const T* fx, T mw, const T* U, const T* V, const T* W,
-                                                const T* Uq) {
-                        T add[D + 1];
-                        p2g_node_values<T, D>(fx, mw, U, V, W, add);
+                    p2g_particle<T, D, MAT, 0, D, true>(P, in, lb, gb,
+                                                        [&](int, int n, T wx, T mw, T wyz, const T* U, const T* Ex) {
+                        atomicAdd(&s_node[0][n], wx * mw);
 #pragma unroll
-                        for (int q = 0; q <= D; ++q) atomicAdd(&s_node[q][n], add[q]);
-                        if constexpr (FL)
-#pragma unroll
-                            for (int a = 0; a < D; ++a) atomicAdd(&s_node[1 + D + a][n], fma(fx[1], V[a], fx[0] * Uq[a]));
+                        for (int a = 0; a < D; ++a) atomicAdd(&s_node[1 + a][n], fma(wyz, Ex[a], wx * U[a]));
                     });
+                    if constexpr (FL)
+                        p2g_particle<T, D, MAT, 0, D, false>(P, in, lb, gb,
+                                                             [&](int, int n, T wx, T, T wyz, const T* U, const T* Ex) {
+#pragma unroll
+                            for (int a = 0; a < D; ++a) atomicAdd(&s_node[1 + D + a][n], fma(wyz, Ex[a], wx * U[a]));
+                        });
                 }
             }
         }
@@ -993,16 +973,16 @@ __global__ __launch_bounds__(NT) void k_sort_p2g2(Geo g, Phys<T> P, Ranges2 rg, 
         for (int r = w; r < mycnt; r += NW) {
             const P2GIn<T, D, MAT> in = nx;
             if (r + NW < mycnt) nx.load(cur, sorted[rank_major_pos(cl, r + NW, s_rmask, s_roff, s_cnt)]);
-            p2g_particle<T, D, MAT, 0, D>(P, in, lb, gb,
-                                          [&](int k, int, const T* fx, T mw, const T* U, const T* V, const T* W,
-                                              const T* Uq) {
-                acc[k][0] = fma(fx[0], mw, acc[k][0]);
+            p2g_particle<T, D, MAT, 0, D, true>(P, in, lb, gb, [&](int k, int, T wx, T mw, T wyz, const T* U, const T* Ex) {
+                acc[k][0] = fma(wx, mw, acc[k][0]);
 #pragma unroll
-                for (int a = 0; a < D; ++a) {
-                    acc[k][1 + a] = fma(fx[2], W[a], fma(fx[1], V[a], fma(fx[0], U[a], acc[k][1 + a])));
-                    if constexpr (FL) acc[k][1 + D + a] = fma(fx[1], V[a], fma(fx[0], Uq[a], acc[k][1 + D + a]));
-                }
+                for (int a = 0; a < D; ++a) acc[k][1 + a] = fma(wyz, Ex[a], fma(wx, U[a], acc[k][1 + a]));
             });
+            if constexpr (FL)
+                p2g_particle<T, D, MAT, 0, D, false>(P, in, lb, gb, [&](int k, int, T wx, T, T wyz, const T* U, const T* Ex) {
+#pragma unroll
+                    for (int a = 0; a < D; ++a) acc[k][1 + D + a] = fma(wyz, Ex[a], fma(wx, U[a], acc[k][1 + D + a]));
+                });
         }
         wave_sync();
 #pragma unroll
