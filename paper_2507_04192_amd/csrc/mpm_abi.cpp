@@ -135,7 +135,7 @@ Geo make_geo(const mpm_config& c)
 }
 
 struct Layout {
-    size_t st[2], pid[2], eps[2], key, perm, tmp, tmpk, count[2], range[2], tile_perm, tile_key, tile_off, tile_slot, active, part, meta, status;
+    size_t st[2], pid[2], eps[2], key, perm, tmp, tmpk, count[2], range[2], moved, tile_perm, tile_key, tile_off, tile_slot, active, cell_cnt, part, meta, status;
     size_t part_grid, gv, gmass, gvo;
     size_t inv, loss, box_sum, box_cnt, box_coef;
     size_t ckpt, ckpt_pid, tape, tape_pid, adj[2], mid, gtape, amu;
@@ -172,15 +172,17 @@ Layout make_layout(const mpm_config& c, const Geo& g, int64_t cap, int tape_step
     L.perm = take(ucap * 4);
     L.tmp = take(ucap * 4);
     L.tmpk = take(ucap * 4);
-    // 2-D steps alternate between two sets of counts and of the tiles' ranges
+    // steps alternate between two sets of the tiles' ranges, in 2-D of counts too
     for (int b = 0; b < 2; ++b) L.count[b] = (b == 0 || c.dim == 2) ? take((size_t)g.ntiles * 4) : 0;
-    for (int b = 0; b < 2; ++b) L.range[b] = c.dim == 2 ? take((size_t)g.ntiles * 8) : 0;
+    for (int b = 0; b < 2; ++b) L.range[b] = take((size_t)g.ntiles * 8);
+    L.moved = c.dim == 3 ? take((size_t)g.ntiles * 4) : 0;
     const bool rows = c.dim == 2 && g.ntiles <= kSmallTiles;
     L.tile_perm = rows ? take((size_t)g.ntiles * kTileRow * 4) : 0;
     L.tile_key = rows ? take((size_t)g.ntiles * kTileRow * 4) : 0;
     L.tile_off = take((size_t)g.ntiles * 4);
     L.tile_slot = take((size_t)g.ntiles * 4);
     L.active = take((size_t)g.ntiles * sizeof(ActiveTile));
+    L.cell_cnt = c.dim == 3 ? take((size_t)g.ntiles * 64 * 4) : 0;
     size_t nsb = (size_t)((g.ntiles + kScanChunk - 1) / kScanChunk);
     L.part = take(nsb * 2 * 4);
     L.meta = take(64 * 4);
@@ -350,11 +352,13 @@ int mpm_bind_workspace(mpm_ctx* c, void* dev_ptr, size_t bytes, int64_t n_partic
     const bool rows = c->cfg.dim == 2 && c->geo.ntiles <= kSmallTiles;
     c->tile_perm = rows ? (int32_t*)(b + L.tile_perm) : nullptr;
     c->tile_key = rows ? (int32_t*)(b + L.tile_key) : nullptr;
+    c->moved = (int32_t*)(b + L.moved);
     c->turn = 0;
     c->ranges_known = false;
     c->tile_off = (int32_t*)(b + L.tile_off);
     c->tile_slot = (int32_t*)(b + L.tile_slot);
     c->active = (ActiveTile*)(b + L.active);
+    c->cell_cnt = (int32_t*)(b + L.cell_cnt);
     c->part = (int32_t*)(b + L.part);
     c->meta = (int32_t*)(b + L.meta);
     c->status = (int32_t*)(b + L.status);

@@ -36,12 +36,10 @@ template <> struct TileShape<3> { static constexpr int TE = 4, BE = 6, NB = 216;
 template <> struct TileShape<2> { static constexpr int TE = 8, BE = 10, NB = 100; };
 
 constexpr int kSortCap = 1024;   // particles per tile sorted in LDS (larger: in perm)
-// threads of a P2G workgroup, one tile each: binary64 one wave; binary32 two
-// waves that share the tile's particles and split the node values between
-// them (mass and momentum x | the other momentum components)
-// With FLIP the node values double (momentum with and without the internal
-// force): binary32 then uses four waves per tile.
-template <class T, bool FL = false> constexpr int kP2GBlock = sizeof(T) == 4 ? (FL ? 256 : 128) : 64;
+// threads of a 3-D P2G workgroup, one tile each: two waves that split the node
+// values; with FLIP, whose node values double (momentum with and without the
+// internal force), four
+template <bool FL> constexpr int kP2GBlock = FL ? 256 : 128;
 // threads of a G2P workgroup (3-D binary64: smaller groups, measured faster)
 template <class T, int D> constexpr int kG2PBlock = sizeof(T) == 8 && D == 3 ? 128 : 256;
 // G2P loads the next tile's node block while it works on the current one
@@ -49,12 +47,12 @@ template <class T, int D> constexpr int kG2PBlock = sizeof(T) == 8 && D == 3 ? 1
 template <class T> constexpr bool kG2PPrefetch = sizeof(T) == 8;
 constexpr int kGridBlock = 128;  // threads of a grid-update workgroup
 
-// Particle data read once per step (P2G's inputs, G2P's old state) and the
-// part of G2P's output that no later kernel of the step reads (F or J, pid)
-// go through the non-temporal cache hint.  Measured on the 3-D cylinder:
-// binary32 P2G 106 -> 98 us, G2P 140 -> 137 us, binary64 P2G 200 -> 192,
-// G2P 256 -> 246; the hint on the stores that P2G reads next (x, v, C, the
-// stress cache) made G2P slower, so those stay ordinary stores.
+// Particle data read once per step (G2P's old state; P2G's inputs where the
+// state outgrows the caches, see p2g_hint) and the part of G2P's output that no
+// later kernel of the step reads (F or J, pid) go through the non-temporal
+// cache hint.  Measured on the 3-D cylinder: G2P 140 -> 137 us binary32, 256 ->
+// 246 binary64; the hint on the stores that P2G reads next (x, v, C, the stress
+// cache) made G2P slower, so those stay ordinary stores.
 template <class T>
 __device__ __forceinline__ T ld_once(const T* p)
 {
@@ -270,22 +268,23 @@ __device__ __forceinline__ void wave_sync()
 // The state of one particle that P2G reads for the momentum components
 // [A0, A1): the position, those components of v, those rows of C and the
 // stress cache.
-template <class T, int D, int MAT, int A0 = 0, int A1 = D>
+template <class T, int D, int MAT, int A0 = 0, int A1 = D, bool NTL = true>
 struct P2GIn {
     static constexpr int NS = mat_iso_stress(MAT) ? 1 : D * (D + 1) / 2;
     static constexpr int NA = A1 - A0;
     T x[D], v[NA], C[NA * D], S[NS];
+    static __device__ __forceinline__ T ld(const T* p) { return NTL ? ld_once(p) : *p; }
     __device__ __forceinline__ void load(const PView<T>& cur, int j)
     {
         const long long cap = cur.cap;
 #pragma unroll
-        for (int a = 0; a < D; ++a) x[a] = ld_once(&cur.x[a * cap + j]);
+        for (int a = 0; a < D; ++a) x[a] = ld(&cur.x[a * cap + j]);
 #pragma unroll
-        for (int a = 0; a < NA; ++a) v[a] = ld_once(&cur.v[(A0 + a) * cap + j]);
+        for (int a = 0; a < NA; ++a) v[a] = ld(&cur.v[(A0 + a) * cap + j]);
 #pragma unroll
-        for (int q = 0; q < NA * D; ++q) C[q] = ld_once(&cur.C[(A0 * D + q) * cap + j]);
+        for (int q = 0; q < NA * D; ++q) C[q] = ld(&cur.C[(A0 * D + q) * cap + j]);
 #pragma unroll
-        for (int q = 0; q < NS; ++q) S[q] = ld_once(&cur.S[q * cap + j]);
+        for (int q = 0; q < NS; ++q) S[q] = ld(&cur.S[q * cap + j]);
     }
 };
 
@@ -312,8 +311,8 @@ __host__ __device__ constexpr int sym_index(int a, int b)
 // sink(k, n, wx, mw, wyz, U, Ex) receives the offset index k, the node's index n
 // in the tile's LDS block, the factors of the mass w_x mw and of P_a = w_x U_a +
 // wyz Ex_a.
-template <class T, int D, int MAT, int A0, int A1, bool FORCE, class Sink>
-__device__ __forceinline__ void p2g_particle(const Phys<T>& P, const P2GIn<T, D, MAT, A0, A1>& in, const int lb[3],
+template <class T, int D, int MAT, int A0, int A1, bool FORCE, bool NTL, class Sink>
+__device__ __forceinline__ void p2g_particle(const Phys<T>& P, const P2GIn<T, D, MAT, A0, A1, NTL>& in, const int lb[3],
                                              const int gb[3], Sink&& sink)
 {
     constexpr int BE = TileShape<D>::BE, NA = A1 - A0;
@@ -409,35 +408,378 @@ __device__ __forceinline__ int rank_major_pos(int c, int q, const unsigned long 
     return r;
 }
 
-// Binary32 P2G of one lane (cell) for the momentum components [A0, A1)
-// (and the mass when MASS): the lane sums the particles of its cell in
-// registers (they all hit the same 3^D nodes), the next particle's state
-// loaded while this one is spread, then adds its sums to node arrays
-// [Q0, Q0 + NQ) of the tile's LDS block.  With QV the sums are those of the
-// momentum without the internal force (node arrays 1 + D + a, for FLIP).
-// The lanes of a wave write distinct nodes per offset and wave_sync orders
-// the offsets.
-template <class T, int D, int MAT, int A0, int A1, bool MASS, bool QV>
-__device__ __forceinline__ void p2g_lane_sums(const Phys<T>& P, const PView<T>& cur, const int* sorted, int lane,
-                                              int mycnt, const int lb[3], const int gb[3],
-                                              const unsigned long long* s_rmask, const int* s_roff,
-                                              const int* s_cnt, T (*node)[TileShape<D>::NB])
+// ---------------------------------------------------------------------------
+// Sort inside a tile: by rank within the cell (previous slot order), then by
+// cell, so that the r-th particles of the 64 cells are adjacent in memory
+// ---------------------------------------------------------------------------
+
+struct TileSort {
+    int cnt[64], off[64], cur[64], roff[64];
+    unsigned long long rmask[64];
+    int unord[kSortCap], sorted[kSortCap];
+    unsigned char ucell[kSortCap];
+    int found;
+};
+
+// One wave: from the histogram cnt the cells' offsets, the number of particles
+// found and the rank table (cells with more than q particles, and the count of
+// earlier ranks).
+__device__ __forceinline__ void tile_sort_scan(TileSort& s, int lane)
+{
+    const int v = s.cnt[lane];
+    int inc = v;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const int t = __shfl_up(inc, o);
+        if (lane >= o) inc += t;
+    }
+    s.off[lane] = inc - v;
+    if (lane == 63) s.found = inc;
+    int run = 0;
+    for (int q = 0; q < 64; ++q) {
+        const unsigned long long m = __ballot(v > q);
+        if (!m) break;
+        if (lane == 0) {
+            s.rmask[q] = m;
+            s.roff[q] = run;
+        }
+        run += __popcll(m);
+    }
+}
+
+// Notes the particle of slot j in its cell's range (arbitrary order inside):
+// in LDS, or for a crowded tile in the tile's range of perm.
+__device__ __forceinline__ void tile_sort_place(TileSort& s, bool in_lds, int c, int j, int* __restrict__ perm_tile)
+{
+    const int u = s.off[c] + atomicAdd(&s.cur[c], 1);
+    if (in_lds) {
+        s.unord[u] = j;
+        s.ucell[u] = (unsigned char)c;
+    } else {
+        perm_tile[u] = j;
+    }
+}
+
+// Ranks the placed particles inside their cells by previous slot and writes
+// the tile's range of perm.  Tiles of up to kSortCap particles in LDS (s.sorted
+// holds the order afterwards); crowded tiles stage the result in their range of
+// tmp, whose bucketed entries are no longer needed.
+template <int NT>
+__device__ __forceinline__ void tile_sort_finish(TileSort& s, bool in_lds, int cnt, int* __restrict__ perm_tile,
+                                                 int* __restrict__ tmp_tile)
+{
+    const int tid = threadIdx.x;
+    if (in_lds) {
+        __syncthreads();
+        for (int u = tid; u < cnt; u += NT) {
+            const int c = s.ucell[u], j = s.unord[u];
+            const int o = s.off[c], n = s.cnt[c], last = o + n - 1;
+            int rank = 0;
+            // four independent LDS reads per pass; reads past the cell's range
+            // repeat its last entry and are not counted
+            for (int q = 0; q < n; q += 4) {
+                int e[4];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) e[i] = s.unord[min(o + q + i, last)];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) rank += (q + i < n && e[i] < j) ? 1 : 0;
+            }
+            s.sorted[rank_major_pos(c, rank, s.rmask, s.roff, s.cnt)] = j;
+        }
+        __syncthreads();
+        for (int k = tid; k < cnt; k += NT) perm_tile[k] = s.sorted[k];
+    } else {
+        __threadfence_block();
+        __syncthreads();
+        for (int k = tid; k < cnt; k += NT) {
+            int lo = 0;
+#pragma unroll
+            for (int step = 32; step >= 1; step >>= 1)
+                if (lo + step < 64 && s.off[lo + step] <= k) lo += step;
+            const int j = perm_tile[k], o = s.off[lo], n = s.cnt[lo];
+            int rank = 0;
+            for (int q = 0; q < n; ++q) rank += perm_tile[o + q] < j;
+            tmp_tile[rank_major_pos(lo, rank, s.rmask, s.roff, s.cnt)] = j;
+        }
+        __threadfence_block();
+        __syncthreads();
+        const volatile int* rm = tmp_tile;
+        for (int k = tid; k < cnt; k += NT) perm_tile[k] = rm[k];
+        __threadfence_block();
+        __syncthreads();
+    }
+}
+
+// The previous step's layout and this step's, for kernels that gather.
+struct Ranges {
+    int* count;              // particles per tile, by the current keys
+    int* count_next;         // 2-D: cleared for this step's G2P (3-D: count itself is)
+    const int2* range;       // previous sort: first slot and number of each tile's particles
+    int2* range_next;        // this sort
+    int* moved;              // 3-D: bit per neighbour that particles came from (cleared for this step's G2P)
+    const int* key;
+    const int* tile_key;     // 2-D: the first kTileRow keys of every tile's range, a row per tile
+    int* tile_perm;          // 2-D: the same of perm (null: not kept)
+    long long N;
+};
+
+// 3-D: sorts each tile's particles into perm and keeps the cells' counts for
+// P2G, in a kernel of its own: the sort is a chain of round trips that needs few
+// registers, P2G a stream that fills them.
+//
+// Where the previous step's layout is known, the particles are found where that
+// step left them, without the scatter over the grid.  G2P left those of each
+// tile in one range of slots, their new keys beside them, and set a bit of the
+// destination's word for every neighbour that one came from; a tile reads the
+// keys of its own range and of the few ranges marked.  Ranges follow the order
+// of the tiles, so taken in that order the particles come by ascending slot, and
+// a particle's rank is the number already seen in its cell: one wave per tile
+// counts along, 64 keys at a time (lanes of one cell are found by six ballots),
+// and no wave waits for another.  A step moves a particle to a neighbouring tile
+// at most; a tile that finds fewer than its count (a step beyond the CFL limit,
+// keys written anew) goes through all keys.
+// Cylinder, 2,780,000 particles: 15 us, where the scatter took 13 and the sort,
+// by LDS placement inside P2G at its three waves per SIMD, about 25 of P2G's 94
+// (binary32; 19 in a kernel of its own).  It waits for its four dependent round
+// trips, one more for each two ranges marked.
+constexpr int kSortBlock = 256;
+constexpr int kOwnBatches = 8;   // batches of a tile's own range held in registers (512 particles, 8 per cell)
+
+template <int Unused = 0>
+__global__ __launch_bounds__(kSortBlock) void k_sort_gather(Geo g, Ranges rg, const int* __restrict__ meta,
+                                                            const ActiveTile* __restrict__ active, int* __restrict__ tmp,
+                                                            int* __restrict__ tmpk, int* __restrict__ perm,
+                                                            int* __restrict__ cell_cnt)
+{
+    constexpr int NW = kSortBlock / 64;
+    __shared__ int s_cnt[NW][64], s_roff[NW][64];
+    __shared__ unsigned long long s_rmask[NW][64];
+    const int n_active = meta[0];
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const unsigned long long below = (1ull << lane) - 1ull;
+    int* cnt = s_cnt[w];
+    // entries by wave: one contiguous chunk of the active list per XCD
+    const int chunk = (n_active + 7) / 8, xcd = blockIdx.x % 8, per = (int)(gridDim.x / 8) * NW;
+    const int end = min((xcd + 1) * chunk, n_active);
+    for (int e = xcd * chunk + (int)(blockIdx.x / 8) * NW + w; e < end; e += per) {
+        const ActiveTile at = active[e];
+        const int2 own = rg.range[at.tile];
+        const unsigned from = (unsigned)rg.moved[at.tile];
+        int tc[3];
+        tile_coords(g, at.tile, tc);
+        // lane q: the range of neighbour q where particles came from
+        int2 nb = make_int2(0, 0);
+        {
+            const int tx = tc[0] + lane % 3 - 1, ty = tc[1] + (lane / 3) % 3 - 1, tz = tc[2] + lane / 9 - 1;
+            if (lane < 27 && ((from >> lane) & 1) && tx >= 0 && ty >= 0 && tz >= 0 && tx < g.ntile[0] && ty < g.ntile[1] &&
+                tz < g.ntile[2])
+                nb = rg.range[(tz * g.ntile[1] + ty) * g.ntile[0] + tx];
+        }
+        int ck[kOwnBatches];   // keys of the own range, then cell | rank << 6, or -1
+#pragma unroll
+        for (int q = 0; q < kOwnBatches; ++q) ck[q] = q * 64 + lane < own.y ? rg.key[own.x + q * 64 + lane] : -1;
+        cnt[lane] = 0;
+        wave_sync();
+        int found = 0, listed = 0;
+        // the next 64 keys in slot order: cell | rank << 6 of those of this tile
+        auto count = [&](int key) {
+            const bool mine = (key >> 6) == at.tile;
+            const unsigned long long m = __ballot(mine);
+            if (!m) return -1;
+            const int c = key & 63;
+            unsigned long long same = m;
+#pragma unroll
+            for (int b = 0; b < 6; ++b) {
+                const unsigned long long bits = __ballot((c >> b) & 1);
+                same &= ((c >> b) & 1) ? bits : ~bits;
+            }
+            found += __popcll(m);
+            int r = -1;
+            if (mine) {
+                const int rk = __popcll(same & below), base = cnt[c];
+                r = c | (base + rk) << 6;
+                if (rk == 0) cnt[c] = base + __popcll(same);
+            }
+            wave_sync();
+            return r;
+        };
+        // a range whose particles go to a list in the tile's range of tmp, tmpk
+        auto list = [&](int first, int num) {
+            for (int u0 = 0; u0 < num; u0 += 64 * 4) {
+                int k[4];
+#pragma unroll
+                for (int q = 0; q < 4; ++q) k[q] = u0 + q * 64 + lane < num ? rg.key[first + u0 + q * 64 + lane] : -1;
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const int r = count(k[q]);
+                    const unsigned long long m = __ballot(r >= 0);
+                    const int at_list = listed + __popcll(m & below);
+                    if (r >= 0 && at_list < at.cnt) {
+                        tmp[at.off + at_list] = first + u0 + q * 64 + lane;
+                        tmpk[at.off + at_list] = r;
+                    }
+                    listed += __popcll(m);
+                }
+            }
+        };
+        bool held = own.y <= kOwnBatches * 64;   // the own range's particles stay in ck
+        for (unsigned b = from & 0x1fffu; b; b &= b - 1) {
+            const int q = __ffs((int)b) - 1;
+            list(__shfl(nb.x, q), __shfl(nb.y, q));
+        }
+        if (held) {
+#pragma unroll
+            for (int q = 0; q < kOwnBatches; ++q) ck[q] = count(ck[q]);
+        } else {
+            list(own.x, own.y);
+        }
+        for (unsigned b = from & 0x7ffc000u; b; b &= b - 1) {
+            const int q = __ffs((int)b) - 1;
+            list(__shfl(nb.x, q), __shfl(nb.y, q));
+        }
+        if (found != at.cnt) {
+            cnt[lane] = 0;
+            wave_sync();
+            found = listed = 0;
+            held = false;
+            list(0, (int)rg.N);
+        }
+        if (lane == 0) {
+            rg.moved[at.tile] = 0;
+            rg.count[at.tile] = 0;
+        }
+        // rank table, then every particle's place
+        const int v = cnt[lane];
+        cell_cnt[e * 64 + lane] = v;
+        int run = 0;
+        for (int q = 0; q < 64; ++q) {
+            const unsigned long long m = __ballot(v > q);
+            if (!m) break;
+            if (lane == 0) {
+                s_rmask[w][q] = m;
+                s_roff[w][q] = run;
+            }
+            run += __popcll(m);
+        }
+        wave_sync();
+        int* out = perm + at.off;
+        if (held) {
+#pragma unroll
+            for (int q = 0; q < kOwnBatches; ++q)
+                if (ck[q] >= 0) out[rank_major_pos(ck[q] & 63, ck[q] >> 6, s_rmask[w], s_roff[w], cnt)] = own.x + q * 64 + lane;
+        }
+        __threadfence_block();   // the list was written by this wave
+        for (int u = lane; u < listed; u += 64) {
+            const int r = ((const volatile int*)tmpk)[at.off + u];
+            out[rank_major_pos(r & 63, r >> 6, s_rmask[w], s_roff[w], cnt)] = ((const volatile int*)tmp)[at.off + u];
+        }
+        wave_sync();
+    }
+}
+
+// The same from the bucketed entries of each tile, which come in no order: by
+// placement into the cells and counting, in LDS.
+template <int Unused = 0>
+__global__ __launch_bounds__(kSortBlock) void k_sort(const int* __restrict__ meta, const ActiveTile* __restrict__ active,
+                                                     int* __restrict__ tmp, const int* __restrict__ tmpk,
+                                                     int* __restrict__ perm, int* __restrict__ cell_cnt)
+{
+    constexpr int NT = kSortBlock, U = (kSortCap + NT - 1) / NT;
+    __shared__ TileSort s;
+    const int n_active = meta[0];
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    for (int it = 0;; ++it) {
+        const int e = tile_entry(it, n_active);
+        if (e < 0) break;
+        const ActiveTile at = active[e];
+        if (tid < 64) {
+            s.cnt[tid] = 0;
+            s.cur[tid] = 0;
+        }
+        const bool in_lds = at.cnt <= kSortCap;
+        // a tile that fits LDS keeps its entries in registers: one batch of loads
+        int cc[U], cj[U];
+        if (in_lds)
+#pragma unroll
+            for (int q = 0; q < U; ++q) {
+                const int u = q * NT + tid;
+                cc[q] = u < at.cnt ? tmpk[at.off + u] & 63 : -1;   // the cell is the low 6 bits of the key
+                cj[q] = u < at.cnt ? tmp[at.off + u] : 0;
+            }
+        __syncthreads();
+        if (in_lds) {
+#pragma unroll
+            for (int q = 0; q < U; ++q)
+                if (cc[q] >= 0) atomicAdd(&s.cnt[cc[q]], 1);
+        } else {
+            for (int k = tid; k < at.cnt; k += NT) atomicAdd(&s.cnt[tmpk[at.off + k] & 63], 1);
+        }
+        __syncthreads();
+        if (w == 0) {
+            tile_sort_scan(s, lane);
+            cell_cnt[e * 64 + lane] = s.cnt[lane];
+        }
+        __syncthreads();
+        if (in_lds) {
+#pragma unroll
+            for (int q = 0; q < U; ++q)
+                if (cc[q] >= 0) tile_sort_place(s, true, cc[q], cj[q], perm + at.off);
+        } else {
+            for (int k = tid; k < at.cnt; k += NT) tile_sort_place(s, false, tmpk[at.off + k] & 63, tmp[at.off + k], perm + at.off);
+        }
+        tile_sort_finish<NT>(s, in_lds, at.cnt, perm + at.off, tmp + at.off);
+        __syncthreads();
+    }
+}
+
+// ---------------------------------------------------------------------------
+// 3-D: P2G
+// ---------------------------------------------------------------------------
+
+// P2G of one wave, lane = cell: round r takes the particle of rank r of every
+// cell that has one; the lanes of a round read adjacent slots.  A cell's
+// particles all hit the same 27 nodes, so a lane sums them in registers: the
+// momentum components [A0, A1) (and the mass when MASS; with QV those of the
+// momentum without the internal force, node arrays 1 + D + a, for FLIP), then
+// adds its sums to the wave's own node arrays, lanes on distinct nodes per
+// offset, ordered by wave_sync.  Slots are fetched two rounds ahead and
+// particles one.
+template <class T, int D, int MAT, int A0, int A1, bool MASS, bool QV, bool NTL>
+__device__ __forceinline__ void p2g_wave(const Phys<T>& P, const PView<T>& cur, const int* __restrict__ perm_tile, int mycnt,
+                                         const int lb[3], const int gb[3], T (*node)[TileShape<D>::NB])
 {
     static_assert(!(MASS && QV), "the mass travels with the momentum including the force");
-    constexpr int NK = (D == 3) ? 27 : 9;
+    constexpr int NK = (D == 3) ? 27 : 9, NB = TileShape<D>::NB;
     constexpr int M = MASS ? 1 : 0;
-    constexpr int NQ = M + A1 - A0;             // node values of this wave
+    constexpr int NQ = M + A1 - A0;                          // node values of this wave
     constexpr int Q0 = M ? 0 : (QV ? 1 + D + A0 : 1 + A0);   // its first node array
+    const int lane = threadIdx.x & 63;
+    for (int i = lane; i < NQ * NB; i += 64) (&node[Q0][0])[i] = T(0);
     T acc[NK][NQ];
 #pragma unroll
     for (int k = 0; k < NK; ++k)
 #pragma unroll
         for (int q = 0; q < NQ; ++q) acc[k][q] = T(0);
-    P2GIn<T, D, MAT, A0, A1> nx;
-    if (mycnt > 0) nx.load(cur, sorted[rank_major_pos(lane, 0, s_rmask, s_roff, s_cnt)]);
+    // slot of this lane's particle of rank r: the particles of earlier ranks,
+    // then those of rank r in earlier cells (called by the lanes that still have
+    // particles, in step)
+    int before = 0;
+    auto slot = [&](int r) {
+        const unsigned long long m = __ballot(mycnt > r);
+        const int pos = before + (int)__builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)m, 0u));
+        before += __popcll(m);
+        return mycnt > r ? perm_tile[pos] : 0;
+    };
+    int j1 = slot(0);
+    P2GIn<T, D, MAT, A0, A1, NTL> nx;
+    if (mycnt > 0) nx.load(cur, j1);
+    j1 = slot(1);
+    wave_sync();
     for (int r = 0; r < mycnt; ++r) {
-        const P2GIn<T, D, MAT, A0, A1> in = nx;
-        if (r + 1 < mycnt) nx.load(cur, sorted[rank_major_pos(lane, r + 1, s_rmask, s_roff, s_cnt)]);
+        const P2GIn<T, D, MAT, A0, A1, NTL> in = nx;
+        const int j = j1;
+        j1 = slot(r + 2);
+        if (r + 1 < mycnt) nx.load(cur, j);
         // the products go straight into the sums (one FMA each)
         p2g_particle<T, D, MAT, A0, A1, !QV>(P, in, lb, gb, [&](int k, int, T wx, T mw, T wyz, const T* U, const T* Ex) {
             if constexpr (MASS) acc[k][0] = fma(wx, mw, acc[k][0]);
@@ -445,165 +787,43 @@ __device__ __forceinline__ void p2g_lane_sums(const Phys<T>& P, const PView<T>& 
             for (int a = 0; a < A1 - A0; ++a) acc[k][M + a] = fma(wyz, Ex[a], fma(wx, U[a], acc[k][M + a]));
         });
     }
-    if (mycnt > 0) {
 #pragma unroll
-        for (int k = 0; k < NK; ++k) {
-            int n = block_node<D>(lb, k);
-            T cv[NQ];
+    for (int k = 0; k < NK; ++k) {
+        int n = block_node<D>(lb, k);
+        T cv[NQ];
 #pragma unroll
-            for (int q = 0; q < NQ; ++q) cv[q] = node[Q0 + q][n];
+        for (int q = 0; q < NQ; ++q) cv[q] = node[Q0 + q][n];
 #pragma unroll
-            for (int q = 0; q < NQ; ++q) node[Q0 + q][n] = cv[q] + acc[k][q];
-            wave_sync();
-        }
-    } else {
-#pragma unroll
-        for (int k = 0; k < NK; ++k) wave_sync();
+        for (int q = 0; q < NQ; ++q) node[Q0 + q][n] = cv[q] + acc[k][q];
+        wave_sync();
     }
 }
 
-// P2G, one tile per workgroup.  The workgroup (1) sorts the tile's particles
-// into perm: by rank within their cell (previous slot order), then by cell,
-// so that the r-th particles of the 64 cells are adjacent in memory; (2)
-// takes them in rounds, lane c holding the r-th particle of cell c for
-// r = 0, 1, ... (the lanes of a round read adjacent slots), binary32 with
-// two waves that split the node values; (3) writes the tile's node block
-// (mass, momentum; with FLIP also the momentum without the internal force)
-// to its partial block.  Register budget: three waves per SIMD in binary32
-// (168 registers), two in binary64.
-template <class T, int D, int MAT, bool FL>
-__global__ __launch_bounds__((kP2GBlock<T, FL>)) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 3 : 2))) void k_p2g(Geo g, Phys<T> P, const int* __restrict__ meta,
-                                                const ActiveTile* __restrict__ active, int* __restrict__ tmp,
-                                                const int* __restrict__ tmpk, PView<T> cur, int* __restrict__ perm,
+// One tile per workgroup, whose waves share the tile's particles and split the
+// node values, so that the sums fit registers: mass and momentum x | the other
+// components; with FLIP the same again for the momentum without the internal
+// force.  No wave waits for another: each clears, sums and writes out its own
+// node arrays.  NTL: the particles are read with the non-temporal hint.
+// What bounds it is reading the particles: cylinder, 2,780,000 particles,
+// binary32 94 us with the sort inside -> 72 (234 MB of state it must read, 260
+// to 330 MB moved), binary64 190 (one wave, LDS atomics at 4 lanes a clock) ->
+// 143, FLIP binary64 (635,000) 90 -> 50.
+template <class T, int D, int MAT, bool FL, bool NTL>
+__global__ __launch_bounds__((kP2GBlock<FL>)) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 3 : 2))) void k_p2g(Geo g, Phys<T> P, const int* __restrict__ meta,
+                                                const ActiveTile* __restrict__ active, const int* __restrict__ cell_cnt,
+                                                PView<T> cur, const int* __restrict__ perm,
                                                 T* __restrict__ part)
 {
     constexpr int TE = TileShape<D>::TE, NB = TileShape<D>::NB;
-    constexpr int NT = kP2GBlock<T, FL>;
     constexpr int NV = FL ? 2 * D + 1 : D + 1;          // node values per block node
-    constexpr bool kRegAcc = sizeof(T) == 4;            // binary32: sums in registers
     __shared__ T s_node[NV][NB];
-    __shared__ int s_cnt[64], s_off[64], s_cur[64];
-    __shared__ int s_unord[kSortCap], s_sorted[kSortCap];
-    __shared__ unsigned char s_ucell[kSortCap];
-    __shared__ int s_max;
-    __shared__ unsigned long long s_rmask[64];
-    __shared__ int s_roff[64];
     const int n_active = meta[0];
-    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     for (int it = 0;; ++it) {
         int e = tile_entry(it, n_active);
         if (e < 0) break;
         const ActiveTile at = active[e];
-        for (int i = tid; i < NV * NB; i += NT) (&s_node[0][0])[i] = T(0);
-        if (tid < 64) { s_cnt[tid] = 0; s_cur[tid] = 0; }
-        __syncthreads();
-        const bool in_lds = at.cnt <= kSortCap;
-        // A tile that fits in LDS keeps its particles' cells and slots in
-        // registers (thread t holds entries t, t + NT, ...): one batch of global
-        // loads instead of one round trip per pass below.
-        constexpr int KPL = (kSortCap + NT - 1) / NT;   // register slots per thread: KPL * NT >= kSortCap
-        static_assert(KPL * NT >= kSortCap, "the register batch must cover an in-LDS tile");
-        const int nk = at.cnt - tid;                 // entry i * NT of this thread exists if below
-        const int* tk = tmpk + at.off + tid;
-        const int* tj = tmp + at.off + tid;
-        int rc[KPL], rj[KPL];
-        if (in_lds) {
-#pragma unroll
-            for (int i = 0; i < KPL; ++i)
-                if (i * NT < nk) {
-                    rc[i] = tk[i * NT] & 63;   // the cell is the low 6 bits of the key
-                    rj[i] = tj[i * NT];
-                }
-#pragma unroll
-            for (int i = 0; i < KPL; ++i)
-                if (i * NT < nk) atomicAdd(&s_cnt[rc[i]], 1);
-        } else {
-            for (int k = tid; k < at.cnt; k += NT) atomicAdd(&s_cnt[tmpk[at.off + k] & 63], 1);
-        }
-        __syncthreads();
-        if (tid < 64) {
-            int v = s_cnt[lane], inc = v, mx = v;
-#pragma unroll
-            for (int o = 1; o < 64; o <<= 1) {
-                int t = __shfl_up(inc, o);
-                if (lane >= o) inc += t;
-                mx = max(mx, __shfl_xor(mx, o));
-            }
-            s_off[lane] = inc - v;
-            if (lane == 0) s_max = mx;
-            // rank table: cells with more than q particles, earlier ranks' count
-            int run = 0;
-            const int lim = mx < 64 ? mx : 64;
-            for (int q = 0; q < lim; ++q) {
-                unsigned long long m = __ballot(v > q);
-                if (lane == 0) {
-                    s_rmask[q] = m;
-                    s_roff[q] = run;
-                }
-                run += __popcll(m);
-            }
-        }
-        __syncthreads();
-        if (in_lds) {
-            // place each particle in its cell's range (arbitrary order inside)
-            // and note the cell of each position; then rank every particle
-            // inside its cell by previous slot: a stable order
-#pragma unroll
-            for (int i = 0; i < KPL; ++i) {
-                if (i * NT >= nk) continue;
-                const int u = s_off[rc[i]] + atomicAdd(&s_cur[rc[i]], 1);
-                s_unord[u] = rj[i];
-                s_ucell[u] = (unsigned char)rc[i];
-            }
-            __syncthreads();
-            for (int u = tid; u < at.cnt; u += NT) {
-                const int c = s_ucell[u], j = s_unord[u];
-                const int o = s_off[c], n = s_cnt[c], last = o + n - 1;
-                int rank = 0;
-                // four independent LDS reads per pass; reads past the cell's
-                // range repeat its last entry and are not counted
-                for (int q = 0; q < n; q += 4) {
-                    int e[4];
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) e[i] = s_unord[min(o + q + i, last)];
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) rank += (q + i < n && e[i] < j) ? 1 : 0;
-                }
-                s_sorted[rank_major_pos(c, rank, s_rmask, s_roff, s_cnt)] = j;
-            }
-            __syncthreads();
-            for (int k = tid; k < at.cnt; k += NT) perm[at.off + k] = s_sorted[k];
-        } else {
-            // crowded tile: the same placement and rank-by-counting, with the
-            // cell-major placement in perm and the rank-major result staged in
-            // this tile's range of tmp (its bucketed input is no longer
-            // needed), then copied back to perm
-            int* unord = perm + at.off;
-            for (int k = tid; k < at.cnt; k += NT) {
-                int c = tmpk[at.off + k] & 63;
-                int pos = atomicAdd(&s_cur[c], 1);
-                unord[s_off[c] + pos] = tmp[at.off + k];
-            }
-            __threadfence_block();
-            __syncthreads();
-            for (int k = tid; k < at.cnt; k += NT) {
-                int p = k, lo = 0;
-#pragma unroll
-                for (int step = 32; step >= 1; step >>= 1)
-                    if (lo + step < 64 && s_off[lo + step] <= p) lo += step;
-                const int j = unord[p], o = s_off[lo], n = s_cnt[lo];
-                int rank = 0;
-                for (int q = 0; q < n; ++q) rank += unord[o + q] < j;
-                tmp[at.off + rank_major_pos(lo, rank, s_rmask, s_roff, s_cnt)] = j;
-            }
-            __threadfence_block();
-            __syncthreads();
-            const volatile int* rm = tmp + at.off;
-            for (int k = tid; k < at.cnt; k += NT) unord[k] = rm[k];
-            __threadfence_block();
-            __syncthreads();
-        }
-        const int* sorted = in_lds ? s_sorted : (perm + at.off);
+        const int mycnt = cell_cnt[e * 64 + lane];
         int tc[3];
         tile_coords(g, at.tile, tc);
         // The lane's cell, made opaque to the compiler for this tile: what is
@@ -618,54 +838,28 @@ __global__ __launch_bounds__((kP2GBlock<T, FL>)) __attribute__((amdgpu_waves_per
         lb[2] = (D == 3) ? cl / (TE * TE) : 0;
 #pragma unroll
         for (int a = 0; a < 3; ++a) gb[a] = tc[a] * TE + lb[a] - g.G;
-        const int mycnt = s_cnt[cl], maxc = s_max;
-        if constexpr (kRegAcc) {
-            // binary32: lane c of each wave sums the particles of cell c in
-            // registers (they all hit the same 3^D nodes), wave 0 the mass and
-            // momentum x, wave 1 the other momentum components, then adds its
-            // sums to the tile's LDS block; the waves write different node
-            // arrays, the lanes of a wave distinct nodes per offset, and
-            // wave_sync orders the offsets
-            // (with FLIP, waves 2 and 3 the same for the momentum without the
-            // internal force)
-            T (*node)[NB] = s_node;
-            if (w == 0)
-                p2g_lane_sums<T, D, MAT, 0, 1, true, false>(P, cur, sorted, cl, mycnt, lb, gb, s_rmask, s_roff, s_cnt, node);
-            else if (w == 1)
-                p2g_lane_sums<T, D, MAT, 1, D, false, false>(P, cur, sorted, cl, mycnt, lb, gb, s_rmask, s_roff, s_cnt, node);
-            else if constexpr (FL) {
-                if (w == 2)
-                    p2g_lane_sums<T, D, MAT, 0, 1, false, true>(P, cur, sorted, cl, mycnt, lb, gb, s_rmask, s_roff, s_cnt, node);
-                else
-                    p2g_lane_sums<T, D, MAT, 1, D, false, true>(P, cur, sorted, cl, mycnt, lb, gb, s_rmask, s_roff, s_cnt, node);
-            }
-        } else {
-            // binary64 (one wave): hardware LDS atomics (ds_add_f64) into the
-            // tile's block, issued without waiting; lanes hit distinct nodes
-            // per offset, so the summation order is fixed
-            for (int r = 0; r < maxc; ++r) {
-                if (r < mycnt) {
-                    P2GIn<T, D, MAT> in;
-                    in.load(cur, sorted[rank_major_pos(cl, r, s_rmask, s_roff, s_cnt)]);
-                    p2g_particle<T, D, MAT, 0, D, true>(P, in, lb, gb,
-                                                        [&](int, int n, T wx, T mw, T wyz, const T* U, const T* Ex) {
-                        atomicAdd(&s_node[0][n], wx * mw);
-#pragma unroll
-                        for (int a = 0; a < D; ++a) atomicAdd(&s_node[1 + a][n], fma(wyz, Ex[a], wx * U[a]));
-                    });
-                    if constexpr (FL)
-                        p2g_particle<T, D, MAT, 0, D, false>(P, in, lb, gb,
-                                                             [&](int, int n, T wx, T, T wyz, const T* U, const T* Ex) {
-#pragma unroll
-                            for (int a = 0; a < D; ++a) atomicAdd(&s_node[1 + D + a][n], fma(wyz, Ex[a], wx * U[a]));
-                        });
-                }
+        T (*node)[NB] = s_node;
+        const int* pt = perm + at.off;
+        int q0 = 0, q1 = NV;                            // this wave's node arrays
+        if (w == 0) {
+            p2g_wave<T, D, MAT, 0, 1, true, false, NTL>(P, cur, pt, mycnt, lb, gb, node);
+            q1 = 2;
+        } else if (w == 1) {
+            p2g_wave<T, D, MAT, 1, D, false, false, NTL>(P, cur, pt, mycnt, lb, gb, node);
+            q0 = 2, q1 = 1 + D;
+        } else if constexpr (FL) {
+            if (w == 2) {
+                p2g_wave<T, D, MAT, 0, 1, false, true, NTL>(P, cur, pt, mycnt, lb, gb, node);
+                q0 = 1 + D, q1 = 2 + D;
+            } else {
+                p2g_wave<T, D, MAT, 1, D, false, true, NTL>(P, cur, pt, mycnt, lb, gb, node);
+                q0 = 2 + D;
             }
         }
-        __syncthreads();
+        wave_sync();
         T* dst = part + (long long)e * NV * NB;
-        for (int i = tid; i < NV * NB; i += NT) dst[i] = (&s_node[0][0])[i];
-        __syncthreads();
+        for (int i = q0 * NB + lane; i < q1 * NB; i += 64) dst[i] = (&s_node[0][0])[i];
+        wave_sync();
     }
 }
 
@@ -698,18 +892,6 @@ __global__ __launch_bounds__((kP2GBlock<T, FL>)) __attribute__((amdgpu_waves_per
 // 131,072: 37.8, 36.1, 38.6).
 constexpr int kSortMany2 = 128;
 
-// The previous step's layout and this step's, for kernels that gather.
-struct Ranges2 {
-    const int* count;        // particles per tile, by the current keys
-    int* count_next;         // cleared here for this step's G2P
-    const int2* range;       // previous sort: first slot and number of each tile's particles
-    int2* range_next;        // this sort
-    const int* key;
-    const int* tile_key;     // the first kTileRow keys of every tile's range, a row per tile
-    int* tile_perm;          // the same of perm (null: not kept)
-    long long N;
-};
-
 // Tile of a workgroup when there is one per tile: a contiguous chunk of tiles
 // on each XCD (workgroup b runs on XCD b % 8).  -1 past the end.
 __device__ __forceinline__ int tile_of_block(int ntiles)
@@ -732,7 +914,7 @@ __device__ __forceinline__ int tile_of_block(int ntiles)
 // G2P 6.2; what bounds both is the chain of launch, two memory round trips,
 // LDS phases and the drain of the stores.
 template <class T, int MAT, bool FL, bool GATHER, int NT>
-__global__ __launch_bounds__(NT) void k_sort_p2g2(Geo g, Phys<T> P, Ranges2 rg, int* __restrict__ meta,
+__global__ __launch_bounds__(NT) void k_sort_p2g2(Geo g, Phys<T> P, Ranges rg, int* __restrict__ meta,
                                                            ActiveTile* __restrict__ active, int* __restrict__ tile_slot,
                                                            int* __restrict__ tmp, int* __restrict__ tmpk, PView<T> cur,
                                                            int* __restrict__ perm, T* __restrict__ part)
@@ -741,11 +923,8 @@ __global__ __launch_bounds__(NT) void k_sort_p2g2(Geo g, Phys<T> P, Ranges2 rg, 
     constexpr int NV = FL ? 2 * D + 1 : D + 1;   // node values per block node
     constexpr int NK = 9;
     __shared__ T s_node[NW][NV][NB];
-    __shared__ int s_cnt[64], s_off[64], s_cur[64], s_roff[64];
-    __shared__ unsigned long long s_rmask[64];
-    __shared__ int s_unord[kSortCap], s_sorted[kSortCap];
-    __shared__ unsigned char s_ucell[kSortCap];
-    __shared__ int s_sum[2][NW], s_first[9], s_num[9], s_found;
+    __shared__ TileSort ts;
+    __shared__ int s_sum[2][NW], s_first[9], s_num[9];
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     const int n_active = GATHER ? 0 : meta[0];
     constexpr int U = GATHER ? 9 : (kSortCap + NT - 1) / NT;
@@ -754,8 +933,8 @@ __global__ __launch_bounds__(NT) void k_sort_p2g2(Geo g, Phys<T> P, Ranges2 rg, 
         ActiveTile at;
         int cj[U], cc[U];   // candidates: slot, and key, then cell or -1
         if (tid < 64) {
-            s_cnt[tid] = 0;
-            s_cur[tid] = 0;
+            ts.cnt[tid] = 0;
+            ts.cur[tid] = 0;
         }
         if constexpr (GATHER) {
             const int t = it == 0 ? tile_of_block(g.ntiles) : -1;
@@ -858,41 +1037,19 @@ __global__ __launch_bounds__(NT) void k_sort_p2g2(Geo g, Phys<T> P, Ranges2 rg, 
                 batch(u0);
 #pragma unroll
                 for (int q = 0; q < U; ++q)
-                    if (cc[q] >= 0) atomicAdd(&s_cnt[cc[q]], 1);
+                    if (cc[q] >= 0) atomicAdd(&ts.cnt[cc[q]], 1);
             }
             __syncthreads();
-            if (w == 0) {
-                const int v = s_cnt[lane];
-                int inc = v;
-#pragma unroll
-                for (int o = 1; o < 64; o <<= 1) {
-                    const int t = __shfl_up(inc, o);
-                    if (lane >= o) inc += t;
-                }
-                s_off[lane] = inc - v;
-                if (lane == 63) s_found = inc;
-                // rank table: cells with more than q particles, earlier ranks' count
-                int run = 0;
-                for (int q = 0; q < 64; ++q) {
-                    const unsigned long long m = __ballot(v > q);
-                    if (!m) break;
-                    if (lane == 0) {
-                        s_rmask[q] = m;
-                        s_roff[q] = run;
-                    }
-                    run += __popcll(m);
-                }
-            }
+            if (w == 0) tile_sort_scan(ts, lane);
             __syncthreads();
-            if (!GATHER || all || s_found == at.cnt) break;
+            if (!GATHER || all || ts.found == at.cnt) break;
             __syncthreads();
-            if (tid < 64) s_cnt[tid] = 0;
+            if (tid < 64) ts.cnt[tid] = 0;
             all = true;
             total = (int)((rg.N + U - 1) / U);
             __syncthreads();
         }
         // cell-major placement, then the rank inside the cell by previous slot
-        int* unord = perm + at.off;   // crowded tiles
         for (int u0 = 0; u0 < total; u0 += NT) {
             if (total > NT) {
                 if (GATHER && u0 == 0 && !all)
@@ -902,56 +1059,11 @@ __global__ __launch_bounds__(NT) void k_sort_p2g2(Geo g, Phys<T> P, Ranges2 rg, 
             }
 #pragma unroll
             for (int q = 0; q < U; ++q)
-                if (cc[q] >= 0) {
-                    const int u = s_off[cc[q]] + atomicAdd(&s_cur[cc[q]], 1);
-                    if (in_lds) {
-                        s_unord[u] = cj[q];
-                        s_ucell[u] = (unsigned char)cc[q];
-                    } else {
-                        unord[u] = cj[q];
-                    }
-                }
+                if (cc[q] >= 0) tile_sort_place(ts, in_lds, cc[q], cj[q], perm + at.off);
         }
-        if (in_lds) {
-            __syncthreads();
-            for (int u = tid; u < at.cnt; u += NT) {
-                const int c = s_ucell[u], j = s_unord[u];
-                const int o = s_off[c], n = s_cnt[c], last = o + n - 1;
-                int rank = 0;
-                for (int q = 0; q < n; q += 4) {
-                    int e[4];
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) e[i] = s_unord[min(o + q + i, last)];
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) rank += (q + i < n && e[i] < j) ? 1 : 0;
-                }
-                s_sorted[rank_major_pos(c, rank, s_rmask, s_roff, s_cnt)] = j;
-            }
-            __syncthreads();
-            for (int k = tid; k < at.cnt; k += NT) perm[at.off + k] = s_sorted[k];
-            if (rg.tile_perm && tid < at.cnt) rg.tile_perm[at.tile * kTileRow + tid] = s_sorted[tid];   // NT = a row
-        } else {
-            __threadfence_block();
-            __syncthreads();
-            for (int k = tid; k < at.cnt; k += NT) {
-                int lo = 0;
-#pragma unroll
-                for (int step = 32; step >= 1; step >>= 1)
-                    if (lo + step < 64 && s_off[lo + step] <= k) lo += step;
-                const int j = unord[k], o = s_off[lo], n = s_cnt[lo];
-                int rank = 0;
-                for (int q = 0; q < n; ++q) rank += unord[o + q] < j;
-                tmp[at.off + rank_major_pos(lo, rank, s_rmask, s_roff, s_cnt)] = j;
-            }
-            __threadfence_block();
-            __syncthreads();
-            const volatile int* rm = tmp + at.off;
-            for (int k = tid; k < at.cnt; k += NT) unord[k] = rm[k];
-            if (rg.tile_perm) rg.tile_perm[at.tile * kTileRow + tid] = rm[tid];   // crowded: more than a row
-            __threadfence_block();
-            __syncthreads();
-        }
-        const int* sorted = in_lds ? s_sorted : (perm + at.off);
+        tile_sort_finish<NT>(ts, in_lds, at.cnt, perm + at.off, tmp + at.off);
+        const int* sorted = in_lds ? ts.sorted : (perm + at.off);
+        if (rg.tile_perm && tid < at.cnt) rg.tile_perm[at.tile * kTileRow + tid] = sorted[tid];   // NT = a row
         int tc[3];
         tile_coords(g, at.tile, tc);
         // opaque to the compiler for this tile, so that what is derived from the
@@ -960,19 +1072,19 @@ __global__ __launch_bounds__(NT) void k_sort_p2g2(Geo g, Phys<T> P, Ranges2 rg, 
         asm volatile("" : "+v"(cl));
         const int lb[3] = {cl % TE, cl / TE, 0};
         const int gb[3] = {tc[0] * TE + lb[0] - g.G, tc[1] * TE + lb[1] - g.G, 0};
-        const int mycnt = s_cnt[cl];
+        const int mycnt = ts.cnt[cl];
         T acc[NK][NV];
 #pragma unroll
         for (int k = 0; k < NK; ++k)
 #pragma unroll
             for (int q = 0; q < NV; ++q) acc[k][q] = T(0);
         P2GIn<T, D, MAT> nx;
-        if (w < mycnt) nx.load(cur, sorted[rank_major_pos(cl, w, s_rmask, s_roff, s_cnt)]);
+        if (w < mycnt) nx.load(cur, sorted[rank_major_pos(cl, w, ts.rmask, ts.roff, ts.cnt)]);
         T(*node)[NB] = s_node[w];
         for (int i = lane; i < NV * NB; i += 64) (&node[0][0])[i] = T(0);
         for (int r = w; r < mycnt; r += NW) {
             const P2GIn<T, D, MAT> in = nx;
-            if (r + NW < mycnt) nx.load(cur, sorted[rank_major_pos(cl, r + NW, s_rmask, s_roff, s_cnt)]);
+            if (r + NW < mycnt) nx.load(cur, sorted[rank_major_pos(cl, r + NW, ts.rmask, ts.roff, ts.cnt)]);
             p2g_particle<T, D, MAT, 0, D, true>(P, in, lb, gb, [&](int k, int, T wx, T mw, T wyz, const T* U, const T* Ex) {
                 acc[k][0] = fma(wx, mw, acc[k][0]);
 #pragma unroll
@@ -1282,7 +1394,7 @@ __global__ __launch_bounds__((kG2PBlock<T, D>)) void k_g2p(Geo g, Phys<T> P, con
                                                 const T* __restrict__ gvo,
                                                 int* __restrict__ key_out, int* __restrict__ count,
                                                 int* __restrict__ status, const T* __restrict__ eps_in,
-                                                T* __restrict__ eps_out, Nodes2<T> nd)
+                                                T* __restrict__ eps_out, Nodes2<T> nd, int* __restrict__ moved)
 {
     constexpr int TE = TileShape<D>::TE, BE = TileShape<D>::BE, NB = TileShape<D>::NB;
     constexpr int NS = D * (D + 1) / 2;
@@ -1526,6 +1638,15 @@ __global__ __launch_bounds__((kG2PBlock<T, D>)) void k_g2p(Geo g, Phys<T> P, con
                 key_out[s] = newkey;
                 if constexpr (D == 2)
                     if (by_tile && k < kTileRow) nd.tile_key[at.tile * kTileRow + k] = newkey;
+                if constexpr (D == 3)
+                    if ((newkey >> 6) != at.tile) {
+                        // into a neighbouring tile: tell it where from
+                        int nt[3];
+                        tile_coords(g, newkey >> 6, nt);
+                        const int dx = tc[0] - nt[0], dy = tc[1] - nt[1], dz = tc[2] - nt[2];
+                        if (abs(dx) <= 1 && abs(dy) <= 1 && abs(dz) <= 1)
+                            atomicOr(&moved[newkey >> 6], 1 << ((dz + 1) * 9 + (dy + 1) * 3 + dx + 1));
+                    }
             }
             int head, len, rank;
             wave_runs(valid ? (newkey >> 6) : -1, valid, head, len, rank);
@@ -1812,6 +1933,17 @@ inline unsigned tile_wgs(const mpm_ctx* c, int block)
     return (unsigned)std::min(full, (long long)tiles);
 }
 
+// Whether P2G reads the particles with the non-temporal hint.  A tile's waves
+// read the same lines, so caching pays where the state that G2P has just written
+// is still in the 256 MB cache: P2G on the cylinder, plain and hinted, 42 MB
+// 15.8 and 17.4 us, 112 MB 29.7 and 36.1, 198 MB 43.5 and 47.2 (the step 181.0
+// both: the other kernels lose what P2G gains); past it the hint keeps the lines
+// that the grid update and G2P need: the step 265.4 and 263.2 us at 334 MB, 328
+// and 314 at 396 MB (binary64), 484 and 463 at 667 MB.  With FLIP four waves
+// read them and plain is better at every size (617 and 616 us at 667 MB, 332
+// and 336 at 334 MB, 142 and 154 at 112 MB).
+inline bool p2g_hint(const mpm_ctx* c) { return (double)c->nsc * (double)c->cap * c->elem > 200e6; }
+
 template <class T, int D>
 struct Solver {
     static int launch_err(mpm_ctx* c, const char* what) { return hip_check(c, hipGetLastError(), what); }
@@ -1846,7 +1978,7 @@ struct Solver {
     static void new_keys(mpm_ctx* c, const PView<T>& v)
     {
         hipStream_t st = c->stream;
-        int* count = c->count[c->turn];
+        int* count = c->count[D == 2 ? c->turn : 0];
         k_fill<int><<<std::min<long long>(nblocks(c->geo.ntiles), 4096), kBlock, 0, st>>>(count, c->geo.ntiles, 0);
         // no tile finds its particles in the rows of the last sort (a captured
         // step that gathers then reads all keys)
@@ -1872,6 +2004,8 @@ struct Solver {
         k_fill<int><<<1, kBlock, 0, st>>>(c->status + 1, 3, 0x7fffffff);
         if (c->geo.ntiles > 0)
             k_fill<int><<<std::min<long long>(nblocks(c->geo.ntiles), 4096), kBlock, 0, st>>>(c->tile_slot, c->geo.ntiles, -1);
+        if (D == 3)
+            k_fill<int><<<std::min<long long>(nblocks(c->geo.ntiles), 4096), kBlock, 0, st>>>(c->moved, c->geo.ntiles, 0);
         return launch_err(c, "clear grid");
     }
 
@@ -1917,23 +2051,38 @@ struct Solver {
             step_views2<MAT, XF>(c, P, cur, nxt, b, nsb);
             return;
         } else {
+        const int o = c->turn, n = 1 - o;
         int* count = c->count[0];
-        sort_tiles(c, nsb, count, b, nullptr, nullptr);
-        k_p2g<T, D, PM, FL><<<tile_wgs(c, kP2GBlock<T, FL>), kP2GBlock<T, FL>, 0, st>>>(g, P, b.meta, b.active, c->tmp, c->tmpk, cur,
-                                                                        b.perm, (T*)c->part_grid);
+        const Ranges r{count, nullptr, c->range[o], c->range[n], c->moved, c->key, nullptr, nullptr, (long long)c->N};
+        scan_tiles(c, nsb, count, b, c->range[n], nullptr);
+        const unsigned swgs = tile_wgs(c, kSortBlock);
+        if (c->ranges_known && c->N < (1ll << 30)) {   // key positions plus a batch stay in int32
+            k_sort_gather<0><<<swgs, kSortBlock, 0, st>>>(g, r, b.meta, b.active, c->tmp, c->tmpk, b.perm, c->cell_cnt);
+        } else {
+            bucket(c, count);
+            k_sort<0><<<swgs, kSortBlock, 0, st>>>(b.meta, b.active, c->tmp, c->tmpk, b.perm, c->cell_cnt);
+        }
+        prof_mark(c, MPM_PROF_BUCKET);
+        if (!FL && p2g_hint(c))
+            k_p2g<T, D, PM, FL, !FL><<<tile_wgs(c, kP2GBlock<FL>), kP2GBlock<FL>, 0, st>>>(g, P, b.meta, b.active, c->cell_cnt,
+                                                                                        cur, b.perm, (T*)c->part_grid);
+        else
+            k_p2g<T, D, PM, FL, false><<<tile_wgs(c, kP2GBlock<FL>), kP2GBlock<FL>, 0, st>>>(g, P, b.meta, b.active, c->cell_cnt,
+                                                                                         cur, b.perm, (T*)c->part_grid);
         prof_mark(c, MPM_PROF_P2G);
         k_grid<T, D, FL><<<tile_wgs(c, kGridBlock), kGridBlock, 0, st>>>(g, P, b.meta, b.active, b.tile_slot, (const T*)c->part_grid,
                                                   b.gv, b.gmass, b.gvt, b.gvo);
         prof_mark(c, MPM_PROF_GRID);
         k_g2p<T, D, MAT, XF><<<tile_wgs(c, kG2PBlock<T, D>), kG2PBlock<T, D>, 0, st>>>(g, P, b.meta, b.active, b.perm, cur, nxt, (const T*)b.gv,
-                                                      (const T*)b.gvo, c->key, count, c->status, b.eps_in, b.eps_out, Nodes2<T>{});
+                                                      (const T*)b.gvo, c->key, count, c->status, b.eps_in, b.eps_out, Nodes2<T>{}, c->moved);
         prof_mark(c, MPM_PROF_G2P);
+        c->turn = n;
+        c->ranges_known = true;
         }
     }
 
-    // The scan over the tiles' counts and the scatter of the particles into
-    // their tiles' ranges.
-    static void sort_tiles(mpm_ctx* c, unsigned nsb, int* count, const StepBufs& b, int2* range, int* count_next)
+    // The scan over the tiles' counts.
+    static void scan_tiles(mpm_ctx* c, unsigned nsb, const int* count, const StepBufs& b, int2* range, int* count_next)
     {
         hipStream_t st = c->stream;
         // one chunk has no earlier chunks to sum: the down-sweep alone
@@ -1941,9 +2090,13 @@ struct Solver {
         k_scan_down<0><<<nsb, kBlock, 0, st>>>(count, c->geo.ntiles, c->part, c->tile_off, b.tile_slot, b.active, b.meta,
                                                range, count_next);
         prof_mark(c, MPM_PROF_SCAN);
-        k_bucket<0><<<(unsigned)((c->N + kBlock * kBucketPer - 1) / (kBlock * kBucketPer)), kBlock, 0, st>>>(
+    }
+
+    // The scatter of the particles into their tiles' ranges (clears the counts).
+    static void bucket(mpm_ctx* c, int* count)
+    {
+        k_bucket<0><<<(unsigned)((c->N + kBlock * kBucketPer - 1) / (kBlock * kBucketPer)), kBlock, 0, c->stream>>>(
             c->N, c->key, count, c->tile_off, c->tmp, c->tmpk);
-        prof_mark(c, MPM_PROF_BUCKET);
     }
 
     // The step in 2-D: two launches where the last sort's layout is known and
@@ -1962,13 +2115,15 @@ struct Solver {
         const bool small = g.ntiles <= kSmallTiles;
         const int o = c->turn, n = small ? 1 - o : o;
         const unsigned wgs = small ? (unsigned)((g.ntiles + 7) / 8 * 8) : (unsigned)kTileWGs;
-        const Ranges2 r{c->count[o], c->count[n], c->range[o], c->range[n], c->key, c->tile_key,
+        const Ranges r{c->count[o], c->count[n], c->range[o], c->range[n], nullptr, c->key, c->tile_key,
                           small ? c->tile_perm : nullptr, (long long)c->N};
         if (small && c->ranges_known && c->N < (1ll << 30)) {   // key positions plus a batch stay in int32
             k_sort_p2g2<T, PM, FL, true, 256><<<wgs, 256, 0, st>>>(g, P, r, b.meta, b.active, b.tile_slot, c->tmp, c->tmpk,
                                                                       cur, b.perm, (T*)c->part_grid);
         } else {
-            sort_tiles(c, nsb, c->count[o], b, small ? c->range[n] : nullptr, small ? c->count[n] : nullptr);
+            scan_tiles(c, nsb, c->count[o], b, small ? c->range[n] : nullptr, small ? c->count[n] : nullptr);
+            bucket(c, c->count[o]);
+            prof_mark(c, MPM_PROF_BUCKET);
             if (small)
                 k_sort_p2g2<T, PM, FL, false, 256><<<wgs, 256, 0, st>>>(g, P, r, b.meta, b.active, b.tile_slot, c->tmp,
                                                                         c->tmpk, cur, b.perm, (T*)c->part_grid);
@@ -1979,7 +2134,7 @@ struct Solver {
         prof_mark(c, MPM_PROF_P2G);
         const Nodes2<T> nd{(const T*)c->part_grid, b.tile_slot, small ? c->range[n] : nullptr, c->tile_perm, c->tile_key, b.gv, b.gmass, b.gvt, b.gvo};
         k_g2p<T, D, MAT, XF><<<wgs, kG2PBlock<T, D>, 0, st>>>(g, P, b.meta, b.active, b.perm, cur, nxt, nullptr, nullptr, c->key,
-                                                              c->count[n], c->status, b.eps_in, b.eps_out, nd);
+                                                              c->count[n], c->status, b.eps_in, b.eps_out, nd, nullptr);
         prof_mark(c, MPM_PROF_G2P);
         c->turn = n;
         c->ranges_known = small;

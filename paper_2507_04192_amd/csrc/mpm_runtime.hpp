@@ -64,14 +64,16 @@ struct mpm_ctx {
     int32_t* tmp = nullptr;
     int32_t* tmpk = nullptr;       // key of each bucketed particle
     int32_t* count[2] = {nullptr, nullptr};  // particles per tile; 2-D steps alternate, 3-D uses the first
-    int2* range[2] = {nullptr, nullptr};     // 2-D: first slot and number of each tile's particles, by turn
+    int2* range[2] = {nullptr, nullptr};     // first slot and number of each tile's particles, by turn
+    int32_t* moved = nullptr;      // 3-D: per tile, the neighbours that particles came from in the last step
     int32_t* tile_perm = nullptr;  // 2-D, few tiles: row per tile of the first entries of perm
     int32_t* tile_key = nullptr;   // and of the keys after the step, else null
-    int turn = 0;                  // 2-D: buffer that describes the current state
-    bool ranges_known = false;     // 2-D: range[turn] is the layout of the current state
+    int turn = 0;                  // buffer that describes the current state
+    bool ranges_known = false;     // range[turn] is the layout of the current state
     int32_t* tile_off = nullptr;
     int32_t* tile_slot = nullptr;
     mpm::ActiveTile* active = nullptr;
+    int32_t* cell_cnt = nullptr;   // 3-D: particles per cell of each active tile
     int32_t* part = nullptr;
     int32_t* meta = nullptr;       // [0] active tiles, [1] particles sorted
     int32_t* status = nullptr;     // [0] flags, [1] smallest bad pid
