@@ -1264,6 +1264,87 @@ __global__ __launch_bounds__(kGridBlock) void k_grid(Geo g, Phys<T> P, const int
 }
 
 // ---------------------------------------------------------------------------
+// Gathers over the stencil
+// ---------------------------------------------------------------------------
+
+// The per-axis factors of a particle's weights: w, w dd (dd = x_i - x_p) and
+// d phi / dx.
+template <class T, int D>
+struct AxisFactors {
+    T w[D][3], wd[D][3], dw[D][3];
+    __device__ __forceinline__ void set(int a, T f, T inv, T h)
+    {
+        weights_from_f(f, inv, w[a], dw[a]);
+#pragma unroll
+        for (int k = 0; k < 3; ++k) wd[a][k] = w[a][k] * ((T(k) - f) * h);
+    }
+};
+
+// Sums of a node field over the stencil with the weights of all axes but one:
+// R[b][k] = sum over the nodes with offset k along b of field * (product of the
+// other axes' w).  Every gather of the field is a sum over k of these with one
+// axis's own factors: sum phi field = sum_k w_0 R_0, sum phi field dd_b =
+// sum_k wd_b R_b, sum field d_b phi = sum_k dw_b R_b; 81 multiply-adds for the
+// R and 21 for the seven sums of a component, where summing each of the seven
+// line by line was 144 and the lines' factors.  The barrier after each plane
+// keeps the compiler from hoisting all LDS reads of the stencil (registers,
+// occupancy).
+template <class T, int D, int NB>
+__device__ __forceinline__ void axis_sums(const T (&f)[NB], int n0, const AxisFactors<T, D>& A, T R[D][3])
+{
+    constexpr int BE = TileShape<D>::BE;
+    if constexpr (D == 2) {
+#pragma unroll
+        for (int k = 0; k < 3; ++k) R[0][k] = R[1][k] = T(0);
+#pragma unroll
+        for (int ky = 0; ky < 3; ++ky)
+#pragma unroll
+            for (int kx = 0; kx < 3; ++kx) {
+                const T p = f[n0 + ky * BE + kx];
+                R[0][kx] = fma(A.w[1][ky], p, R[0][kx]);
+                R[1][ky] = fma(A.w[0][kx], p, R[1][ky]);
+            }
+    } else {
+        T xy[3][3];   // summed along z
+#pragma unroll
+        for (int ky = 0; ky < 3; ++ky)
+#pragma unroll
+            for (int kx = 0; kx < 3; ++kx) xy[ky][kx] = T(0);
+#pragma unroll
+        for (int kz = 0; kz < 3; ++kz) {
+            R[2][kz] = T(0);
+#pragma unroll
+            for (int ky = 0; ky < 3; ++ky) {
+                T x = T(0);   // summed along x
+#pragma unroll
+                for (int kx = 0; kx < 3; ++kx) {
+                    const T p = f[n0 + (kz * BE + ky) * BE + kx];
+                    x = fma(A.w[0][kx], p, x);
+                    xy[ky][kx] = fma(A.w[2][kz], p, xy[ky][kx]);
+                }
+                R[2][kz] = fma(A.w[1][ky], x, R[2][kz]);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+#pragma unroll
+        for (int k = 0; k < 3; ++k) R[0][k] = R[1][k] = T(0);
+#pragma unroll
+        for (int ky = 0; ky < 3; ++ky)
+#pragma unroll
+            for (int kx = 0; kx < 3; ++kx) {
+                R[0][kx] = fma(A.w[1][ky], xy[ky][kx], R[0][kx]);
+                R[1][ky] = fma(A.w[0][kx], xy[ky][kx], R[1][ky]);
+            }
+    }
+}
+
+template <class T>
+__device__ __forceinline__ T dot3(const T a[3], const T b[3])
+{
+    return fma(a[2], b[2], fma(a[1], b[1], a[0] * b[0]));
+}
+
+// ---------------------------------------------------------------------------
 // G2P + kinematics + constitutive
 // ---------------------------------------------------------------------------
 
@@ -1484,66 +1565,34 @@ __global__ __launch_bounds__((kG2PBlock<T, D>)) void k_g2p(Geo g, Phys<T> P, con
                 long long s = at.off + k;
                 const bool mine_first = D == 2 && k0 == 0;
                 int j = mine_first ? j_first : ld_once(&perm[s]);
-                T xp[D], w[D][3], dw[D][3], dd[D][3];
-                int lb[3] = {0, 0, 0};
+                T xp[D];
+                AxisFactors<T, D> A;
+                int n0 = 0, ns = 1;
 #pragma unroll
                 for (int a = 0; a < D; ++a) {
                     xp[a] = mine_first ? x_first[a] : ld_once(&cur.x[a * cap + j]);
-                    int b;
-                    T f;
-                    stencil_axis(xp[a], P.inv, b, f, w[a], dw[a]);
-                    int l = b + g.G - tc[a] * TE;
-                    lb[a] = l < 0 ? 0 : (l > TE - 1 ? TE - 1 : l);   // memory guard only
-#pragma unroll
-                    for (int q = 0; q < 3; ++q) dd[a][q] = (T(q) - f) * P.h;
+                    const T t = mul_exact(xp[a], P.inv), fb = floor(t - T(0.5));
+                    A.set(a, t - fb, P.inv, P.h);
+                    int l = (int)fb + g.G - tc[a] * TE;
+                    l = l < 0 ? 0 : (l > TE - 1 ? TE - 1 : l);   // memory guard only
+                    n0 += l * ns;
+                    ns *= BE;
                 }
-                // Gather over the 3^D stencil nodes of the LDS block:
-                //   vn = sum phi v,  Bm = sum phi v (x_i - x_p)^T,  Lm = sum v (grad phi)^T.
-                // Each weight is a product of per-axis factors: every node
-                // line along x is reduced with the x factors (w, w dd, dw),
-                // then combined with the line's y/z factors.  The scheduling
-                // barrier after each line keeps the compiler from hoisting
-                // all LDS reads of the stencil (registers, occupancy).
+                // vn = sum phi v,  Bm = sum phi v (x_i - x_p)^T,  Lm = sum v (grad phi)^T
                 T vn[D], Bm[D][D], Lm[D][D], vo[FL ? D : 1];
-                {
-                    constexpr int NL = (D == 3) ? 9 : 3;
-                    T wdx[3];
 #pragma unroll
-                    for (int q = 0; q < 3; ++q) wdx[q] = w[0][q] * dd[0][q];
+                for (int a = 0; a < D; ++a) {
+                    T R[D][3];
+                    axis_sums<T, D, NB>(s_v[a], n0, A, R);
+                    vn[a] = dot3(A.w[0], R[0]);
 #pragma unroll
-                    for (int a = 0; a < D; ++a) {
-                        vn[a] = T(0);
-                        if constexpr (FL) vo[a] = T(0);
-#pragma unroll
-                        for (int b = 0; b < D; ++b) { Bm[a][b] = T(0); Lm[a][b] = T(0); }
+                    for (int b = 0; b < D; ++b) {
+                        Bm[a][b] = dot3(A.wd[b], R[b]);
+                        Lm[a][b] = dot3(A.dw[b], R[b]);
                     }
-#pragma unroll
-                    for (int l = 0; l < NL; ++l) {
-                        const int ky = l % 3, kz = l / 3;
-                        const T lw = (D == 3) ? w[1][ky] * w[2][kz] : w[1][ky];
-                        const T ld1 = lw * dd[1][ky];
-                        const T ldw1 = (D == 3) ? dw[1][ky] * w[2][kz] : dw[1][ky];
-                        const int n0 = (D == 3) ? ((lb[2] + kz) * BE + lb[1] + ky) * BE + lb[0] : (lb[1] + ky) * BE + lb[0];
-#pragma unroll
-                        for (int a = 0; a < D; ++a) {
-                            T v0 = s_v[a][n0], v1 = s_v[a][n0 + 1], v2 = s_v[a][n0 + 2];
-                            T A0 = w[0][0] * v0 + w[0][1] * v1 + w[0][2] * v2;
-                            T A1 = wdx[0] * v0 + wdx[1] * v1 + wdx[2] * v2;
-                            T A2 = dw[0][0] * v0 + dw[0][1] * v1 + dw[0][2] * v2;
-                            vn[a] += lw * A0;
-                            Bm[a][0] += lw * A1;
-                            Bm[a][1] += ld1 * A0;
-                            Lm[a][0] += lw * A2;
-                            Lm[a][1] += ldw1 * A0;
-                            if constexpr (D == 3) {
-                                Bm[a][2] += (lw * dd[2][kz]) * A0;
-                                Lm[a][2] += (w[1][ky] * dw[2][kz]) * A0;
-                            }
-                            if constexpr (FL)
-                                vo[a] += lw * (w[0][0] * s_vo[a][n0] + w[0][1] * s_vo[a][n0 + 1] +
-                                               w[0][2] * s_vo[a][n0 + 2]);
-                        }
-                        __builtin_amdgcn_sched_barrier(0);
+                    if constexpr (FL) {
+                        axis_sums<T, D, NB>(s_vo[a], n0, A, R);
+                        vo[a] = dot3(A.w[0], R[0]);
                     }
                 }
                 bool bad = false, fast = false, noconv = false;
