@@ -17,6 +17,8 @@
 //             writing each particle's adjoint at its slot before the step.
 #pragma once
 
+#include <type_traits>
+
 #include "mpm_adjoint_device.hpp"
 #include "mpm_kernels.hpp"
 
@@ -39,12 +41,125 @@ template <int D> struct MidLayout {
     static_assert(D + 1 + D * (D + 1) / 2 <= D + D * D, "stress adjoint fits the intermediate");
 };
 
+// f = x/h - base of a position, and along one axis the weight factors and the
+// offset of the stencil's first node in the tile's block (clamped: memory guard).
+template <class T>
+__device__ __forceinline__ T block_axis_f(const Phys<T>& P, T x)
+{
+    const T t = mul_exact(x, P.inv);
+    return t - floor(t - T(0.5));
+}
+
+template <class T, int D>
+__device__ __forceinline__ int block_axis(const Geo& g, const Phys<T>& P, int a, T x, int tc, AxisFactors<T, D>& A)
+{
+    constexpr int TE = TileShape<D>::TE;
+    const T t = mul_exact(x, P.inv), fb = floor(t - T(0.5));
+    A.set(a, t - fb, P.inv, P.h);
+    const int l = (int)fb + g.G - tc * TE;
+    return l < 0 ? 0 : (l > TE - 1 ? TE - 1 : l);
+}
+
+// A transfer of component a between particle and nodes is
+//   T(k) = w_x w_y w_z c + E^x(k_x) w_y w_z + w_x E^y(k_y) w_z + w_x w_y E^z(k_z),
+//   E^b(k) = wd_b(k) p_b + dw_b(k) q_b
+// (P2G: c = m v_a, p = m C_a, q = -dt V sigma_a; the adjoint of G2P: c, p and q
+// the adjoints of the velocity, of C and of the velocity gradient).  axis_vjp
+// contracts it with a node field f: R[b][k] = sum of f over the nodes with
+// offset k along b, weighted with the other axes' w (the adjoint of E^b(k)), and
+// wb[b][k] += the adjoint of w_b(k) through c and the other axes' E.  171
+// multiply-adds per component, one reading of the field.
+template <class B, class T, int D>
+__device__ __forceinline__ void axis_vjp(const T (&f)[B::LN], int n0, const AxisFactors<T, D>& A, T c, const T E[D][3], T R[D][3],
+                                         T wb[D][3])
+{
+    constexpr int LY = B::LY, LZ = B::LZ;
+#pragma unroll
+    for (int k = 0; k < 3; ++k) R[0][k] = R[1][k] = T(0);
+    if constexpr (D == 2) {
+#pragma unroll
+        for (int ky = 0; ky < 3; ++ky)
+#pragma unroll
+            for (int kx = 0; kx < 3; ++kx) {
+                const T p = f[n0 + ky * LY + kx];
+                R[0][kx] = fma(A.w[1][ky], p, R[0][kx]);
+                R[1][ky] = fma(A.w[0][kx], p, R[1][ky]);
+                wb[0][kx] = fma(E[1][ky], p, wb[0][kx]);
+                wb[1][ky] = fma(E[0][kx], p, wb[1][ky]);
+            }
+    } else {
+        T xy[3][3];   // summed along z
+#pragma unroll
+        for (int ky = 0; ky < 3; ++ky)
+#pragma unroll
+            for (int kx = 0; kx < 3; ++kx) xy[ky][kx] = T(0);
+#pragma unroll
+        for (int kz = 0; kz < 3; ++kz) {
+            T xz[3] = {T(0), T(0), T(0)};   // summed along y
+            R[2][kz] = T(0);
+#pragma unroll
+            for (int ky = 0; ky < 3; ++ky) {
+                T yz = T(0);                // summed along x
+#pragma unroll
+                for (int kx = 0; kx < 3; ++kx) {
+                    const T p = f[n0 + kz * LZ + ky * LY + kx];
+                    yz = fma(A.w[0][kx], p, yz);
+                    xz[kx] = fma(A.w[1][ky], p, xz[kx]);
+                    xy[ky][kx] = fma(A.w[2][kz], p, xy[ky][kx]);
+                }
+                R[2][kz] = fma(A.w[1][ky], yz, R[2][kz]);
+                wb[1][ky] = fma(E[2][kz], yz, wb[1][ky]);
+                wb[2][kz] = fma(E[1][ky], yz, wb[2][kz]);
+            }
+#pragma unroll
+            for (int kx = 0; kx < 3; ++kx) {
+                wb[0][kx] = fma(E[2][kz], xz[kx], wb[0][kx]);
+                wb[2][kz] = fma(E[0][kx], xz[kx], wb[2][kz]);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+#pragma unroll
+        for (int ky = 0; ky < 3; ++ky)
+#pragma unroll
+            for (int kx = 0; kx < 3; ++kx) {
+                R[0][kx] = fma(A.w[1][ky], xy[ky][kx], R[0][kx]);
+                R[1][ky] = fma(A.w[0][kx], xy[ky][kx], R[1][ky]);
+                wb[0][kx] = fma(E[1][ky], xy[ky][kx], wb[0][kx]);
+                wb[1][ky] = fma(E[0][kx], xy[ky][kx], wb[1][ky]);
+            }
+    }
+#pragma unroll
+    for (int b = 0; b < D; ++b)
+#pragma unroll
+        for (int k = 0; k < 3; ++k) wb[b][k] = fma(c, R[b][k], wb[b][k]);
+}
+
+// E of one component (see axis_vjp).
+template <class T, int D>
+__device__ __forceinline__ void axis_terms(const AxisFactors<T, D>& A, const T p[D], const T q[D], T E[D][3])
+{
+#pragma unroll
+    for (int b = 0; b < D; ++b)
+#pragma unroll
+        for (int k = 0; k < 3; ++k) E[b][k] = fma(A.dw[b][k], q[b], A.wd[b][k] * p[b]);
+}
+
+// Position adjoint of one component through E: d wd_b / dx = dw_b dd - w_b and
+// d dw_b / dx = ddw, the second derivative of the quadratic B-spline,
+// (1, -2, 1) / h^2; with p_b = q_b summed against R once: sum_k R_b(k) (p_b
+// (dw_b(k) dd(k) - w_b(k)) + q_b ddw(k)).  dwd: dw dd - w.
+template <class T>
+__device__ __forceinline__ T axis_dx(const T dwd[3], T inv2, T p, T q, const T R[3])
+{
+    return fma(p, dot3(dwd, R), q * (inv2 * (R[0] - T(2) * R[1] + R[2])));
+}
+
 // Reverse of the constitutive update, the kinematics x' = x + dt v and G2P,
 // per particle of a tile.  First part: recomputes the G2P velocity and
 // velocity gradient from the tile's node block and applies the constitutive
-// VJP.  Second part, line by line: node adjoints of the velocity
+// VJP.  Second part, component by component: node adjoints of the velocity
 // (accumulated in binary64 in LDS, then written as the tile's partial block)
-// and the position adjoint through the weights and x_i - x_p.  The velocity,
+// and the position adjoint through the weights and x_i - x_p (see axis_vjp).  The velocity,
 // velocity-gradient and partial position adjoints pass between the parts in
 // registers; the F (or J) adjoint and the position adjoint go to mid.
 // FLIP (FL): v' = sum phi v_i + alpha (v_p - sum phi v_i^n); the adjoint of
@@ -52,8 +167,14 @@ template <int D> struct MidLayout {
 // written after the first in the tile's partial block), its weights pass
 // an adjoint to the position, and alpha times the adjoint of v' goes to mid
 // as the direct adjoint of v_p.
+// What bounds it: binary32 the LDS atomics (81 per particle, half of its time)
+// beside the arithmetic, binary64 the registers.  3-D dam-break, 1,843,200
+// particles, by lines along x -> by axis sums: binary32 153 -> 133 us, binary64
+// 333 -> 221 at two waves per SIMD, which the materials without F fit (sand
+// would spill: 114 -> 190 us on the half cylinder, where by axis sums alone it
+// went 125 -> 114).
 template <class T, int D, int MAT, bool FL>
-__global__ __launch_bounds__((kAdjBlock<D>)) void k_g2p_adj(Geo g, Phys<T> P, const int* __restrict__ meta,
+__global__ __launch_bounds__((kAdjBlock<D>)) __attribute__((amdgpu_waves_per_eu(mat_has_F(MAT) ? 1 : 2))) void k_g2p_adj(Geo g, Phys<T> P, const int* __restrict__ meta,
                                                     const ActiveTile* __restrict__ active,
                                                     const int* __restrict__ perm, PView<T> st, PView<T> aout,
                                                     const T* __restrict__ gv, const T* __restrict__ gvo,
@@ -63,10 +184,15 @@ __global__ __launch_bounds__((kAdjBlock<D>)) void k_g2p_adj(Geo g, Phys<T> P, co
     constexpr int NS = D * (D + 1) / 2;
     constexpr int NVA = FL ? 2 * D + 1 : D + 1;   // partial block values per node
     using ML = MidLayout<D>;
-    __shared__ T s_v[D][NB];
-    __shared__ double s_b[D][NB];
-    __shared__ T s_vo[FL ? D : 1][FL ? NB : 1];
-    __shared__ double s_bo[FL ? D : 1][FL ? NB : 1];
+    // binary32: the node adjoints' LDS atomics are a third faster on the padded
+    // block (3-D dam-break 147 -> 134 us); binary64 221 -> 227
+    using B = std::conditional_t<D == 3 && sizeof(T) == 4, PaddedBlock, DenseBlock<D>>;
+    constexpr int LY = B::LY, LZ = B::LZ, LN = B::LN;
+    constexpr int stride[3] = {1, LY, LZ};
+    __shared__ T s_v[D][LN];
+    __shared__ double s_b[D][LN];
+    __shared__ T s_vo[FL ? D : 1][FL ? LN : 1];
+    __shared__ double s_bo[FL ? D : 1][FL ? LN : 1];
     const int n_active = meta[0];
     const int tid = threadIdx.x;
     const long long cap = st.cap;
@@ -79,14 +205,15 @@ __global__ __launch_bounds__((kAdjBlock<D>)) void k_g2p_adj(Geo g, Phys<T> P, co
         tile_coords(g, at.tile, tc);
         for (int i = tid; i < NB; i += kAdjBlock<D>) {
             int l0 = i % BE, l1 = (i / BE) % BE, l2 = (D == 3) ? i / (BE * BE) : 0;
+            const int q = B::at(i);
             long long node = node_index(g, tc[0] * TE + l0, tc[1] * TE + l1, (D == 3) ? tc[2] * TE + l2 : 0);
 #pragma unroll
             for (int a = 0; a < D; ++a) {
-                s_v[a][i] = gv[a * g.NN + node];
-                s_b[a][i] = 0.0;
+                s_v[a][q] = gv[a * g.NN + node];
+                s_b[a][q] = 0.0;
                 if constexpr (FL) {
-                    s_vo[a][i] = gvo[a * g.NN + node];
-                    s_bo[a][i] = 0.0;
+                    s_vo[a][q] = gvo[a * g.NN + node];
+                    s_bo[a][q] = 0.0;
                 }
             }
         }
@@ -96,47 +223,23 @@ __global__ __launch_bounds__((kAdjBlock<D>)) void k_g2p_adj(Geo g, Phys<T> P, co
             int j = perm[s];
             T xbar_c[D], vt_c[D], Lb_c[D][D], vob_c[FL ? D : 1];
             {
-                T xp[D], w[D][3], dw[D][3];
-                int lb[3] = {0, 0, 0};
+                T xp[D];
+                AxisFactors<T, D> A;
+                int n0 = 0;
     #pragma unroll
                 for (int a = 0; a < D; ++a) {
                     xp[a] = st.x[a * cap + j];
-                    int b;
-                    T f;
-                    stencil_axis(xp[a], P.inv, b, f, w[a], dw[a]);
-                    int l = b + g.G - tc[a] * TE;
-                    lb[a] = l < 0 ? 0 : (l > TE - 1 ? TE - 1 : l);
+                    n0 += block_axis(g, P, a, xp[a], tc[a], A) * stride[a];
                 }
-                // forward G2P of this particle: velocity and velocity gradient,
-                // line by line along x as in the forward kernel (per-axis weight
-                // factors; a scheduling barrier per line bounds register use)
+                // forward G2P of this particle: velocity and velocity gradient
                 T vn[D], Lm[D][D];
-                {
-                    constexpr int NL = (D == 3) ? 9 : 3;
     #pragma unroll
-                    for (int a = 0; a < D; ++a) {
-                        vn[a] = T(0);
+                for (int a = 0; a < D; ++a) {
+                    T R[D][3];
+                    axis_sums<B>(s_v[a], n0, A, R);
+                    vn[a] = dot3(A.w[0], R[0]);
     #pragma unroll
-                        for (int b = 0; b < D; ++b) Lm[a][b] = T(0);
-                    }
-    #pragma unroll
-                    for (int l = 0; l < NL; ++l) {
-                        const int ky = l % 3, kz = l / 3;
-                        const T lw = (D == 3) ? w[1][ky] * w[2][kz] : w[1][ky];
-                        const T ldw1 = (D == 3) ? dw[1][ky] * w[2][kz] : dw[1][ky];
-                        const int n0 = (D == 3) ? ((lb[2] + kz) * BE + lb[1] + ky) * BE + lb[0] : (lb[1] + ky) * BE + lb[0];
-    #pragma unroll
-                        for (int a = 0; a < D; ++a) {
-                            T v0 = s_v[a][n0], v1 = s_v[a][n0 + 1], v2 = s_v[a][n0 + 2];
-                            T A0 = w[0][0] * v0 + w[0][1] * v1 + w[0][2] * v2;
-                            T A2 = dw[0][0] * v0 + dw[0][1] * v1 + dw[0][2] * v2;
-                            vn[a] += lw * A0;
-                            Lm[a][0] += lw * A2;
-                            Lm[a][1] += ldw1 * A0;
-                            if constexpr (D == 3) Lm[a][2] += (w[1][ky] * dw[2][kz]) * A0;
-                        }
-                        __builtin_amdgcn_sched_barrier(0);
-                    }
+                    for (int b = 0; b < D; ++b) Lm[a][b] = dot3(A.dw[b], R[b]);
                 }
                 // reverse of the constitutive update
                 T Lb[D][D];
@@ -196,17 +299,15 @@ __global__ __launch_bounds__((kAdjBlock<D>)) void k_g2p_adj(Geo g, Phys<T> P, co
                 }
             }
             {
-                T w[D][3], dw[D][3], dd[D][3];
-                int lb[3] = {0, 0, 0};
+                AxisFactors<T, D> A;
+                T dwd[D][3];
+                int n0 = 0;
     #pragma unroll
                 for (int a = 0; a < D; ++a) {
-                    int b;
-                    T f;
-                    stencil_axis(st.x[a * cap + j], P.inv, b, f, w[a], dw[a]);
-                    int l = b + g.G - tc[a] * TE;
-                    lb[a] = l < 0 ? 0 : (l > TE - 1 ? TE - 1 : l);
+                    const T f = block_axis_f(P, st.x[a * cap + j]);
+                    n0 += block_axis(g, P, a, st.x[a * cap + j], tc[a], A) * stride[a];
     #pragma unroll
-                    for (int q = 0; q < 3; ++q) dd[a][q] = (T(q) - f) * P.h;
+                    for (int q = 0; q < 3; ++q) dwd[a][q] = A.dw[a][q] * ((T(q) - f) * P.h) - A.w[a][q];
                 }
                 T xbar[D], vt[D], Cb[D][D], Lb[D][D];
     #pragma unroll
@@ -230,102 +331,52 @@ __global__ __launch_bounds__((kAdjBlock<D>)) void k_g2p_adj(Geo g, Phys<T> P, co
                             Cb[a][b] = T(0);
                         }
                 }
-                // Line by line along x (per-axis weight factors).  Node adjoint of
-                // the velocity, scattered:
-                //   phi (vt + Dinv Cb dd) + Lb grad phi = w_x U + w_x dd_x V + dw_x W.
-                // Position adjoint, gathered with u = Cb^T v_i, g = Lb^T v_i,
-                // wbar = v_i.vt + Dinv dd.u:
-                //   xbar += sum wbar grad phi + sum Hess(phi) g - Dinv Cb^T vn,
-                // vn = sum phi v_i (the forward G2P velocity).
-                constexpr int NL = (D == 3) ? 9 : 3;
-                const T ddw[3] = {inv2, T(-2) * inv2, inv2};
-                T X1[D], X2[D], vn[D];
+                // Per component: the node adjoint of the velocity, scattered,
+                //   phi (vt + Dinv Cb dd) + Lb grad phi,
+                // a transfer of the same form as P2G (see axis_vjp), and its
+                // position adjoint against the node velocities.
+                T wb[D][3];
     #pragma unroll
-                for (int a = 0; a < D; ++a) { X1[a] = T(0); X2[a] = T(0); vn[a] = T(0); }
+                for (int b = 0; b < D; ++b)
     #pragma unroll
-                for (int l = 0; l < NL; ++l) {
-                    const int ky = l % 3, kz = l / 3;
-                    const int n0 = (D == 3) ? ((lb[2] + kz) * BE + lb[1] + ky) * BE + lb[0] : (lb[1] + ky) * BE + lb[0];
-                    const T wy = w[1][ky], dwy = dw[1][ky];
-                    const T wz = (D == 3) ? w[D - 1][kz] : T(1), dwz = (D == 3) ? dw[D - 1][kz] : T(0);
-                    const T ddz = (D == 3) ? dd[D - 1][kz] : T(0);
-                    const T wyz = wy * wz;
-                    T U[D], V[D], Wl[D];
+                    for (int q = 0; q < 3; ++q) wb[b][q] = T(0);
     #pragma unroll
-                    for (int a = 0; a < D; ++a) {
-                        T u = vt[a] + P.Dinv * Cb[a][1] * dd[1][ky];
-                        if constexpr (D == 3) u += P.Dinv * Cb[a][D - 1] * ddz;
-                        u = wyz * u + Lb[a][1] * dwy * wz;
-                        if constexpr (D == 3) u += Lb[a][D - 1] * wy * dwz;
-                        U[a] = u;
-                        V[a] = wyz * P.Dinv * Cb[a][0];
-                        Wl[a] = wyz * Lb[a][0];
-                    }
-                    T A = T(0), B = T(0), VN[D], Cx[6] = {T(0), T(0), T(0), T(0), T(0), T(0)};
+                for (int a = 0; a < D; ++a) {
+                    T E[D][3], R[D][3], pc[D];
     #pragma unroll
-                    for (int a = 0; a < D; ++a) VN[a] = T(0);
+                    for (int b = 0; b < D; ++b) pc[b] = P.Dinv * Cb[a][b];
+                    axis_terms<T, D>(A, pc, Lb[a], E);
+                    axis_vjp<B>(s_v[a], n0, A, vt[a], E, R, wb);
     #pragma unroll
-                    for (int kx = 0; kx < 3; ++kx) {
-                        const int n = n0 + kx;
-                        const T ddn[3] = {dd[0][kx], dd[1][ky], ddz};
-                        T vi[D];
+                    for (int b = 0; b < D; ++b) xbar[b] += axis_dx(dwd[b], inv2, pc[b], Lb[a][b], R[b]);
+                    constexpr int KZ = (D == 3) ? 3 : 1;
     #pragma unroll
-                        for (int a = 0; a < D; ++a) {
-                            vi[a] = s_v[a][n];
-                            T nbv = w[0][kx] * U[a] + w[0][kx] * dd[0][kx] * V[a] + dw[0][kx] * Wl[a];
-                            atomicAdd(&s_b[a][n], (double)nbv);
-                            if constexpr (FL) atomicAdd(&s_bo[a][n], (double)(w[0][kx] * wyz * vob_c[a]));
-                        }
-                        T wbar = T(0), gq[D];
+                    for (int kz = 0; kz < KZ; ++kz)
     #pragma unroll
-                        for (int b = 0; b < D; ++b) {
-                            T ub = T(0), gb = T(0);
-    #pragma unroll
-                            for (int a = 0; a < D; ++a) {
-                                ub += Cb[a][b] * vi[a];
-                                gb += Lb[a][b] * vi[a];
+                        for (int ky = 0; ky < 3; ++ky) {
+                            T wyz = A.w[1][ky], U = fma(A.w[1][ky], vt[a], E[1][ky]);
+                            if constexpr (D == 3) {
+                                wyz *= A.w[D - 1][kz];
+                                U = fma(A.w[D - 1][kz], U, A.w[1][ky] * E[D - 1][kz]);
                             }
-                            gq[b] = gb;
-                            wbar += vi[b] * vt[b] + P.Dinv * ddn[b] * ub;
-                            if constexpr (FL) wbar += s_vo[b][n] * vob_c[b];
-                        }
-                        A += wbar * dw[0][kx];
-                        B += wbar * w[0][kx];
     #pragma unroll
-                        for (int a = 0; a < D; ++a) VN[a] += vi[a] * w[0][kx];
-                        Cx[0] += gq[0] * ddw[kx];
-                        Cx[1] += gq[1] * dw[0][kx];
-                        Cx[3] += gq[0] * dw[0][kx];
-                        Cx[4] += gq[1] * w[0][kx];
-                        if constexpr (D == 3) {
-                            Cx[2] += gq[D - 1] * dw[0][kx];
-                            Cx[5] += gq[D - 1] * w[0][kx];
+                            for (int kx = 0; kx < 3; ++kx) {
+                                const int n = n0 + kz * LZ + ky * LY + kx;
+                                atomicAdd(&s_b[a][n], (double)fma(wyz, E[0][kx], A.w[0][kx] * U));
+                                if constexpr (FL) atomicAdd(&s_bo[a][n], (double)(A.w[0][kx] * wyz * vob_c[a]));
+                            }
                         }
-                    }
+                    if constexpr (FL) {
     #pragma unroll
-                    for (int a = 0; a < D; ++a) vn[a] += wyz * VN[a];
-                    if constexpr (D == 3) {
-                        X1[0] += wyz * A;
-                        X1[1] += dwy * wz * B;
-                        X1[2] += wy * dwz * B;
-                        X2[0] += wyz * Cx[0] + dwy * wz * Cx[1] + wy * dwz * Cx[2];
-                        X2[1] += dwy * wz * Cx[3] + ddw[ky] * wz * Cx[4] + dwy * dwz * Cx[5];
-                        X2[2] += wy * dwz * Cx[3] + dwy * dwz * Cx[4] + wy * ddw[kz] * Cx[5];
-                    } else {
-                        X1[0] += wy * A;
-                        X1[1] += dwy * B;
-                        X2[0] += wy * Cx[0] + dwy * Cx[1];
-                        X2[1] += dwy * Cx[3] + ddw[ky] * Cx[4];
+                        for (int b = 0; b < D; ++b)
+    #pragma unroll
+                            for (int q = 0; q < 3; ++q) E[b][q] = T(0);
+                        axis_vjp<B>(s_vo[a], n0, A, vob_c[a], E, R, wb);
                     }
                     __builtin_amdgcn_sched_barrier(0);
                 }
     #pragma unroll
-                for (int c = 0; c < D; ++c) {
-                    T t = X1[c] + X2[c];
-    #pragma unroll
-                    for (int a = 0; a < D; ++a) t -= P.Dinv * Cb[a][c] * vn[a];
-                    xbar[c] += t;
-                }
+                for (int b = 0; b < D; ++b) xbar[b] += dot3(wb[b], A.dw[b]);
     #pragma unroll
                 for (int a = 0; a < D; ++a) mid[(ML::X + a) * cap + s] = xbar[a];
             }
@@ -333,9 +384,9 @@ __global__ __launch_bounds__((kAdjBlock<D>)) void k_g2p_adj(Geo g, Phys<T> P, co
         __syncthreads();
         // 2-D: by tile, so that the next kernel need not look the block up
         T* dst = part + (long long)(D == 2 ? at.tile : e) * NVA * NB;
-        for (int i = tid; i < D * NB; i += kAdjBlock<D>) dst[i] = (T)(&s_b[0][0])[i];
+        for (int i = tid; i < D * NB; i += kAdjBlock<D>) dst[i] = (T)s_b[i / NB][B::at(i % NB)];
         if constexpr (FL)
-            for (int i = tid; i < D * NB; i += kAdjBlock<D>) dst[D * NB + i] = (T)(&s_bo[0][0])[i];
+            for (int i = tid; i < D * NB; i += kAdjBlock<D>) dst[D * NB + i] = (T)s_bo[i / NB][B::at(i % NB)];
         __syncthreads();
     }
 }
@@ -534,8 +585,10 @@ __device__ __forceinline__ void node_adj_block2(const Geo& g, const Phys<T>& P, 
     }
 }
 
-// At least two waves per SIMD: binary64 needs a few more than 256 registers
-// per lane and would otherwise run one wave (measured faster with the spills).
+// At least two waves per SIMD in binary64.  3-D dam-break, 1,843,200 particles,
+// by lines along x -> by axis sums: binary32 117 -> 97 us, binary64 191 -> 156;
+// it is left with its traffic (the adjoint goes back to the order before the
+// sort, partial lines at its ends).
 // FLIP (FL): the force-free momentum Q (for v^n = Q / m) shares P's affine
 // part, so the affine gathers take p + q (q the adjoint of Q, gqb) and the
 // force's gathers p alone; the direct adjoint of v_p comes from mid.
@@ -549,6 +602,8 @@ __global__ __launch_bounds__((kAdjBlock<D>)) __attribute__((amdgpu_waves_per_eu(
 {
     constexpr int TE = TileShape<D>::TE, BE = TileShape<D>::BE, NB = TileShape<D>::NB;
     using ML = MidLayout<D>;
+    using B = DenseBlock<D>;
+    constexpr int stride[3] = {1, B::LY, B::LZ};
     __shared__ T s_p[D][NB];     // p (FL: p + q)
     __shared__ T s_f[FL ? D : 1][FL ? NB : 1];   // FL: p
     __shared__ T s_m[NB];
@@ -583,17 +638,15 @@ __global__ __launch_bounds__((kAdjBlock<D>)) __attribute__((amdgpu_waves_per_eu(
         for (int k = tid; k < at.cnt; k += kAdjBlock<D>) {
             long long s = at.off + k;
             int j = perm[s];
-            T w[D][3], dw[D][3], dd[D][3], vp[D], Cp[D][D], Sp[D][D];
-            int lb[3] = {0, 0, 0};
+            AxisFactors<T, D> A;
+            T dwd[D][3], vp[D], Cp[D][D], Sp[D][D];
+            int n0 = 0;
 #pragma unroll
             for (int a = 0; a < D; ++a) {
-                int b;
-                T f;
-                stencil_axis(st.x[a * cap + j], P.inv, b, f, w[a], dw[a]);
-                int l = b + g.G - tc[a] * TE;
-                lb[a] = l < 0 ? 0 : (l > TE - 1 ? TE - 1 : l);
+                const T xa = st.x[a * cap + j], f = block_axis_f(P, xa);
+                n0 += block_axis(g, P, a, xa, tc[a], A) * stride[a];
 #pragma unroll
-                for (int q = 0; q < 3; ++q) dd[a][q] = (T(q) - f) * P.h;
+                for (int q = 0; q < 3; ++q) dwd[a][q] = A.dw[a][q] * ((T(q) - f) * P.h) - A.w[a][q];
                 vp[a] = st.v[a * cap + j];
 #pragma unroll
                 for (int b2 = 0; b2 < D; ++b2) Cp[a][b2] = st.C[(a * D + b2) * cap + j];
@@ -613,147 +666,58 @@ __global__ __launch_bounds__((kAdjBlock<D>)) __attribute__((amdgpu_waves_per_eu(
                 Sp[0][0] = st.S[0 * cap + j]; Sp[1][1] = st.S[1 * cap + j];
                 Sp[0][1] = Sp[1][0] = st.S[2 * cap + j];
             }
-            // With p_i, m_i the node adjoints of momentum and mass, the
-            // particle's adjoints are gathers over its stencil:
-            //   vbar = m sum phi p,  Cbar = m sum phi p (x_i - x_p)^T,
-            //   Sbar = -dt sum p (grad phi)^T =: -dt Lp,
-            //   xbar += m [ sum grad phi (m_i + (x_i - x_p).(Cp^T p)) + Lp^T v_p
-            //              - Cp^T (sum phi p) ] - dt sum Hess(phi) (S_p p).
-            T V[D], Bp[D][D], Lp[D][D], X1[D], X2[D];
-            T Lf[FL ? D : 1][FL ? D : 1];   // FL: the force's sum p (grad phi)^T
+            // With p_i, m_i the node adjoints of momentum and mass, per component
+            // (see axis_vjp, c = m v, p = m C, q = -dt S):
+            //   vbar = m sum phi p,  Cbar_b = m sum phi p dd_b = m sum_k wd_b R_b,
+            //   Sbar_b = -dt sum p d_b phi = -dt sum_k dw_b R_b,
+            // and the position adjoint through the weights (wb) and through E.
+            // FLIP: the affine part takes p + q (s_p), the force p alone (s_f).
+            T xbar[D], vbar[D], Cbar[D][D], Sbar[D][D], wb[D][3];
+#pragma unroll
+            for (int b = 0; b < D; ++b) {
+                xbar[b] = mid[b * cap + s];
+#pragma unroll
+                for (int q = 0; q < 3; ++q) wb[b][q] = T(0);
+            }
 #pragma unroll
             for (int a = 0; a < D; ++a) {
-                V[a] = T(0);
-                X1[a] = T(0);
-                X2[a] = T(0);
-#pragma unroll
-                for (int b = 0; b < D; ++b) { Bp[a][b] = T(0); Lp[a][b] = T(0); }
-            }
-            if constexpr (FL)
-#pragma unroll
-                for (int a = 0; a < D; ++a)
-#pragma unroll
-                    for (int b = 0; b < D; ++b) Lf[a][b] = T(0);
-            // Both passes run line by line along x: every weight, gradient and
-            // Hessian entry of phi is a product of per-axis factors, so each
-            // line is first reduced with the x factors, then combined with
-            // the line's y/z factors.  ddw, the second derivative of the
-            // quadratic B-spline, is (1, -2, 1)/h^2 along each axis.
-            constexpr int NL = (D == 3) ? 9 : 3;
-            const T ddw[3] = {inv2, T(-2) * inv2, inv2};
-            T wdx[3];
-#pragma unroll
-            for (int q = 0; q < 3; ++q) wdx[q] = w[0][q] * dd[0][q];
-            // pass 1: the G2P-like gathers of p
-#pragma unroll
-            for (int l = 0; l < NL; ++l) {
-                const int ky = l % 3, kz = l / 3;
-                const T lw = (D == 3) ? w[1][ky] * w[2][kz] : w[1][ky];
-                const T ld1 = lw * dd[1][ky];
-                const T ldw1 = (D == 3) ? dw[1][ky] * w[2][kz] : dw[1][ky];
-                const int n0 = (D == 3) ? ((lb[2] + kz) * BE + lb[1] + ky) * BE + lb[0] : (lb[1] + ky) * BE + lb[0];
-#pragma unroll
-                for (int a = 0; a < D; ++a) {
-                    T p0 = s_p[a][n0], p1 = s_p[a][n0 + 1], p2 = s_p[a][n0 + 2];
-                    T A0 = w[0][0] * p0 + w[0][1] * p1 + w[0][2] * p2;
-                    T A1 = wdx[0] * p0 + wdx[1] * p1 + wdx[2] * p2;
-                    T A2 = dw[0][0] * p0 + dw[0][1] * p1 + dw[0][2] * p2;
-                    V[a] += lw * A0;
-                    Bp[a][0] += lw * A1;
-                    Bp[a][1] += ld1 * A0;
-                    Lp[a][0] += lw * A2;
-                    Lp[a][1] += ldw1 * A0;
-                    if constexpr (D == 3) {
-                        Bp[a][2] += (lw * dd[2][kz]) * A0;
-                        Lp[a][2] += (w[1][ky] * dw[2][kz]) * A0;
-                    }
-                    if constexpr (FL) {
-                        T f0 = s_f[a][n0], f1 = s_f[a][n0 + 1], f2 = s_f[a][n0 + 2];
-                        T F0 = w[0][0] * f0 + w[0][1] * f1 + w[0][2] * f2;
-                        T F2 = dw[0][0] * f0 + dw[0][1] * f1 + dw[0][2] * f2;
-                        Lf[a][0] += lw * F2;
-                        Lf[a][1] += ldw1 * F0;
-                        if constexpr (D == 3) Lf[a][2] += (w[1][ky] * dw[2][kz]) * F0;
-                    }
-                }
-                __builtin_amdgcn_sched_barrier(0);
-            }
-            // pass 2: X1 = sum grad phi (m_i + (x_i - x_p).(Cp^T p_i)) and
-            // X2 = sum Hess(phi) (S_p p_i); per node s_i and sp_i = S_p p_i,
-            // per line the x-reductions
-            //   A = sum s dw_x, B = sum s w_x, C1 = sum sp_x ddw_x,
-            //   C2 = sum sp_y dw_x, C3 = sum sp_z dw_x, C4 = sum sp_x dw_x,
-            //   C5 = sum sp_y w_x, C6 = sum sp_z w_x
-#pragma unroll
-            for (int l = 0; l < NL; ++l) {
-                const int ky = l % 3, kz = l / 3;
-                const int n0 = (D == 3) ? ((lb[2] + kz) * BE + lb[1] + ky) * BE + lb[0] : (lb[1] + ky) * BE + lb[0];
-                T A = T(0), B = T(0), Cx[6] = {T(0), T(0), T(0), T(0), T(0), T(0)};
-#pragma unroll
-                for (int kx = 0; kx < 3; ++kx) {
-                    const int n = n0 + kx;
-                    T pb[D], pf[D];
-#pragma unroll
-                    for (int a = 0; a < D; ++a) {
-                        pb[a] = s_p[a][n];
-                        if constexpr (FL) pf[a] = s_f[a][n];
-                        else pf[a] = pb[a];
-                    }
-                    T sc = s_m[n], sp[D];
-                    const T ddn[3] = {dd[0][kx], dd[1][ky], (D == 3) ? dd[D - 1][kz] : T(0)};
-#pragma unroll
-                    for (int b = 0; b < D; ++b) {
-                        T ub = T(0), sb = T(0);
-#pragma unroll
-                        for (int a = 0; a < D; ++a) {
-                            ub += Cp[a][b] * pb[a];
-                            sb += Sp[b][a] * pf[a];
-                        }
-                        sp[b] = sb;
-                        sc += ddn[b] * ub;
-                    }
-                    A += sc * dw[0][kx];
-                    B += sc * w[0][kx];
-                    Cx[0] += sp[0] * ddw[kx];
-                    Cx[1] += sp[1] * dw[0][kx];
-                    Cx[3] += sp[0] * dw[0][kx];
-                    Cx[4] += sp[1] * w[0][kx];
-                    if constexpr (D == 3) {
-                        Cx[2] += sp[D - 1] * dw[0][kx];
-                        Cx[5] += sp[D - 1] * w[0][kx];
-                    }
-                }
-                if constexpr (D == 3) {
-                    const T wy = w[1][ky], dwy = dw[1][ky], wz = w[2][kz], dwz = dw[2][kz];
-                    X1[0] += wy * wz * A;
-                    X1[1] += dwy * wz * B;
-                    X1[2] += wy * dwz * B;
-                    X2[0] += wy * wz * Cx[0] + dwy * wz * Cx[1] + wy * dwz * Cx[2];
-                    X2[1] += dwy * wz * Cx[3] + ddw[ky] * wz * Cx[4] + dwy * dwz * Cx[5];
-                    X2[2] += wy * dwz * Cx[3] + dwy * dwz * Cx[4] + wy * ddw[kz] * Cx[5];
-                } else {
-                    const T wy = w[1][ky], dwy = dw[1][ky];
-                    X1[0] += wy * A;
-                    X1[1] += dwy * B;
-                    X2[0] += wy * Cx[0] + dwy * Cx[1];
-                    X2[1] += dwy * Cx[3] + ddw[ky] * Cx[4];
-                }
-                __builtin_amdgcn_sched_barrier(0);
-            }
-            T xbar[D], vbar[D], Cbar[D][D], Sbar[D][D];
-#pragma unroll
-            for (int c = 0; c < D; ++c) {
-                T t = X1[c];
-#pragma unroll
-                for (int a = 0; a < D; ++a) t += Lp[a][c] * vp[a] - Cp[a][c] * V[a];
-                xbar[c] = mid[c * cap + s] + P.mass * t - P.dt * X2[c];
-                vbar[c] = P.mass * V[c];
-                if constexpr (FL) vbar[c] += mid[(ML::V + c) * cap + s];
+                T E[D][3], R[D][3], pc[D], qc[D], none[D];
+                const T c = P.mass * vp[a];
 #pragma unroll
                 for (int b = 0; b < D; ++b) {
-                    Cbar[c][b] = P.mass * Bp[c][b];
-                    if constexpr (FL) Sbar[c][b] = -P.dt * Lf[c][b];
-                    else Sbar[c][b] = -P.dt * Lp[c][b];
+                    pc[b] = P.mass * Cp[a][b];
+                    qc[b] = -P.dt * Sp[a][b];
+                    none[b] = T(0);
+                }
+                axis_terms<T, D>(A, pc, FL ? none : qc, E);
+                axis_vjp<B>(s_p[a], n0, A, c, E, R, wb);
+                vbar[a] = P.mass * dot3(A.w[0], R[0]);
+                if constexpr (FL) vbar[a] += mid[(ML::V + a) * cap + s];
+#pragma unroll
+                for (int b = 0; b < D; ++b) {
+                    Cbar[a][b] = P.mass * dot3(A.wd[b], R[b]);
+                    if constexpr (!FL) Sbar[a][b] = -P.dt * dot3(A.dw[b], R[b]);
+                    xbar[b] += axis_dx(dwd[b], inv2, pc[b], FL ? T(0) : qc[b], R[b]);
+                }
+                if constexpr (FL) {
+                    axis_terms<T, D>(A, none, qc, E);
+                    axis_vjp<B>(s_f[a], n0, A, T(0), E, R, wb);
+#pragma unroll
+                    for (int b = 0; b < D; ++b) {
+                        Sbar[a][b] = -P.dt * dot3(A.dw[b], R[b]);
+                        xbar[b] += axis_dx(dwd[b], inv2, T(0), qc[b], R[b]);
+                    }
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            {
+                T R[D][3];
+                axis_sums<B>(s_m, n0, A, R);
+#pragma unroll
+                for (int b = 0; b < D; ++b) {
+#pragma unroll
+                    for (int q = 0; q < 3; ++q) wb[b][q] = fma(P.mass, R[b][q], wb[b][q]);
+                    xbar[b] += dot3(wb[b], A.dw[b]);
                 }
             }
             // the particle's adjoint goes to its slot before the step's sort

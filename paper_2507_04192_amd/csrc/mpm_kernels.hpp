@@ -32,8 +32,23 @@
 namespace mpm {
 
 template <int D> struct TileShape;
+// TE: cells per edge, BE: block nodes per edge, NB: block nodes.
 template <> struct TileShape<3> { static constexpr int TE = 4, BE = 6, NB = 216; };
 template <> struct TileShape<2> { static constexpr int TE = 8, BE = 10, NB = 100; };
+
+// How a block lies in LDS: row and plane stride, size, and the place of block
+// node i.  DenseBlock: as in memory.  PaddedBlock (3-D): lanes are cells, at
+// x + LY y + LZ z over a tile's 4^3; with 8 and 52 a binary64 access meets each
+// pair of banks from exactly two lanes, where the dense 6 and 36 collide.
+template <int D>
+struct DenseBlock {
+    static constexpr int LY = TileShape<D>::BE, LZ = LY * LY, LN = TileShape<D>::NB;
+    static __device__ __forceinline__ int at(int i) { return i; }
+};
+struct PaddedBlock {
+    static constexpr int LY = 8, LZ = 52, LN = 312;
+    static __device__ __forceinline__ int at(int i) { return (i / 36) * LZ + (i / 6) % 6 * LY + i % 6; }
+};
 
 constexpr int kSortCap = 1024;   // particles per tile sorted in LDS (larger: in perm)
 // threads of a 3-D P2G workgroup, one tile each: two waves that split the node
@@ -1289,10 +1304,10 @@ struct AxisFactors {
 // line by line was 144 and the lines' factors.  The barrier after each plane
 // keeps the compiler from hoisting all LDS reads of the stencil (registers,
 // occupancy).
-template <class T, int D, int NB>
-__device__ __forceinline__ void axis_sums(const T (&f)[NB], int n0, const AxisFactors<T, D>& A, T R[D][3])
+template <class B, class T, int D>
+__device__ __forceinline__ void axis_sums(const T (&f)[B::LN], int n0, const AxisFactors<T, D>& A, T R[D][3])
 {
-    constexpr int BE = TileShape<D>::BE;
+    constexpr int LY = B::LY, LZ = B::LZ;
     if constexpr (D == 2) {
 #pragma unroll
         for (int k = 0; k < 3; ++k) R[0][k] = R[1][k] = T(0);
@@ -1300,7 +1315,7 @@ __device__ __forceinline__ void axis_sums(const T (&f)[NB], int n0, const AxisFa
         for (int ky = 0; ky < 3; ++ky)
 #pragma unroll
             for (int kx = 0; kx < 3; ++kx) {
-                const T p = f[n0 + ky * BE + kx];
+                const T p = f[n0 + ky * LY + kx];
                 R[0][kx] = fma(A.w[1][ky], p, R[0][kx]);
                 R[1][ky] = fma(A.w[0][kx], p, R[1][ky]);
             }
@@ -1318,7 +1333,7 @@ __device__ __forceinline__ void axis_sums(const T (&f)[NB], int n0, const AxisFa
                 T x = T(0);   // summed along x
 #pragma unroll
                 for (int kx = 0; kx < 3; ++kx) {
-                    const T p = f[n0 + (kz * BE + ky) * BE + kx];
+                    const T p = f[n0 + kz * LZ + ky * LY + kx];
                     x = fma(A.w[0][kx], p, x);
                     xy[ky][kx] = fma(A.w[2][kz], p, xy[ky][kx]);
                 }
@@ -1567,7 +1582,8 @@ __global__ __launch_bounds__((kG2PBlock<T, D>)) void k_g2p(Geo g, Phys<T> P, con
                 int j = mine_first ? j_first : ld_once(&perm[s]);
                 T xp[D];
                 AxisFactors<T, D> A;
-                int n0 = 0, ns = 1;
+                int n0 = 0;
+                const int stride[3] = {1, BE, BE * BE};
 #pragma unroll
                 for (int a = 0; a < D; ++a) {
                     xp[a] = mine_first ? x_first[a] : ld_once(&cur.x[a * cap + j]);
@@ -1575,15 +1591,14 @@ __global__ __launch_bounds__((kG2PBlock<T, D>)) void k_g2p(Geo g, Phys<T> P, con
                     A.set(a, t - fb, P.inv, P.h);
                     int l = (int)fb + g.G - tc[a] * TE;
                     l = l < 0 ? 0 : (l > TE - 1 ? TE - 1 : l);   // memory guard only
-                    n0 += l * ns;
-                    ns *= BE;
+                    n0 += l * stride[a];
                 }
                 // vn = sum phi v,  Bm = sum phi v (x_i - x_p)^T,  Lm = sum v (grad phi)^T
                 T vn[D], Bm[D][D], Lm[D][D], vo[FL ? D : 1];
 #pragma unroll
                 for (int a = 0; a < D; ++a) {
                     T R[D][3];
-                    axis_sums<T, D, NB>(s_v[a], n0, A, R);
+                    axis_sums<DenseBlock<D>>(s_v[a], n0, A, R);
                     vn[a] = dot3(A.w[0], R[0]);
 #pragma unroll
                     for (int b = 0; b < D; ++b) {
@@ -1591,7 +1606,7 @@ __global__ __launch_bounds__((kG2PBlock<T, D>)) void k_g2p(Geo g, Phys<T> P, con
                         Lm[a][b] = dot3(A.dw[b], R[b]);
                     }
                     if constexpr (FL) {
-                        axis_sums<T, D, NB>(s_vo[a], n0, A, R);
+                        axis_sums<DenseBlock<D>>(s_vo[a], n0, A, R);
                         vo[a] = dot3(A.w[0], R[0]);
                     }
                 }
