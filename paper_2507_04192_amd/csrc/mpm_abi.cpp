@@ -206,8 +206,8 @@ Layout make_layout(const mpm_config& c, const Geo& g, int64_t cap, int tape_step
         size_t nts = (size_t)tape_segs_of(c, tape_steps, ckpt_every);
         L.ckpt = take(nck * sb);
         L.ckpt_pid = take(nck * ucap * 4);
-        L.tape = take(nts * (size_t)(ckpt_every + 1) * sb);
-        L.tape_pid = take(nts * (size_t)(ckpt_every + 1) * ucap * 4);
+        L.tape = take(nts * (size_t)ckpt_every * sb);
+        L.tape_pid = take(nts * (size_t)ckpt_every * ucap * 4);
         L.adj[0] = take(sb);
         L.adj[1] = take(sb);
         // position and F adjoints (FLIP: and the direct velocity adjoint)

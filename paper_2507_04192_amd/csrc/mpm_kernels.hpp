@@ -2097,9 +2097,12 @@ struct Solver {
     // (FLIP: P2G and the grid update also form the velocity before the
     // update).  The transfer is a template parameter: as a run-time choice it
     // kept both affine candidates live in G2P and cost it half its waves.
+    // Without `advance` the new particle state is not wanted: in 3-D the step
+    // ends with the grid (in 2-D the nodes are formed by G2P's launch), and the
+    // caller forms the keys before the next step (new_keys).
     template <int MAT, int XF = XF_APIC>
     static void step_views(mpm_ctx* c, const Phys<T>& P, const PView<T>& cur, const PView<T>& nxt,
-                           const StepBufs& b)
+                           const StepBufs& b, bool advance = true)
     {
         constexpr bool FL = XF == XF_FLIP;
         // P2G depends on the material only through the stored stress: one
@@ -2137,9 +2140,11 @@ struct Solver {
         k_grid<T, D, FL><<<tile_wgs(c, kGridBlock), kGridBlock, 0, st>>>(g, P, b.meta, b.active, b.tile_slot, (const T*)c->part_grid,
                                                   b.gv, b.gmass, b.gvt, b.gvo);
         prof_mark(c, MPM_PROF_GRID);
-        k_g2p<T, D, MAT, XF><<<tile_wgs(c, kG2PBlock<T, D>), kG2PBlock<T, D>, 0, st>>>(g, P, b.meta, b.active, b.perm, cur, nxt, (const T*)b.gv,
-                                                      (const T*)b.gvo, c->key, count, c->status, b.eps_in, b.eps_out, Nodes2<T>{}, c->moved);
-        prof_mark(c, MPM_PROF_G2P);
+        if (advance) {
+            k_g2p<T, D, MAT, XF><<<tile_wgs(c, kG2PBlock<T, D>), kG2PBlock<T, D>, 0, st>>>(g, P, b.meta, b.active, b.perm, cur, nxt, (const T*)b.gv,
+                                                          (const T*)b.gvo, c->key, count, c->status, b.eps_in, b.eps_out, Nodes2<T>{}, c->moved);
+            prof_mark(c, MPM_PROF_G2P);
+        }
         c->turn = n;
         c->ranges_known = true;
         }

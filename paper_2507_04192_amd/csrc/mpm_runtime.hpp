@@ -86,7 +86,7 @@ struct mpm_ctx {
     // forward-plus-adjoint rollout (mpm_forward_loss / mpm_backward)
     char* ckpt = nullptr;          // checkpoints, one state every ckpt_every steps
     int32_t* ckpt_pid = nullptr;
-    char* tape = nullptr;          // states of tape_segs segments (ckpt_every + 1 each)
+    char* tape = nullptr;          // states of tape_segs segments (ckpt_every each: their start is the checkpoint)
     int32_t* tape_pid = nullptr;
     char* adj[2] = {nullptr, nullptr};   // adjoint states (same layout as a state)
     void* mid = nullptr;           // per slot: position and F (or J) adjoints between the reverse kernels (FLIP: and the direct velocity adjoint)
