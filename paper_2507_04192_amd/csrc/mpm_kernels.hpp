@@ -61,6 +61,14 @@ template <class T, int D> constexpr int kG2PBlock = sizeof(T) == 8 && D == 3 ? 1
 // (binary64: measured faster; binary32: slower)
 template <class T> constexpr bool kG2PPrefetch = sizeof(T) == 8;
 constexpr int kGridBlock = 128;  // threads of a grid-update workgroup
+constexpr int kScanOnce = 1024;  // threads of the one-launch scan
+// Tiles up to which the scan is one launch whose workgroups each sum all
+// earlier counts: latency, not bytes, bounds the scan, and that trip is shorter
+// than a launch until the counts of the last workgroup's sum take as long.
+// Two launches and one: 1,000 tiles 12.4 and 6.9 us, 20,480 14.3 and 7.8, 64,000
+// 15.1 and 10.1, 131,072 15.5 and 13.0, 262,144 16.4 and 18.0, 512,000 21.4 and
+// 28.5.  Cylinder (65 k tiles) 13.8 and 9.9, columns 14.5 and 7.9.
+constexpr int kScanOnceTiles = 131072;
 
 // Particle data read once per step (G2P's old state; P2G's inputs where the
 // state outgrows the caches, see p2g_hint) and the part of G2P's output that no
@@ -119,6 +127,94 @@ __device__ __forceinline__ void block_scan2(int a, int b, int& ex_a, int& ex_b, 
     __syncthreads();
 }
 
+// What the scan leaves for tile t with c particles from `off` on; slot: its
+// place in the active list.
+__device__ __forceinline__ void scan_put(int t, int c, int off, int& slot, int* __restrict__ tile_off,
+                                         int* __restrict__ tile_slot, ActiveTile* __restrict__ active,
+                                         int2* __restrict__ range, int* __restrict__ count_next)
+{
+    tile_off[t] = off;
+    if (range) range[t] = make_int2(off, c);
+    if (count_next) count_next[t] = 0;
+    if (c > 0) {
+        tile_slot[t] = slot;
+        ActiveTile e;
+        e.tile = t;
+        e.off = off;
+        e.cnt = c;
+        e.pad = 0;
+        active[slot] = e;
+        ++slot;
+    } else {
+        tile_slot[t] = -1;
+    }
+}
+
+// The scan in one launch: each workgroup sums all earlier counts itself, 32 per
+// thread and trip.
+template <int Unused = 0>
+__global__ __launch_bounds__(kScanOnce) void k_scan_once(const int* __restrict__ count, int ntiles,
+                                                         int* __restrict__ tile_off, int* __restrict__ tile_slot,
+                                                         ActiveTile* __restrict__ active, int* __restrict__ meta,
+                                                         int2* __restrict__ range, int* __restrict__ count_next)
+{
+    constexpr int PER = kScanChunk / kScanOnce, NW = kScanOnce / 64, BATCH = 8;
+    __shared__ int s_sum[NW][4];
+    const int base = blockIdx.x * kScanChunk, t0 = base + (int)threadIdx.x * PER;
+    int c[PER], ls = 0, la = 0;
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+        c[k] = t0 + k < ntiles ? count[t0 + k] : 0;
+        ls += c[k];
+        la += c[k] > 0;
+    }
+    const int4* before = (const int4*)count;   // base is a multiple of 4
+    int ps = 0, pa = 0;
+    for (int i0 = 0; i0 < base / 4; i0 += BATCH * kScanOnce) {
+        int4 v[BATCH];
+#pragma unroll
+        for (int q = 0; q < BATCH; ++q) {
+            const int i = i0 + q * kScanOnce + (int)threadIdx.x;
+            v[q] = i < base / 4 ? before[i] : make_int4(0, 0, 0, 0);
+        }
+#pragma unroll
+        for (int q = 0; q < BATCH; ++q) {
+            ps += v[q].x + v[q].y + v[q].z + v[q].w;
+            pa += (v[q].x > 0) + (v[q].y > 0) + (v[q].z > 0) + (v[q].w > 0);
+        }
+    }
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    int is = ls, ia = la;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const int ts = __shfl_up(is, o), ta = __shfl_up(ia, o);
+        if (lane >= o) { is += ts; ia += ta; }
+        ps += __shfl_xor(ps, o);
+        pa += __shfl_xor(pa, o);
+    }
+    if (lane == 63) {
+        s_sum[w][0] = ps;
+        s_sum[w][1] = pa;
+        s_sum[w][2] = is;
+        s_sum[w][3] = ia;
+    }
+    __syncthreads();
+    int off = is - ls, slot = ia - la;
+    for (int k = 0; k < NW; ++k) {
+        off += s_sum[k][0] + (k < w ? s_sum[k][2] : 0);
+        slot += s_sum[k][1] + (k < w ? s_sum[k][3] : 0);
+    }
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+        if (t0 + k < ntiles) scan_put(t0 + k, c[k], off, slot, tile_off, tile_slot, active, range, count_next);
+        off += c[k];
+    }
+    if (blockIdx.x == gridDim.x - 1 && threadIdx.x == kScanOnce - 1) {
+        meta[0] = slot;
+        meta[1] = off;
+    }
+}
+
 template <int Unused = 0>
 __global__ __launch_bounds__(kBlock) void k_scan_reduce(const int* __restrict__ count, int ntiles,
                                                         int* __restrict__ part)
@@ -173,23 +269,7 @@ __global__ __launch_bounds__(kBlock) void k_scan_down(const int* __restrict__ co
 #pragma unroll
     for (int k = 0; k < PER; ++k) {
         int t = t0 + k;
-        if (t < ntiles) {
-            tile_off[t] = off;
-            if (range) range[t] = make_int2(off, c[k]);
-            if (count_next) count_next[t] = 0;
-            if (c[k] > 0) {
-                tile_slot[t] = slot;
-                ActiveTile e;
-                e.tile = t;
-                e.off = off;
-                e.cnt = c[k];
-                e.pad = 0;
-                active[slot] = e;
-                ++slot;
-            } else {
-                tile_slot[t] = -1;
-            }
-        }
+        if (t < ntiles) scan_put(t, c[k], off, slot, tile_off, tile_slot, active, range, count_next);
         off += c[k];
     }
     if (blockIdx.x == gridDim.x - 1 && threadIdx.x == kBlock - 1) {
@@ -2112,8 +2192,6 @@ struct Solver {
         const Geo& g = c->geo;
         unsigned nsb = (unsigned)((g.ntiles + kScanChunk - 1) / kScanChunk);
         prof_mark(c, -1);
-        // one chunk has no earlier chunks to sum: the down-sweep alone (a
-        // launch fewer for the small grids, whose steps are launch-bound)
         if constexpr (D == 2) {
             step_views2<MAT, XF>(c, P, cur, nxt, b, nsb);
             return;
@@ -2154,8 +2232,13 @@ struct Solver {
     static void scan_tiles(mpm_ctx* c, unsigned nsb, const int* count, const StepBufs& b, int2* range, int* count_next)
     {
         hipStream_t st = c->stream;
-        // one chunk has no earlier chunks to sum: the down-sweep alone
-        if (nsb > 1) k_scan_reduce<0><<<nsb, kBlock, 0, st>>>(count, c->geo.ntiles, c->part);
+        if (c->geo.ntiles <= kScanOnceTiles) {
+            k_scan_once<0><<<nsb, kScanOnce, 0, st>>>(count, c->geo.ntiles, c->tile_off, b.tile_slot, b.active, b.meta, range,
+                                                      count_next);
+            prof_mark(c, MPM_PROF_SCAN);
+            return;
+        }
+        k_scan_reduce<0><<<nsb, kBlock, 0, st>>>(count, c->geo.ntiles, c->part);
         k_scan_down<0><<<nsb, kBlock, 0, st>>>(count, c->geo.ntiles, c->part, c->tile_off, b.tile_slot, b.active, b.meta,
                                                range, count_next);
         prof_mark(c, MPM_PROF_SCAN);
