@@ -407,30 +407,23 @@ __device__ __forceinline__ void node_adjoint(const Geo& g, const Phys<T>& P, con
 #pragma unroll
         for (int a = 0; a < D; ++a) qb[a] = T(0);
     if (!(m > T(0))) return;
+    // the walls forward, the velocity before each kept for its reverse (all
+    // indexes are constants after unrolling, so nothing goes to scratch)
     T vin[2 * D][D], vel[D];
-    int nf = 0, fc[2 * D];
-    T fmu[2 * D];
 #pragma unroll
     for (int a = 0; a < D; ++a) vel[a] = vt[a];
-    for (int a = 0; a < D; ++a) {
-        int ip = I[a] - g.G;
-        for (int side = 0; side < 2; ++side) {
-            bool beyond = side == 0 ? (ip <= 0) : (ip >= g.n[a]);
-            if (!beyond) continue;
-            int face = 2 * a + side;
-            T mu = P.wall_mu[face];
-            if (face == 2 * (D - 1) && P.floor_mu) {
-                int fx = min(I[0], g.box[0] - 1);
-                int fi = (D == 3) ? min(I[1], g.box[1] - 1) * P.floor_stride + fx : fx;
-                mu = P.floor_mu[fi];
-            }
+    auto beyond = [&](int face) { const int ip = I[face / 2] - g.G; return face % 2 == 0 ? ip <= 0 : ip >= g.n[face / 2]; };
+    auto floor_at = [&] {
+        const int fx = min(I[0], g.box[0] - 1);
+        return (D == 3) ? min(I[1], g.box[1] - 1) * P.floor_stride + fx : fx;
+    };
+    auto friction = [&](int face) { return face == 2 * (D - 1) && P.floor_mu ? P.floor_mu[floor_at()] : P.wall_mu[face]; };
 #pragma unroll
-            for (int q = 0; q < D; ++q) vin[nf][q] = vel[q];
-            fc[nf] = face;
-            fmu[nf] = mu;
-            ++nf;
-            wall_node<T, D>(P.wall_mode[face], mu, a, side == 0 ? T(-1) : T(1), vel);
-        }
+    for (int face = 0; face < 2 * D; ++face) {
+#pragma unroll
+        for (int q = 0; q < D; ++q) vin[face][q] = vel[q];
+        if (beyond(face))
+            wall_node<T, D>(P.wall_mode[face], friction(face), face / 2, face % 2 == 0 ? T(-1) : T(1), vel);
     }
     // resting obstacles after the walls (Sec. 4.2.1): a component that one of
     // them removed passes no adjoint back
@@ -438,24 +431,18 @@ __device__ __forceinline__ void node_adjoint(const Geo& g, const Phys<T>& P, con
         double xi[D];
 #pragma unroll
         for (int a = 0; a < D; ++a) xi[a] = double(I[a] - g.G) * P.obst_h;
-        int cut[kMaxObstacles];
         for (int o = 0; o < P.n_obst; ++o) {
-            cut[o] = obstacle_component<T, D>(P, o, xi, vel);
-            if (cut[o] >= 0) vel[cut[o]] = T(0);
-        }
-        for (int o = P.n_obst - 1; o >= 0; --o)
+            const int cut = obstacle_component<T, D>(P, o, xi, vel);
+#pragma unroll
             for (int a = 0; a < D; ++a)
-                if (cut[o] == a) vb[a] = T(0);
-    }
-    for (int f = nf - 1; f >= 0; --f) {
-        int face = fc[f], a = face / 2;
-        T sign = (face % 2 == 0) ? T(-1) : T(1);
-        T mub = wall_node_vjp<T, D>(P.wall_mode[face], fmu[f], a, sign, vin[f], vb);
-        if (amu && face == 2 * (D - 1) && P.floor_mu && mub != T(0)) {
-            int fx = min(I[0], g.box[0] - 1);
-            int fi = (D == 3) ? min(I[1], g.box[1] - 1) * P.floor_stride + fx : fx;
-            atomicAdd(&amu[fi], (double)mub);
+                if (cut == a) vel[a] = vb[a] = T(0);
         }
+    }
+#pragma unroll
+    for (int face = 2 * D - 1; face >= 0; --face) {
+        if (!beyond(face)) continue;
+        const T mub = wall_node_vjp<T, D>(P.wall_mode[face], friction(face), face / 2, face % 2 == 0 ? T(-1) : T(1), vin[face], vb);
+        if (amu && face == 2 * (D - 1) && P.floor_mu && mub != T(0)) atomicAdd(&amu[floor_at()], (double)mub);
     }
     T dot = T(0);
 #pragma unroll
@@ -478,64 +465,39 @@ __global__ __launch_bounds__((kAdjBlock<D>)) void k_grid_adj(Geo g, Phys<T> P, c
                                                      T* __restrict__ gv, T* __restrict__ gvo,
                                                      double* __restrict__ amu)
 {
-    constexpr int TE = TileShape<D>::TE, BE = TileShape<D>::BE, NB = TileShape<D>::NB;
-    const int n_active = meta[0];
+    // FLIP: the partial blocks also carry the adjoint of the velocity before
+    // the update, after the first D
+    constexpr int NVA = FL ? 2 * D + 1 : D + 1, NS = FL ? 2 * D : D;
+    struct Node {
+        T m, vt[D], vo[D];
+    };
+    __shared__ int s_around[kAdjBlock<D> / 64][27];
     for (int it = 0;; ++it) {
-        int e = tile_entry(it, n_active);
-        if (e < 0) break;
-        int tile = active[e].tile;
-        int tc[3];
-        tile_coords(g, tile, tc);
-        for (int i = threadIdx.x; i < NB; i += kAdjBlock<D>) {
-            int l[3] = {i % BE, (i / BE) % BE, (D == 3) ? i / (BE * BE) : 0};
-            int I[3], own[3];
-            bool down[3];
+        const int tile = node_tile<kAdjBlock<D> / 64>(it, meta, active, g.ntiles);
+        if (tile < 0) break;
+        tile_nodes<T, NVA, NS>(
+            g, tile, tile_slot, part, s_around[threadIdx.x >> 6],
+            [&](long long node) {
+                Node in;
+                in.m = gmass[node];
 #pragma unroll
-            for (int a = 0; a < 3; ++a) {
-                I[a] = (a < D) ? tc[a] * TE + l[a] : 0;
-                own[a] = I[a] / TE;
-                down[a] = (a < D) && (I[a] % TE < 2) && own[a] >= 1;
-            }
-            constexpr int NC = 1 << D;
-            int slot[NC], li[NC];
-            const int des = node_blocks<D>(g, I, own, down, tile_slot, slot, li);
-            if (des != tile) continue;
-            // FLIP: the partial blocks also carry the adjoint of the velocity
-            // before the update, after the first D
-            constexpr int NVA = FL ? 2 * D + 1 : D + 1;
-            T vb[D], vob[D];
+                for (int a = 0; a < D; ++a) {
+                    in.vt[a] = gvt[a * g.NN + node];
+                    if constexpr (FL) in.vo[a] = gvo[a * g.NN + node];
+                }
+                return in;
+            },
+            [&](const int I[3], long long node, const Node& in, T sum[NS]) {
+                T pb[D], qb[D], mb;
+                node_adjoint<T, D, FL>(g, P, I, in.m, in.vt, sum, in.vo, sum + NS - D, amu, pb, mb, qb);
 #pragma unroll
-            for (int a = 0; a < D; ++a) {
-                vb[a] = T(0);
-                vob[a] = T(0);
-            }
-#pragma unroll
-            for (int msk = 0; msk < NC; ++msk) {
-                if (slot[msk] < 0) continue;
-                const T* src = part + (long long)slot[msk] * NVA * NB;
-#pragma unroll
-                for (int a = 0; a < D; ++a) vb[a] += src[a * NB + li[msk]];
+                for (int a = 0; a < D; ++a) gv[a * g.NN + node] = pb[a];
+                gmass[node] = mb;
+                // FLIP: the adjoint of Q replaces v^n in the record
                 if constexpr (FL)
 #pragma unroll
-                    for (int a = 0; a < D; ++a) vob[a] += src[(D + a) * NB + li[msk]];
-            }
-            long long node = node_index(g, I[0], I[1], I[2]);
-            const T m = gmass[node];
-            T vt[D], vo[D], pb[D], qb[D], mb;
-#pragma unroll
-            for (int a = 0; a < D; ++a) {
-                vt[a] = gvt[a * g.NN + node];
-                if constexpr (FL) vo[a] = gvo[a * g.NN + node];
-            }
-            node_adjoint<T, D, FL>(g, P, I, m, vt, vb, vo, vob, amu, pb, mb, qb);
-#pragma unroll
-            for (int a = 0; a < D; ++a) gv[a * g.NN + node] = pb[a];
-            gmass[node] = mb;
-            // FLIP: the adjoint of Q replaces v^n in the record
-            if constexpr (FL)
-#pragma unroll
-                for (int a = 0; a < D; ++a) gvo[a * g.NN + node] = qb[a];
-        }
+                    for (int a = 0; a < D; ++a) gvo[a * g.NN + node] = qb[a];
+            });
     }
 }
 

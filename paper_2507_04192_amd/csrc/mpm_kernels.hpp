@@ -61,13 +61,16 @@ template <class T, int D> constexpr int kG2PBlock = sizeof(T) == 8 && D == 3 ? 1
 // (binary64: measured faster; binary32: slower)
 template <class T> constexpr bool kG2PPrefetch = sizeof(T) == 8;
 constexpr int kGridBlock = 128;  // threads of a grid-update workgroup
+constexpr int kHaloAt = 2;       // meta[kHaloAt]: halo tiles of the step (see Halo)
+constexpr int kHaloSum = 8;      // where it gathers in the context's meta
 constexpr int kScanOnce = 1024;  // threads of the one-launch scan
 // Tiles up to which the scan is one launch whose workgroups each sum all
 // earlier counts: latency, not bytes, bounds the scan, and that trip is shorter
 // than a launch until the counts of the last workgroup's sum take as long.
 // Two launches and one: 1,000 tiles 12.4 and 6.9 us, 20,480 14.3 and 7.8, 64,000
 // 15.1 and 10.1, 131,072 15.5 and 13.0, 262,144 16.4 and 18.0, 512,000 21.4 and
-// 28.5.  Cylinder (65 k tiles) 13.8 and 9.9, columns 14.5 and 7.9.
+// 28.5.  Cylinder (65 k tiles) 13.8 and 9.9, columns 14.5 and 7.9 (11.5 and 8.6
+// with the halo list beside it).
 constexpr int kScanOnceTiles = 131072;
 
 // Particle data read once per step (G2P's old state; P2G's inputs where the
@@ -102,6 +105,34 @@ __device__ __forceinline__ int tile_entry(int it, int n_active)
     return e < end ? e : -1;
 }
 
+// Lane q: the active slot of neighbour q of a 3-D tile (x fastest, the tile
+// itself at 13), -1 where that is empty or outside the grid or q > 26.
+__device__ __forceinline__ int around_slot(const Geo& g, int tile, const int* __restrict__ tile_slot)
+{
+    const int lane = threadIdx.x & 63;
+    int tc[3];
+    tile_coords(g, tile, tc);
+    const int tx = tc[0] + lane % 3 - 1, ty = tc[1] + (lane / 3) % 3 - 1, tz = tc[2] + lane / 9 - 1;
+    if (lane > 26 || tx < 0 || ty < 0 || tz < 0 || tx >= g.ntile[0] || ty >= g.ntile[1] || tz >= g.ntile[2]) return -1;
+    return tile_slot[(tz * g.ntile[1] + ty) * g.ntile[0] + tx];
+}
+
+// Tile handled by this wave (one of the workgroup's NW) on iteration `it`: an
+// active tile, then a halo tile, each list in one contiguous chunk per
+// XCD; -1: none left.
+template <int NW>
+__device__ __forceinline__ int node_tile(int it, const int* __restrict__ meta, const ActiveTile* __restrict__ active, int ntiles)
+{
+    const int n_active = meta[0], n_halo = meta[kHaloAt];
+    const int xcd = blockIdx.x % 8;
+    int i = ((int)(blockIdx.x / 8) + it * (int)(gridDim.x / 8)) * NW + (int)(threadIdx.x >> 6);
+    const int ca = (n_active + 7) / 8, ch = (n_halo + 7) / 8;
+    const int na = max(min((xcd + 1) * ca, n_active) - xcd * ca, 0), nh = max(min((xcd + 1) * ch, n_halo) - xcd * ch, 0);
+    if (i < na) return active[xcd * ca + i].tile;
+    i -= na;
+    return i < nh ? active[ntiles - 1 - (xcd * ch + i)].tile : -1;
+}
+
 // ---------------------------------------------------------------------------
 // Block-wide exclusive scan of two ints (256 threads).
 // ---------------------------------------------------------------------------
@@ -125,6 +156,51 @@ __device__ __forceinline__ void block_scan2(int a, int b, int& ex_a, int& ex_b, 
     ex_a = pa + ia - a;
     ex_b = pb + ib - b;
     __syncthreads();
+}
+
+// Halo tiles (3-D): the empty ones that a particle's block of nodes can reach,
+// that is, with particles in one of the seven tiles below.  The grid kernels
+// visit them after the active tiles.  They are appended to `active` from its
+// end, in no particular order (no result depends on it); their number gathers in
+// `n`, which the step's sort moves to meta[kHaloAt] and clears.  Workgroups of
+// the scan's launch beside those that scan form the list, so that it is done
+// when they are: as work of the scanning ones it took 3.5 us more, in the sort 5
+// (its wave waits for the list's counter), in P2G 7 (it costs the stream
+// registers).
+struct Halo {
+    int* n;        // nullptr: no list (2-D)
+    int nx, ny;    // tiles along x and y
+    int first;     // the launch's first workgroup that forms the list
+};
+__device__ __forceinline__ void halo_list(const Halo& h, const int* __restrict__ count, int ntiles, ActiveTile* __restrict__ active)
+{
+    for (int t = ((int)blockIdx.x - h.first) * (int)blockDim.x + (int)threadIdx.x; t - (int)(threadIdx.x & 63) < ntiles;
+         t += ((int)gridDim.x - h.first) * (int)blockDim.x) {
+        const int tx = t % h.nx, ty = (t / h.nx) % h.ny, tz = t / (h.nx * h.ny);
+        int own = 1, below = 0;
+        if (t < ntiles) {
+            own = count[t];
+#pragma unroll
+            for (int m = 1; m < 8; ++m) {
+                const int bx = m & 1, by = (m >> 1) & 1, bz = m >> 2;
+                if (tx >= bx && ty >= by && tz >= bz) below |= count[t - bx - h.nx * (by + h.ny * bz)];
+            }
+        }
+        const bool is = own == 0 && below != 0;
+        const unsigned long long m = __ballot(is);
+        if (!m) continue;
+        const int lane = threadIdx.x & 63;
+        int at = 0;   // one atomic per wave
+        if (lane == 0) at = atomicAdd(h.n, __popcll(m));
+        at = __builtin_amdgcn_readfirstlane(at) + __popcll(m & ((1ull << lane) - 1ull));
+        if (is) active[ntiles - 1 - at].tile = t;
+    }
+}
+// At the start of a step's sort, one thread.
+__device__ __forceinline__ void halo_take(int* __restrict__ n, int* __restrict__ meta)
+{
+    meta[kHaloAt] = *n;
+    *n = 0;
 }
 
 // What the scan leaves for tile t with c particles from `off` on; slot: its
@@ -156,10 +232,14 @@ template <int Unused = 0>
 __global__ __launch_bounds__(kScanOnce) void k_scan_once(const int* __restrict__ count, int ntiles,
                                                          int* __restrict__ tile_off, int* __restrict__ tile_slot,
                                                          ActiveTile* __restrict__ active, int* __restrict__ meta,
-                                                         int2* __restrict__ range, int* __restrict__ count_next)
+                                                         int2* __restrict__ range, int* __restrict__ count_next, Halo halo)
 {
     constexpr int PER = kScanChunk / kScanOnce, NW = kScanOnce / 64, BATCH = 8;
     __shared__ int s_sum[NW][4];
+    if ((int)blockIdx.x >= halo.first) {
+        halo_list(halo, count, ntiles, active);
+        return;
+    }
     const int base = blockIdx.x * kScanChunk, t0 = base + (int)threadIdx.x * PER;
     int c[PER], ls = 0, la = 0;
 #pragma unroll
@@ -209,7 +289,7 @@ __global__ __launch_bounds__(kScanOnce) void k_scan_once(const int* __restrict__
         if (t0 + k < ntiles) scan_put(t0 + k, c[k], off, slot, tile_off, tile_slot, active, range, count_next);
         off += c[k];
     }
-    if (blockIdx.x == gridDim.x - 1 && threadIdx.x == kScanOnce - 1) {
+    if ((int)blockIdx.x == halo.first - 1 && threadIdx.x == kScanOnce - 1) {
         meta[0] = slot;
         meta[1] = off;
     }
@@ -242,8 +322,12 @@ __global__ __launch_bounds__(kBlock) void k_scan_down(const int* __restrict__ co
                                                       const int* __restrict__ part,
                                                       int* __restrict__ tile_off, int* __restrict__ tile_slot,
                                                       ActiveTile* __restrict__ active, int* __restrict__ meta,
-                                                     int2* __restrict__ range, int* __restrict__ count_next)
+                                                     int2* __restrict__ range, int* __restrict__ count_next, Halo halo)
 {
+    if ((int)blockIdx.x >= halo.first) {
+        halo_list(halo, count, ntiles, active);
+        return;
+    }
     // prefix of the earlier chunks
     int ps = 0, pa = 0;
     for (int i = threadIdx.x; i < (int)blockIdx.x; i += kBlock) {
@@ -272,7 +356,7 @@ __global__ __launch_bounds__(kBlock) void k_scan_down(const int* __restrict__ co
         if (t < ntiles) scan_put(t, c[k], off, slot, tile_off, tile_slot, active, range, count_next);
         off += c[k];
     }
-    if (blockIdx.x == gridDim.x - 1 && threadIdx.x == kBlock - 1) {
+    if ((int)blockIdx.x == halo.first - 1 && threadIdx.x == kBlock - 1) {
         meta[0] = slot;
         meta[1] = off;
     }
@@ -641,7 +725,7 @@ constexpr int kSortBlock = 256;
 constexpr int kOwnBatches = 8;   // batches of a tile's own range held in registers (512 particles, 8 per cell)
 
 template <int Unused = 0>
-__global__ __launch_bounds__(kSortBlock) void k_sort_gather(Geo g, Ranges rg, const int* __restrict__ meta,
+__global__ __launch_bounds__(kSortBlock) void k_sort_gather(Geo g, Ranges rg, int* __restrict__ meta, int* __restrict__ n_halo,
                                                             const ActiveTile* __restrict__ active, int* __restrict__ tmp,
                                                             int* __restrict__ tmpk, int* __restrict__ perm,
                                                             int* __restrict__ cell_cnt)
@@ -653,6 +737,7 @@ __global__ __launch_bounds__(kSortBlock) void k_sort_gather(Geo g, Ranges rg, co
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     const unsigned long long below = (1ull << lane) - 1ull;
     int* cnt = s_cnt[w];
+    if (blockIdx.x == 0 && threadIdx.x == 0) halo_take(n_halo, meta);
     // entries by wave: one contiguous chunk of the active list per XCD
     const int chunk = (n_active + 7) / 8, xcd = blockIdx.x % 8, per = (int)(gridDim.x / 8) * NW;
     const int end = min((xcd + 1) * chunk, n_active);
@@ -775,7 +860,7 @@ __global__ __launch_bounds__(kSortBlock) void k_sort_gather(Geo g, Ranges rg, co
 // The same from the bucketed entries of each tile, which come in no order: by
 // placement into the cells and counting, in LDS.
 template <int Unused = 0>
-__global__ __launch_bounds__(kSortBlock) void k_sort(const int* __restrict__ meta, const ActiveTile* __restrict__ active,
+__global__ __launch_bounds__(kSortBlock) void k_sort(int* __restrict__ meta, int* __restrict__ n_halo, const ActiveTile* __restrict__ active,
                                                      int* __restrict__ tmp, const int* __restrict__ tmpk,
                                                      int* __restrict__ perm, int* __restrict__ cell_cnt)
 {
@@ -783,6 +868,7 @@ __global__ __launch_bounds__(kSortBlock) void k_sort(const int* __restrict__ met
     __shared__ TileSort s;
     const int n_active = meta[0];
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    if (blockIdx.x == 0 && tid == 0) halo_take(n_halo, meta);
     for (int it = 0;; ++it) {
         const int e = tile_entry(it, n_active);
         if (e < 0) break;
@@ -1222,40 +1308,106 @@ __global__ __launch_bounds__(NT) void k_sort_p2g2(Geo g, Phys<T> P, Ranges rg, i
 // the partial blocks that cover it, in that same fixed order.
 // ---------------------------------------------------------------------------
 
-// The partial blocks that cover block node I (global node coordinates):
-// candidate msk takes its own tile minus one along every axis whose bit is
-// set, own tile first.  Writes each candidate's active slot (-1: none) and
-// the node's index in that block, and returns the node's owner tile: the
-// first active candidate (-1 if none).  All slots are loaded before any is
-// used.
-template <int D>
-__device__ __forceinline__ int node_blocks(const Geo& g, const int I[3], const int own[3], const bool down[3],
-                                           const int* __restrict__ tile_slot, int slot[1 << D], int li[1 << D])
+// Whether a node's eight candidate blocks are loaded in one batch or two (past
+// 16 bytes per block two, the registers would cost waves: binary64 18.8 and
+// 18.5 us on the cylinder, FLIP 13.2 and 12.7 on the column).
+template <class T, int NS> constexpr int kNodeUnroll = NS * sizeof(T) <= 16 ? 2 : 1;
+
+// Sums the partial blocks over the 64 nodes of an active or a halo tile, one per
+// lane: NS of a block's NV values per node.  A node's blocks are those of the
+// tile it lies in and of that tile minus one along axes where it is one of the
+// first two nodes; the sum takes them in the order of the bits (x first).  With
+// one wave per tile every lane has its node; when each active tile went over the
+// 216 nodes of its block and left those that another tile owned, 70 % of the
+// threads were idle, and a second pass for the nodes past an active tile alone
+// took longer than the first (three trips to memory in a row).  The 27 tiles
+// around are looked up once, one per lane.  Latency bounds it: the lists, the
+// neighbours, the blocks, the stores.  Grid update, block by block and so: 2.78 M
+// particles binary32 20.9 -> 15.1 us, binary64 26.0 -> 19.2, 1.92 M 20.6 -> 12.7,
+// FLIP binary64 (635,000) 17.2 -> 13.3; its reverse, 1.84 M binary32 26.2 ->
+// 15.5, 442,368 binary64 15.7 -> 10.7.
+// pre(node) loads what else the node needs; post(I, node, in, sum) writes it.
+template <class T, int NV, int NS, class Pre, class Post>
+__device__ __forceinline__ void tile_nodes(const Geo& g, int tile, const int* __restrict__ tile_slot,
+                                           const T* __restrict__ part, int* around_of, Pre pre, Post post)
 {
-    constexpr int TE = TileShape<D>::TE, BE = TileShape<D>::BE, NC = 1 << D;
-    int tl[NC];
+    constexpr int TE = TileShape<3>::TE, BE = TileShape<3>::BE, NB = TileShape<3>::NB;
+    const int lane = threadIdx.x & 63;
+    int tc[3];
+    tile_coords(g, tile, tc);
+    const int around = around_slot(g, tile, tile_slot);
+    // the node at l of the block, h tiles up; slot(b): the block of the tile b
+    // below the one it lies in (-1: none)
+    auto add = [&](const int l[3], const int h[3], auto slot) {
+        const int I[3] = {tc[0] * TE + l[0], tc[1] * TE + l[1], tc[2] * TE + l[2]};
+        const long long node = node_index(g, I[0], I[1], I[2]);
+        const auto in = pre(node);
+        bool any = false;
+        T sum[NS];
 #pragma unroll
-    for (int msk = 0; msk < NC; ++msk) {
-        bool ok = true;
-        int ct[3] = {own[0], own[1], own[2]};
+        for (int q = 0; q < NS; ++q) sum[q] = T(0);
+#pragma unroll kNodeUnroll<T, NS>
+        for (int b2 = 0; b2 < 2; ++b2) {
+            T v[4][NS];
 #pragma unroll
-        for (int a = 0; a < D; ++a) {
-            if ((msk >> a) & 1) {
-                if (!down[a]) ok = false;
-                ct[a] -= 1;
+            for (int m = 0; m < 4; ++m) {
+                const int b[3] = {m & 1, m >> 1, b2}, s = slot(b);
+                any |= s >= 0;
+                const int o[3] = {l[0] + TE * (b[0] - h[0]), l[1] + TE * (b[1] - h[1]), l[2] + TE * (b[2] - h[2])};
+                const T* src = part + (long long)s * NV * NB + (o[2] * BE + o[1]) * BE + o[0];
+#pragma unroll
+                for (int q = 0; q < NS; ++q) v[m][q] = s >= 0 ? src[q * NB] : T(0);
             }
-            if (ct[a] >= g.ntile[a]) ok = false;
-        }
-        tl[msk] = (ct[2] * g.ntile[1] + ct[1]) * g.ntile[0] + ct[0];
-        if constexpr (D == 3) li[msk] = ((I[2] - ct[2] * TE) * BE + I[1] - ct[1] * TE) * BE + I[0] - ct[0] * TE;
-        else li[msk] = (I[1] - ct[1] * TE) * BE + I[0] - ct[0] * TE;
-        slot[msk] = ok ? tile_slot[tl[msk]] : -1;
-    }
-    int des = -1;
 #pragma unroll
-    for (int msk = NC - 1; msk >= 0; --msk)
-        if (slot[msk] >= 0) des = tl[msk];
-    return des;
+            for (int m = 0; m < 4; ++m)
+#pragma unroll
+                for (int q = 0; q < NS; ++q) sum[q] += v[m][q];
+        }
+        if (any) post(I, node, in, sum);
+    };
+    {
+        const int l[3] = {lane % TE, (lane / TE) % TE, lane / (TE * TE)}, h[3] = {0, 0, 0};
+        add(l, h, [&](const int b[3]) {
+            const int s = __builtin_amdgcn_readlane(around, 13 - b[0] - 3 * b[1] - 9 * b[2]);
+            return (!b[0] || l[0] < 2) && (!b[1] || l[1] < 2) && (!b[2] || l[2] < 2) ? s : -1;
+        });
+    }
+    // Past the last tiles of the grid lie two more layers of nodes, which only a
+    // particle beyond the walls reaches.  Each belongs to the first active one of
+    // the tiles whose blocks cover it, in the same order.
+    const unsigned act = (unsigned)__ballot(around >= 0);
+    if (!((act >> 13) & 1) || (tc[0] + 1 < g.ntile[0] && tc[1] + 1 < g.ntile[1] && tc[2] + 1 < g.ntile[2])) return;
+    if (lane < 27) around_of[lane] = around;
+    wave_sync();
+    for (int j0 = 0; j0 < NB - 64; j0 += 64) {
+        // the block's nodes past the tile along z (72), else y (48), else x (32)
+        const int j = j0 + lane;
+        int l[3];
+        if (j < 72) l[0] = j % 6, l[1] = (j / 6) % 6, l[2] = 4 + j / 36;
+        else if (j < 120) l[0] = (j - 72) % 6, l[1] = 4 + ((j - 72) / 6) % 2, l[2] = (j - 72) / 12;
+        else l[0] = 4 + (j - 120) % 2, l[1] = ((j - 120) / 2) % 4, l[2] = (j - 120) / 8;
+        const int h[3] = {l[0] >= TE, l[1] >= TE, l[2] >= TE};
+        auto place = [&](const int b[3]) {
+            const bool covers = (!b[0] || l[0] - TE * h[0] < 2) && (!b[1] || l[1] - TE * h[1] < 2) &&
+                                (!b[2] || l[2] - TE * h[2] < 2);
+            return covers ? 13 + h[0] - b[0] + 3 * (h[1] - b[1]) + 9 * (h[2] - b[2]) : 31;   // bit 31 of act is clear
+        };
+        int owner = -1;
+#pragma unroll
+        for (int msk = 7; msk >= 0; --msk) {
+            const int b[3] = {msk & 1, (msk >> 1) & 1, msk >> 2};
+            if ((act >> place(b)) & 1) owner = msk;
+        }
+        const bool past = (h[0] && tc[0] + 1 == g.ntile[0]) || (h[1] && tc[1] + 1 == g.ntile[1]) ||
+                          (h[2] && tc[2] + 1 == g.ntile[2]);
+        const bool mine = j < NB - 64 && past && owner == (h[0] | h[1] << 1 | h[2] << 2);
+        if (mine)
+            add(l, h, [&](const int b[3]) {
+                const int q = place(b);
+                return (act >> q) & 1 ? around_of[q] : -1;
+            });
+    }
+    wave_sync();
 }
 
 // Velocity of a node of mass m > 0 and momentum p after the grid update, the
@@ -1298,63 +1450,29 @@ __global__ __launch_bounds__(kGridBlock) void k_grid(Geo g, Phys<T> P, const int
                                                  T* __restrict__ gv, T* __restrict__ gmass, T* __restrict__ gvt,
                                                  T* __restrict__ gvo)
 {
-    constexpr int TE = TileShape<D>::TE, BE = TileShape<D>::BE, NB = TileShape<D>::NB;
     constexpr int NV = FL ? 2 * D + 1 : D + 1;
-    const int n_active = meta[0];
+    __shared__ int s_around[kGridBlock / 64][27];
     for (int it = 0;; ++it) {
-        int e = tile_entry(it, n_active);
-        if (e < 0) break;
-        int tile = active[e].tile;
-        int tc[3];
-        tile_coords(g, tile, tc);
-        for (int i = threadIdx.x; i < NB; i += kGridBlock) {
-            int l[3] = {i % BE, (i / BE) % BE, (D == 3) ? i / (BE * BE) : 0};
-            int I[3], own[3];
-            bool down[3];
+        const int tile = node_tile<kGridBlock / 64>(it, meta, active, g.ntiles);
+        if (tile < 0) break;
+        tile_nodes<T, NV, NV>(
+            g, tile, tile_slot, part, s_around[threadIdx.x >> 6], [](long long) { return 0; },
+            [&](const int I[3], long long node, int, const T sum[NV]) {
+                const T m = sum[0];
+                T v[D], vt[D];
 #pragma unroll
-            for (int a = 0; a < 3; ++a) {
-                I[a] = (a < D) ? tc[a] * TE + l[a] : 0;
-                own[a] = I[a] / TE;
-                down[a] = (a < D) && (I[a] % TE < 2) && own[a] >= 1;
-            }
-            constexpr int NC = 1 << D;
-            int slot[NC], li[NC];
-            const int des = node_blocks<D>(g, I, own, down, tile_slot, slot, li);
-            T m = T(0), p[D], pq[FL ? D : 1];
+                for (int a = 0; a < D; ++a) v[a] = vt[a] = T(0);
+                if (m > T(0)) node_velocity<T, D>(g, P, I, m, sum + 1, v, vt);
+                if (gvt)
 #pragma unroll
-            for (int a = 0; a < D; ++a) p[a] = T(0);
-            if constexpr (FL)
+                    for (int a = 0; a < D; ++a) gvt[a * g.NN + node] = vt[a];
 #pragma unroll
-                for (int a = 0; a < D; ++a) pq[a] = T(0);
-            if (des == tile) {
+                for (int a = 0; a < D; ++a) gv[a * g.NN + node] = v[a];
+                if constexpr (FL)
 #pragma unroll
-                for (int msk = 0; msk < NC; ++msk) {
-                    if (slot[msk] < 0) continue;
-                    const T* src = part + (long long)slot[msk] * NV * NB;
-                    m += src[li[msk]];
-#pragma unroll
-                    for (int a = 0; a < D; ++a) p[a] += src[(1 + a) * NB + li[msk]];
-                    if constexpr (FL)
-#pragma unroll
-                        for (int a = 0; a < D; ++a) pq[a] += src[(1 + D + a) * NB + li[msk]];
-                }
-            }
-            if (des != tile) continue;
-            long long node = node_index(g, I[0], I[1], I[2]);
-            T v[D], vt[D];
-#pragma unroll
-            for (int a = 0; a < D; ++a) v[a] = vt[a] = T(0);
-            if (m > T(0)) node_velocity<T, D>(g, P, I, m, p, v, vt);
-            if (gvt)
-#pragma unroll
-                for (int a = 0; a < D; ++a) gvt[a * g.NN + node] = vt[a];
-#pragma unroll
-            for (int a = 0; a < D; ++a) gv[a * g.NN + node] = v[a];
-            if constexpr (FL)
-#pragma unroll
-                for (int a = 0; a < D; ++a) gvo[a * g.NN + node] = m > T(0) ? pq[a] / m : T(0);
-            if (P.keep_grid) gmass[node] = m;
-        }
+                    for (int a = 0; a < D; ++a) gvo[a * g.NN + node] = m > T(0) ? sum[1 + D + a] / m : T(0);
+                if (P.keep_grid) gmass[node] = m;
+            });
     }
 }
 
@@ -2148,8 +2266,10 @@ struct Solver {
         k_fill<int><<<1, kBlock, 0, st>>>(c->status + 1, 3, 0x7fffffff);
         if (c->geo.ntiles > 0)
             k_fill<int><<<std::min<long long>(nblocks(c->geo.ntiles), 4096), kBlock, 0, st>>>(c->tile_slot, c->geo.ntiles, -1);
-        if (D == 3)
+        if (D == 3) {
             k_fill<int><<<std::min<long long>(nblocks(c->geo.ntiles), 4096), kBlock, 0, st>>>(c->moved, c->geo.ntiles, 0);
+            k_fill<int><<<1, kBlock, 0, st>>>(c->meta, 64, 0);
+        }
         return launch_err(c, "clear grid");
     }
 
@@ -2202,10 +2322,10 @@ struct Solver {
         scan_tiles(c, nsb, count, b, c->range[n], nullptr);
         const unsigned swgs = tile_wgs(c, kSortBlock);
         if (c->ranges_known && c->N < (1ll << 30)) {   // key positions plus a batch stay in int32
-            k_sort_gather<0><<<swgs, kSortBlock, 0, st>>>(g, r, b.meta, b.active, c->tmp, c->tmpk, b.perm, c->cell_cnt);
+            k_sort_gather<0><<<swgs, kSortBlock, 0, st>>>(g, r, b.meta, c->meta + kHaloSum, b.active, c->tmp, c->tmpk, b.perm, c->cell_cnt);
         } else {
             bucket(c, count);
-            k_sort<0><<<swgs, kSortBlock, 0, st>>>(b.meta, b.active, c->tmp, c->tmpk, b.perm, c->cell_cnt);
+            k_sort<0><<<swgs, kSortBlock, 0, st>>>(b.meta, c->meta + kHaloSum, b.active, c->tmp, c->tmpk, b.perm, c->cell_cnt);
         }
         prof_mark(c, MPM_PROF_BUCKET);
         if (!FL && p2g_hint(c))
@@ -2232,15 +2352,20 @@ struct Solver {
     static void scan_tiles(mpm_ctx* c, unsigned nsb, const int* count, const StepBufs& b, int2* range, int* count_next)
     {
         hipStream_t st = c->stream;
-        if (c->geo.ntiles <= kScanOnceTiles) {
-            k_scan_once<0><<<nsb, kScanOnce, 0, st>>>(count, c->geo.ntiles, c->tile_off, b.tile_slot, b.active, b.meta, range,
-                                                      count_next);
-            prof_mark(c, MPM_PROF_SCAN);
-            return;
+        const Geo& g = c->geo;
+        const Halo halo{D == 3 ? c->meta + kHaloSum : nullptr, g.ntile[0], g.ntile[1], (int)nsb};
+        const bool once = g.ntiles <= kScanOnceTiles;
+        // the list's workgroups: a tile per thread, as far as the chip has room
+        const int nt = once ? kScanOnce : kBlock;
+        const unsigned wgs = nsb + (D == 3 ? (unsigned)std::min((g.ntiles + nt - 1) / nt, 1024) : 0u);
+        if (once) {
+            k_scan_once<0><<<wgs, kScanOnce, 0, st>>>(count, g.ntiles, c->tile_off, b.tile_slot, b.active, b.meta, range,
+                                                      count_next, halo);
+        } else {
+            k_scan_reduce<0><<<nsb, kBlock, 0, st>>>(count, g.ntiles, c->part);
+            k_scan_down<0><<<wgs, kBlock, 0, st>>>(count, g.ntiles, c->part, c->tile_off, b.tile_slot, b.active, b.meta, range,
+                                                   count_next, halo);
         }
-        k_scan_reduce<0><<<nsb, kBlock, 0, st>>>(count, c->geo.ntiles, c->part);
-        k_scan_down<0><<<nsb, kBlock, 0, st>>>(count, c->geo.ntiles, c->part, c->tile_off, b.tile_slot, b.active, b.meta,
-                                               range, count_next);
         prof_mark(c, MPM_PROF_SCAN);
     }
 
