@@ -233,10 +233,10 @@ TRAFFIC_FILE = os.path.join(ROOT, "profiles", "hbm_traffic_cylinder.txt")
 
 def traffic_kernels(cls, elem):
     """The 3-D sand kernels behind a timed class (template arguments:
-    precision, dimension, material, then FLIP for P2G and the transfer for
-    G2P)."""
+    precision, dimension, material, then FLIP and the non-temporal hint for P2G
+    and the transfer for G2P)."""
     t = "float" if elem == 4 else "double"
-    names = {"p2g": f"k_p2g<{t}, 3, 1, false>", "g2p": f"k_g2p<{t}, 3, 1, 0>",
+    names = {"p2g": f"k_p2g<{t}, 3, 1, false, true>", "g2p": f"k_g2p<{t}, 3, 1, 0>",
              "g2p_adj": f"k_g2p_adj<{t}, 3, 1, false>", "p2g_adj": f"k_p2g_adj<{t}, 3, 1, false>"}
     return [names.get(cls, cls)]
 

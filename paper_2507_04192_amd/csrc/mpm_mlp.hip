@@ -21,7 +21,7 @@ namespace mpm {
 void set_global_error(const char* msg);
 }
 
-// Work buffer of mpm_mlp_backward_noalloc (the layer adjoints dZ), a
+// Work buffer of mpm_mlp_backward_noalloc (the workgroups' gradients), a
 // file-scope device array: every GPU the library runs on holds one copy
 // for the life of the process.  Host code never passes this name to a
 // kernel (on the host it is a stand-in, not a device address); it uses the
