@@ -152,7 +152,7 @@ typedef struct mpm_config {
     /* memory for speed in a forward-plus-adjoint rollout: the number of
      * trailing segments kept on the tape, whose steps the backward sweep
      * does not recompute (0 or 1: the last segment; at most the number of
-     * segments and MPM_MAX_TAPE_SEGMENTS; each costs ckpt_every + 1 states
+     * segments and MPM_MAX_TAPE_SEGMENTS; each costs ckpt_every states
      * and ckpt_every grid records of workspace) */
     int32_t tape_segments;
     /* 1: carry the equivalent plastic strain (MPM_FIELD_EPS_EQ) through
@@ -174,7 +174,7 @@ int mpm_create(const mpm_config* cfg, void* hip_stream, mpm_ctx** out);
 /* Device bytes needed for n_particles and, if tape_steps > 0, for a
  * forward-plus-adjoint rollout of tape_steps steps checkpointed every
  * ckpt_every steps (Sec. 3.3: memory O(N_t / n) per segment): one state per
- * checkpoint, a tape of ckpt_every + 1 states, and a grid tape holding each
+ * checkpoint, a tape of ckpt_every states, and a grid tape holding each
  * step of a segment's sort and nodal mass and velocities. */
 int mpm_workspace_bytes(const mpm_config* cfg, int64_t n_particles, int32_t tape_steps,
                         int32_t ckpt_every, size_t* bytes);

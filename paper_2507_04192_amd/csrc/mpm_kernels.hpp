@@ -501,11 +501,16 @@ struct P2GIn {
     static constexpr int NA = A1 - A0;
     T x[D], v[NA], C[NA * D], S[NS];
     static __device__ __forceinline__ T ld(const T* p) { return NTL ? ld_once(p) : *p; }
+    // Both waves of a tile read the position: in binary32 it is loaded without
+    // the hint, so that the second wave finds it in the cache (cylinder 74.6 ->
+    // 71.8 us, G2P 135.8 -> 134.7).  Binary64 keeps the hint (145.1 and 146.1,
+    // G2P 252 and 256), and so does the stress (72.6; binary64 156).
+    static constexpr bool kLdX = sizeof(T) == 4;
     __device__ __forceinline__ void load(const PView<T>& cur, int j)
     {
         const long long cap = cur.cap;
 #pragma unroll
-        for (int a = 0; a < D; ++a) x[a] = ld(&cur.x[a * cap + j]);
+        for (int a = 0; a < D; ++a) x[a] = kLdX ? cur.x[a * cap + j] : ld(&cur.x[a * cap + j]);
 #pragma unroll
         for (int a = 0; a < NA; ++a) v[a] = ld(&cur.v[(A0 + a) * cap + j]);
 #pragma unroll
