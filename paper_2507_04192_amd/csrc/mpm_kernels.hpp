@@ -435,18 +435,6 @@ __global__ __launch_bounds__(kBlock) void k_init(Geo g, Phys<T> P, const T* __re
     if (valid && rank == 0) atomicAdd(&count[k >> 6], len);
 }
 
-// The tiles' counts to zero; the rows of the last sort, where there are any, to
-// no particle (a captured step that gathers then reads all keys).
-template <int Unused = 0>
-__global__ __launch_bounds__(kBlock) void k_clear_keys(int* __restrict__ count, int* __restrict__ tile_key, int ntiles)
-{
-    const long long n = tile_key ? (long long)ntiles * kTileRow : ntiles, step = (long long)gridDim.x * kBlock;
-    for (long long i = (long long)blockIdx.x * kBlock + threadIdx.x; i < n; i += step) {
-        if (i < ntiles) count[i] = 0;
-        if (tile_key) tile_key[i] = -1;
-    }
-}
-
 template <class T, int D>
 __global__ __launch_bounds__(kBlock) void k_keys(Geo g, Phys<T> P, PView<T> cur, long long N,
                                                  int* __restrict__ key, int* __restrict__ count)
@@ -2273,10 +2261,10 @@ struct Solver {
     }
 
     static int* key_count(const mpm_ctx* c) { return c->count[D == 2 ? c->turn : 0]; }
+    // The tiles' counts to zero; no step has laid out the state that follows.
     static void clear_keys(mpm_ctx* c)
     {
-        const long long n = c->tile_key ? (long long)c->geo.ntiles * kTileRow : c->geo.ntiles;
-        k_clear_keys<0><<<std::min<long long>(nblocks(n), 4096), kBlock, 0, c->stream>>>(key_count(c), c->tile_key, c->geo.ntiles);
+        k_fill<int><<<std::min<long long>(nblocks(c->geo.ntiles), 4096), kBlock, 0, c->stream>>>(key_count(c), c->geo.ntiles, 0);
         c->ranges_known = false;
     }
 
@@ -2347,9 +2335,10 @@ struct Solver {
         hipStream_t st = c->stream;
         const Geo& g = c->geo;
         unsigned nsb = (unsigned)((g.ntiles + kScanChunk - 1) / kScanChunk);
+        const unsigned long long seq = work_seq(c);
         prof_mark(c, -1);
         if constexpr (D == 2) {
-            step_views2<MAT, XF>(c, P, cur, nxt, b, nsb);
+            step_views2<MAT, XF>(c, P, cur, nxt, b, nsb, seq);
             return;
         } else {
         const int o = c->turn, n = 1 - o;
@@ -2357,7 +2346,7 @@ struct Solver {
         const Ranges r{count, nullptr, c->range[o], c->range[n], c->moved, c->key, nullptr, nullptr, (long long)c->N};
         scan_tiles(c, nsb, count, b, c->range[n], nullptr);
         const unsigned swgs = tile_wgs(c, kSortBlock);
-        if (c->ranges_known && c->N < (1ll << 30)) {   // key positions plus a batch stay in int32
+        if (know_ranges(c, seq) && c->N < (1ll << 30)) {   // key positions plus a batch stay in int32
             k_sort_gather<0><<<swgs, kSortBlock, 0, st>>>(g, r, b.meta, c->meta + kHaloSum, b.active, c->tmp, c->tmpk, b.perm, c->cell_cnt);
         } else {
             bucket(c, count);
@@ -2381,6 +2370,7 @@ struct Solver {
         }
         c->turn = n;
         c->ranges_known = true;
+        c->ranges_seq = seq;
         }
     }
 
@@ -2416,10 +2406,11 @@ struct Solver {
     // the tiles are few enough that a workgroup can sum all earlier counts
     // itself (one scan chunk: 8 loads per thread), else the scan and the
     // scatter before them.  Everything that alternates between steps does so on
-    // every step, so that an even number of captured steps can be replayed.
+    // every step, so that an even number of captured steps can be replayed (the
+    // first of them finds its particles by their keys, see work_seq).
     template <int MAT, int XF>
     static void step_views2(mpm_ctx* c, const Phys<T>& P, const PView<T>& cur, const PView<T>& nxt, const StepBufs& b,
-                            unsigned nsb)
+                            unsigned nsb, unsigned long long seq)
     {
         constexpr bool FL = XF == XF_FLIP;
         constexpr int PM = mat_iso_stress(MAT) ? MAT_FLUID : MAT_SAND;
@@ -2430,7 +2421,7 @@ struct Solver {
         const unsigned wgs = small ? (unsigned)((g.ntiles + 7) / 8 * 8) : (unsigned)kTileWGs;
         const Ranges r{c->count[o], c->count[n], c->range[o], c->range[n], nullptr, c->key, c->tile_key,
                           small ? c->tile_perm : nullptr, (long long)c->N};
-        if (small && c->ranges_known && c->N < (1ll << 30)) {   // key positions plus a batch stay in int32
+        if (small && know_ranges(c, seq) && c->N < (1ll << 30)) {   // key positions plus a batch stay in int32
             k_sort_p2g2<T, PM, FL, true, 256><<<wgs, 256, 0, st>>>(g, P, r, b.meta, b.active, b.tile_slot, c->tmp, c->tmpk,
                                                                       cur, b.perm, (T*)c->part_grid);
         } else {
@@ -2451,6 +2442,7 @@ struct Solver {
         prof_mark(c, MPM_PROF_G2P);
         c->turn = n;
         c->ranges_known = small;
+        c->ranges_seq = seq;
     }
 
     template <int MAT, int XF = XF_APIC>

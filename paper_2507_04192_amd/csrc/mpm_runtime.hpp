@@ -69,7 +69,8 @@ struct mpm_ctx {
     int32_t* tile_perm = nullptr;  // 2-D, few tiles: row per tile of the first entries of perm
     int32_t* tile_key = nullptr;   // and of the keys after the step, else null
     int turn = 0;                  // buffer that describes the current state
-    bool ranges_known = false;     // range[turn] is the layout of the current state
+    bool ranges_known = false;     // range[turn] is the layout of the current state ...
+    unsigned long long ranges_seq = 0;   // ... in this sequence of work (see work_seq)
     int32_t* tile_off = nullptr;
     int32_t* tile_slot = nullptr;
     mpm::ActiveTile* active = nullptr;
@@ -145,6 +146,26 @@ struct Ops {
 };
 
 extern const Ops ops_f32_2d, ops_f32_3d, ops_f64_2d, ops_f64_3d;
+
+// The sequence of work that a call's launches go to: 0 for the stream itself,
+// else one value per stream capture.  What a step left behind is known to the
+// next one only within a sequence: captured steps have not run when the call
+// returns, and run later, any number of times, from whatever state there is
+// then.  kNoSeq: not known (no sequence follows it).
+constexpr unsigned long long kNoSeq = ~0ull;
+inline unsigned long long work_seq(const mpm_ctx* c)
+{
+    if (!c->stream) return 0;   // the legacy stream cannot be captured
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    unsigned long long id = 0;
+    if (hipStreamGetCaptureInfo(c->stream, &status, &id) != hipSuccess) {
+        (void)hipGetLastError();
+        return kNoSeq;
+    }
+    if (status == hipStreamCaptureStatusNone) return 0;
+    return status == hipStreamCaptureStatusActive ? id + 1 : kNoSeq;
+}
+inline bool know_ranges(const mpm_ctx* c, unsigned long long seq) { return c->ranges_known && seq != kNoSeq && c->ranges_seq == seq; }
 
 // Records an event on the context's stream that closes a span of kernel class
 // cls (cls < 0 opens a step).  No-op unless profiling is on.
