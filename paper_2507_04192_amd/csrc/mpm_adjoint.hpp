@@ -1070,6 +1070,7 @@ struct Adjoint {
         const int first = nseg - nt, tl = first * k;
         c->taped = 0;
         k_fill<double><<<1, kBlock, 0, st>>>(c->loss, 2, 0.0);
+        const int cur0 = c->cur;
         PView<T> now = ckpt(c, 0);   // the state at t
         int rc = copy_state(c, now, view<T>(c, c->cur));
         if (rc) return rc;
@@ -1089,8 +1090,11 @@ struct Adjoint {
             int fi = frame_index(c, t + 1);
             if (fi >= 0) observe(c, now, fi, nullptr);
         }
-        // the context's state, sort and grid again describe the last step
+        // the context's state, sort and grid again describe the last step; the
+        // state buffer is the one that as many steps off the tape end in
         {
+            c->cur = tl % 2 == 0 ? cur0 : 1 - cur0;
+            S::match_turn(c, true);
             const int ql = nt - 1, il = n - (nseg - 1) * k;
             rc = copy_state(c, view<T>(c, c->cur), now);
             if (rc) return rc;

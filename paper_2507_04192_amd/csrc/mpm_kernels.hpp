@@ -435,6 +435,18 @@ __global__ __launch_bounds__(kBlock) void k_init(Geo g, Phys<T> P, const T* __re
     if (valid && rank == 0) atomicAdd(&count[k >> 6], len);
 }
 
+// The layout of the current state from one set of ranges (2-D: and counts) to
+// the other.
+template <int Unused = 0>
+__global__ __launch_bounds__(kBlock) void k_copy_layout(const int2* __restrict__ range, int2* __restrict__ range_to,
+                                                        const int* __restrict__ count, int* __restrict__ count_to, int ntiles)
+{
+    for (int t = blockIdx.x * kBlock + threadIdx.x; t < ntiles; t += gridDim.x * kBlock) {
+        range_to[t] = range[t];
+        if (count) count_to[t] = count[t];
+    }
+}
+
 template <class T, int D>
 __global__ __launch_bounds__(kBlock) void k_keys(Geo g, Phys<T> P, PView<T> cur, long long N,
                                                  int* __restrict__ key, int* __restrict__ count)
@@ -2246,6 +2258,7 @@ struct Solver {
 
     static int init_particles(mpm_ctx* c, const void* x, const void* v)
     {
+        match_turn(c, false);
         clear_keys(c);
         if (c->cap > 0)
             k_init<T, D><<<nblocks(c->cap), kBlock, 0, c->stream>>>(
@@ -2256,8 +2269,25 @@ struct Solver {
 
     static int recompute_keys(mpm_ctx* c)
     {
+        match_turn(c, false);
         new_keys(c, view<T>(c, c->cur));
         return launch_err(c, "keys");
+    }
+
+    // Whether steps alternate between two sets of ranges (2-D: and counts).
+    static bool alternates(const mpm_ctx* c) { return D == 3 || c->geo.ntiles <= kSmallTiles; }
+    // Between calls the set in use goes with the state buffer in use, so that
+    // captured steps find both where they were at the capture whenever the
+    // state is in the same buffer again.  carry: the set's contents move.
+    static void match_turn(mpm_ctx* c, bool carry)
+    {
+        if (!alternates(c) || c->turn == c->cur) return;
+        if (carry) {
+            const int n = c->geo.ntiles;
+            k_copy_layout<0><<<std::min<long long>(nblocks(n), 4096), kBlock, 0, c->stream>>>(
+                c->range[c->turn], c->range[c->cur], D == 2 ? c->count[c->turn] : nullptr, c->count[D == 2 ? c->cur : 0], n);
+        }
+        c->turn = c->cur;
     }
 
     static int* key_count(const mpm_ctx* c) { return c->count[D == 2 ? c->turn : 0]; }

@@ -40,8 +40,8 @@ def _capture(s, stream, steps=2):
 def _same(a, b, stream, what):
     import torch
     stream.synchronize()
-    for p, q in zip([s for f in FIELDS + ("pid",) for s in [a.mpm_read_state(f)]] + list(a.mpm_read_sort()),
-                    [s for f in FIELDS + ("pid",) for s in [b.mpm_read_state(f)]] + list(b.mpm_read_sort())):
+    read = [[s.mpm_read_state(f) for f in FIELDS + ("pid",)] + [s.read_keys()] for s in (a, b)]
+    for p, q in zip(*read):
         assert torch.equal(p, q), what
 
 
@@ -71,6 +71,72 @@ def test_steps_after_a_capture_that_has_not_run(dim):
         for s in (a, b):
             s.mpm_step(1)
         _same(a, b, st, "eager after a dropped capture")
+    for s in (a, b):
+        assert s.mpm_sync_status()[0] == 0
+        s.close()
+
+
+@DIMS
+def test_replay_after_new_particles(dim):
+    """New particles start in the buffers of the first ones, after any number of
+    eager steps."""
+    import torch
+    cfg, x, v = _problem(dim)
+    st = torch.cuda.Stream()
+    with torch.cuda.stream(st):
+        a, b = _pair(cfg, x.shape[1], st)
+        a.mpm_init_particles(x, v)
+        a.mpm_step(2)
+    g = _capture(a, st)
+    with torch.cuda.stream(st):
+        for k, steps in enumerate((1, 2, 3)):
+            a.mpm_step(steps)
+            y = np.ascontiguousarray(x[:, ::-1])
+            for s in (a, b):
+                s.mpm_init_particles(y, v)
+            g.replay()
+            g.replay()
+            b.mpm_step(4)
+            _same(a, b, st, steps)
+            for s in (a, b):        # and the eager steps go on from the replays
+                s.mpm_step(2)
+            _same(a, b, st, steps)
+    for s in (a, b):
+        assert s.mpm_sync_status()[0] == 0
+        s.close()
+
+
+# rollouts whose steps off the tape, and whose segments before the taped ones,
+# are even and odd in number; with and without the reverse sweep after them
+@DIMS
+@pytest.mark.parametrize("steps,every,reverse", [(4, 2, False), (5, 2, False), (5, 2, True), (6, 3, False), (8, 4, False)])
+def test_replay_after_a_rollout(dim, steps, every, reverse):
+    import torch
+    cfg, x, v = _problem(dim)
+    n = x.shape[1]
+    st = torch.cuda.Stream()
+    with torch.cuda.stream(st):
+        a, b = _pair(cfg, n, st, tape_steps=steps, ckpt_every=every)
+        for s in (a, b):
+            s.mpm_init_particles(x, v)
+            s.mpm_step(2)
+    g = _capture(a, st)
+    with torch.cuda.stream(st):
+        a.mpm_set_observations([steps], tracer_pid=np.arange(8), lag_field="x", lag_target=np.zeros((1, dim, 8)))
+        off_tape = (steps - 1) // every * every
+        a.mpm_forward_loss(steps)
+        b.mpm_step(steps)
+        if reverse:
+            a.mpm_backward()
+        if off_tape % 2:            # the state is in the other buffer, as after as many steps
+            for s in (a, b):
+                s.mpm_step(1)
+        g.replay()
+        b.mpm_step(2)
+        _same(a, b, st, "replay")
+        for s in (a, b):
+            s.mpm_step(3)
+        _same(a, b, st, "eager")
     for s in (a, b):
         assert s.mpm_sync_status()[0] == 0
         s.close()
