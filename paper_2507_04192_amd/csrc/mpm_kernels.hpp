@@ -827,14 +827,11 @@ __global__ __launch_bounds__(kSortBlock) void k_sort_gather(Geo g, Ranges rg, in
                 same &= ((c >> b) & 1) ? bits : ~bits;
             }
             found += __popcll(m);
-            int r = -1;
-            if (mine) {
-                const int rk = __popcll(same & below), base = cnt[c];
-                r = c | (base + rk) << 6;
-                if (rk == 0) cnt[c] = base + __popcll(same);
-            }
+            const int rk = __popcll(same & below), base = cnt[c];
+            wave_sync();   // all lanes of a cell have read its count before its first one adds to it
+            if (mine && rk == 0) cnt[c] = base + __popcll(same);
             wave_sync();
-            return r;
+            return mine ? c | (base + rk) << 6 : -1;
         };
         // a range whose particles go to a list in the tile's range of tmp, tmpk
         auto list = [&](int first, int num) {
