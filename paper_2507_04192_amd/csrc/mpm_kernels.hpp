@@ -435,6 +435,17 @@ __global__ __launch_bounds__(kBlock) void k_init(Geo g, Phys<T> P, const T* __re
     if (valid && rank == 0) atomicAdd(&count[k >> 6], len);
 }
 
+// The tiles' counts and the marks of the last step's moves to none.
+template <int Unused = 0>
+__global__ __launch_bounds__(kBlock) void k_clear_keys(int* __restrict__ count, int* __restrict__ moved, int* __restrict__ head, int ntiles)
+{
+    for (int t = blockIdx.x * kBlock + threadIdx.x; t < ntiles; t += gridDim.x * kBlock) {
+        count[t] = 0;
+        if (moved) moved[t] = 0;
+        if (head) head[t] = -1;
+    }
+}
+
 // The layout of the current state from one set of ranges (2-D: and counts) to
 // the other.
 template <int Unused = 0>
@@ -742,13 +753,28 @@ __device__ __forceinline__ void tile_sort_finish(TileSort& s, bool in_lds, int c
     }
 }
 
+// Particles that left their tile's neighbourhood in a step (beyond the CFL
+// limit), which the next step's sort does not meet in the ranges around their new
+// tile: chained per new tile by G2P, in no order, through their slots.
+struct Far {
+    int* head;   // per tile: a slot, -1 none
+    int* next;   // per slot of a chained particle
+    __device__ __forceinline__ void push(int tile, int slot) const { next[slot] = atomicExch(&head[tile], slot); }
+};
+constexpr int kFarBit = 1 << 27;   // of `moved` (3-D): the tile has such a chain
+// A tile of more particles than this goes through all keys instead of its chain,
+// which is a serial walk, and ranked by counting: at most 4096 tiles are.
+constexpr int kFarCrowd = 4096;
+__device__ __forceinline__ bool far_scans_all(int cnt, long long N) { return cnt > kFarCrowd && cnt > N / 4096; }
+
 // The previous step's layout and this step's, for kernels that gather.
 struct Ranges {
     int* count;              // particles per tile, by the current keys
     int* count_next;         // 2-D: cleared for this step's G2P (3-D: count itself is)
     const int2* range;       // previous sort: first slot and number of each tile's particles
     int2* range_next;        // this sort
-    int* moved;              // 3-D: bit per neighbour that particles came from (cleared for this step's G2P)
+    int* moved;              // 3-D: bit per neighbour that particles came from, kFarBit (cleared for this step's G2P)
+    Far far;                 // chains of the last step (left empty for this step's G2P)
     const int* key;
     const int* tile_key;     // 2-D: the first kTileRow keys of every tile's range, a row per tile
     int* tile_perm;          // 2-D: the same of perm (null: not kept)
@@ -768,8 +794,11 @@ struct Ranges {
 // a particle's rank is the number already seen in its cell: one wave per tile
 // counts along, 64 keys at a time (lanes of one cell are found by six ballots),
 // and no wave waits for another.  A step moves a particle to a neighbouring tile
-// at most; a tile that finds fewer than its count (a step beyond the CFL limit,
-// keys written anew) goes through all keys.
+// at most; those that moved further (a step beyond the CFL limit) are chained to
+// their new tile (see Far), sorted by slot and taken between the ranges, so that
+// such a step costs each particle a few trips to memory, too: with all of 2.65 M
+// particles moved 20 cells the step after takes 0.89 ms (0.26 without), where
+// every tile went through all keys 5.9, and more with every tile and particle.
 // Cylinder, 2,780,000 particles: 15 us, where the scatter took 13 and the sort,
 // by LDS placement inside P2G at its three waves per SIMD, about 25 of P2G's 94
 // (binary32; 19 in a kernel of its own).  It waits for its four dependent round
@@ -777,8 +806,31 @@ struct Ranges {
 constexpr int kSortBlock = 256;
 constexpr int kOwnBatches = 8;   // batches of a tile's own range held in registers (512 particles, 8 per cell)
 
+// One wave: takes a tile's chain and leaves its slots, ascending, in the end of
+// the tile's range of tmp; their number (0 also for a crowded tile).
+__device__ __forceinline__ int far_sorted(const Ranges& rg, const ActiveTile& at, int* __restrict__ tmp, int* __restrict__ scratch)
+{
+    const int lane = threadIdx.x & 63;
+    int j = __builtin_amdgcn_readfirstlane(rg.far.head[at.tile]), n = 0;
+    if (far_scans_all(at.cnt, rg.N)) j = -1;
+    for (; j >= 0 && n < at.cnt; ++n) {
+        if (lane == 0) scratch[n] = j;
+        j = __builtin_amdgcn_readfirstlane(rg.far.next[j]);
+    }
+    if (lane == 0) rg.far.head[at.tile] = -1;
+    __threadfence_block();
+    for (int u = lane; u < n; u += 64) {
+        const int f = scratch[u];
+        int r = 0;
+        for (int q = 0; q < n; ++q) r += scratch[q] < f;
+        tmp[at.off + at.cnt - n + r] = f;
+    }
+    __threadfence_block();
+    return n;
+}
+
 template <int Unused = 0>
-__global__ __launch_bounds__(kSortBlock) void k_sort_gather(Geo g, Ranges rg, int* __restrict__ meta, int* __restrict__ n_halo,
+__global__ __launch_bounds__(kSortBlock) __attribute__((amdgpu_waves_per_eu(8))) void k_sort_gather(Geo g, Ranges rg, int* __restrict__ meta, int* __restrict__ n_halo,
                                                             const ActiveTile* __restrict__ active, int* __restrict__ tmp,
                                                             int* __restrict__ tmpk, int* __restrict__ perm,
                                                             int* __restrict__ cell_cnt)
@@ -833,30 +885,45 @@ __global__ __launch_bounds__(kSortBlock) void k_sort_gather(Geo g, Ranges rg, in
             wave_sync();
             return mine ? c | (base + rk) << 6 : -1;
         };
-        // a range whose particles go to a list in the tile's range of tmp, tmpk
+        // particles that go to a list in the tile's range of tmp, tmpk
+        auto put = [&](int slot, int r) {
+            const unsigned long long m = __ballot(r >= 0);
+            const int at_list = listed + __popcll(m & below);
+            if (r >= 0 && at_list < at.cnt) {
+                tmp[at.off + at_list] = slot;
+                tmpk[at.off + at_list] = r;
+            }
+            listed += __popcll(m);
+        };
         auto list = [&](int first, int num) {
             for (int u0 = 0; u0 < num; u0 += 64 * 4) {
                 int k[4];
 #pragma unroll
                 for (int q = 0; q < 4; ++q) k[q] = u0 + q * 64 + lane < num ? rg.key[first + u0 + q * 64 + lane] : -1;
 #pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const int r = count(k[q]);
-                    const unsigned long long m = __ballot(r >= 0);
-                    const int at_list = listed + __popcll(m & below);
-                    if (r >= 0 && at_list < at.cnt) {
-                        tmp[at.off + at_list] = first + u0 + q * 64 + lane;
-                        tmpk[at.off + at_list] = r;
-                    }
-                    listed += __popcll(m);
-                }
+                for (int q = 0; q < 4; ++q) put(first + u0 + q * 64 + lane, count(k[q]));
+            }
+        };
+        // the far ones wait in the end of that range, which the list reaches
+        // only after it has taken as many of them
+        const int n_far = from & kFarBit ? far_sorted(rg, at, tmp, perm + at.off) : 0;
+        int far_at = 0;
+        auto far_before = [&](int slot) {
+            while (far_at < n_far) {
+                const int u = far_at + lane, j = u < n_far ? tmp[at.off + at.cnt - n_far + u] : 0x7fffffff;
+                const int num = __popcll(__ballot(j < slot));
+                put(j, count(j < slot ? rg.key[j] : -1));
+                far_at += num;
+                if (num < 64) break;
             }
         };
         bool held = own.y <= kOwnBatches * 64;   // the own range's particles stay in ck
         for (unsigned b = from & 0x1fffu; b; b &= b - 1) {
             const int q = __ffs((int)b) - 1;
+            far_before(__shfl(nb.x, q));
             list(__shfl(nb.x, q), __shfl(nb.y, q));
         }
+        far_before(own.x);
         if (held) {
 #pragma unroll
             for (int q = 0; q < kOwnBatches; ++q) ck[q] = count(ck[q]);
@@ -865,9 +932,11 @@ __global__ __launch_bounds__(kSortBlock) void k_sort_gather(Geo g, Ranges rg, in
         }
         for (unsigned b = from & 0x7ffc000u; b; b &= b - 1) {
             const int q = __ffs((int)b) - 1;
+            far_before(__shfl(nb.x, q));
             list(__shfl(nb.x, q), __shfl(nb.y, q));
         }
-        if (found != at.cnt) {
+        far_before(0x7fffffff);
+        if (found != at.cnt) {   // a crowded tile whose chain was not taken
             cnt[lane] = 0;
             wave_sync();
             found = listed = 0;
@@ -910,8 +979,8 @@ __global__ __launch_bounds__(kSortBlock) void k_sort_gather(Geo g, Ranges rg, in
 // The same from the bucketed entries of each tile, which come in no order: by
 // placement into the cells and counting, in LDS.
 template <int Unused = 0>
-__global__ __launch_bounds__(kSortBlock) void k_sort(int* __restrict__ meta, int* __restrict__ n_halo, const ActiveTile* __restrict__ active,
-                                                     int* __restrict__ tmp, const int* __restrict__ tmpk,
+__global__ __launch_bounds__(kSortBlock) void k_sort(Ranges rg, int* __restrict__ meta, int* __restrict__ n_halo,
+                                                     const ActiveTile* __restrict__ active, int* __restrict__ tmp, const int* __restrict__ tmpk,
                                                      int* __restrict__ perm, int* __restrict__ cell_cnt)
 {
     constexpr int NT = kSortBlock, U = (kSortCap + NT - 1) / NT;
@@ -926,6 +995,10 @@ __global__ __launch_bounds__(kSortBlock) void k_sort(int* __restrict__ meta, int
         if (tid < 64) {
             s.cnt[tid] = 0;
             s.cur[tid] = 0;
+        }
+        if (tid == 0) {   // what the last step marked is not used here
+            rg.moved[at.tile] = 0;
+            rg.far.head[at.tile] = -1;
         }
         const bool in_lds = at.cnt <= kSortCap;
         // a tile that fits LDS keeps its entries in registers: one batch of loads
@@ -1112,8 +1185,8 @@ __global__ __launch_bounds__((kP2GBlock<FL>)) __attribute__((amdgpu_waves_per_eu
 // are also kept in a row per tile, whose place is known without the range, so
 // counts, ranges and keys come in one round trip (G2P likewise finds its
 // particles in a row of perm).  A workgroup that finds
-// fewer than its tile's count (a particle moved further, in a step beyond the
-// CFL limit) reads all keys.  The order inside the tile is by cell and previous
+// fewer than its tile's count (particles moved further, in a step beyond the
+// CFL limit) takes the rest from their chain (see Far).  The order inside the tile is by cell and previous
 // slot, whatever order they were found in, so both ways of finding give the
 // same permutation and, from there, the same bits.
 // ---------------------------------------------------------------------------
@@ -1155,7 +1228,7 @@ __global__ __launch_bounds__(NT) void k_sort_p2g2(Geo g, Phys<T> P, Ranges rg, i
     constexpr int NK = 9;
     __shared__ T s_node[NW][NV][NB];
     __shared__ TileSort ts;
-    __shared__ int s_sum[2][NW], s_first[9], s_num[9];
+    __shared__ int s_sum[2][NW], s_first[9], s_num[9], s_far;
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     const int n_active = GATHER ? 0 : meta[0];
     constexpr int U = GATHER ? 9 : (kSortCap + NT - 1) / NT;
@@ -1227,6 +1300,7 @@ __global__ __launch_bounds__(NT) void k_sort_p2g2(Geo g, Phys<T> P, Ranges rg, i
             const int e = tile_entry(it, n_active);
             if (e < 0) break;
             at = active[e];
+            if (rg.far.head && tid == 0) rg.far.head[at.tile] = -1;   // not used here
             __syncthreads();
         }
         const bool in_lds = at.cnt <= kSortCap;
@@ -1263,6 +1337,7 @@ __global__ __launch_bounds__(NT) void k_sort_p2g2(Geo g, Phys<T> P, Ranges rg, i
 #pragma unroll
             for (int b = 0; b < 9; ++b) total = max(total, s_num[b]);
         }
+        int n_far = 0;   // particles of the tile's chain, listed in its range of tmp
         for (;;) {
             for (int u0 = 0; u0 < total; u0 += NT) {
                 batch(u0);
@@ -1274,8 +1349,31 @@ __global__ __launch_bounds__(NT) void k_sort_p2g2(Geo g, Phys<T> P, Ranges rg, i
             if (w == 0) tile_sort_scan(ts, lane);
             __syncthreads();
             if (!GATHER || all || ts.found == at.cnt) break;
+            if (w == 0) {
+                // some came from further away: along their chain, one by one
+                int j = __builtin_amdgcn_readfirstlane(rg.far.head[at.tile]), n = 0;
+                if (far_scans_all(at.cnt, rg.N)) j = -1;
+                for (; j >= 0 && n < at.cnt; ++n) {
+                    if (lane == 0) {
+                        tmp[at.off + n] = j;
+                        atomicAdd(&ts.cnt[rg.key[j] & 63], 1);
+                    }
+                    j = __builtin_amdgcn_readfirstlane(rg.far.next[j]);
+                }
+                if (lane == 0) {
+                    rg.far.head[at.tile] = -1;
+                    s_far = n;
+                }
+                wave_sync();
+                tile_sort_scan(ts, lane);
+            }
+            __syncthreads();
+            n_far = s_far;
+            if (ts.found == at.cnt) break;
+            // a crowded tile whose chain was not taken
             __syncthreads();
             if (tid < 64) ts.cnt[tid] = 0;
+            n_far = 0;
             all = true;
             total = (int)((rg.N + U - 1) / U);
             __syncthreads();
@@ -1292,6 +1390,11 @@ __global__ __launch_bounds__(NT) void k_sort_p2g2(Geo g, Phys<T> P, Ranges rg, i
             for (int q = 0; q < U; ++q)
                 if (cc[q] >= 0) tile_sort_place(ts, in_lds, cc[q], cj[q], perm + at.off);
         }
+        if constexpr (GATHER)
+            for (int u = tid; u < n_far; u += NT) {
+                const int j = tmp[at.off + u];
+                tile_sort_place(ts, in_lds, rg.key[j] & 63, j, perm + at.off);
+            }
         tile_sort_finish<NT>(ts, in_lds, at.cnt, perm + at.off, tmp + at.off);
         const int* sorted = in_lds ? ts.sorted : (perm + at.off);
         if (rg.tile_perm && tid < at.cnt) rg.tile_perm[at.tile * kTileRow + tid] = sorted[tid];   // NT = a row
@@ -1738,7 +1841,7 @@ __global__ __launch_bounds__((kG2PBlock<T, D>)) void k_g2p(Geo g, Phys<T> P, con
                                                 const T* __restrict__ gvo,
                                                 int* __restrict__ key_out, int* __restrict__ count,
                                                 int* __restrict__ status, const T* __restrict__ eps_in,
-                                                T* __restrict__ eps_out, Nodes2<T> nd, int* __restrict__ moved)
+                                                T* __restrict__ eps_out, Nodes2<T> nd, int* __restrict__ moved, Far far)
 {
     constexpr int TE = TileShape<D>::TE, BE = TileShape<D>::BE, NB = TileShape<D>::NB;
     constexpr int NS = D * (D + 1) / 2;
@@ -1950,15 +2053,19 @@ __global__ __launch_bounds__((kG2PBlock<T, D>)) void k_g2p(Geo g, Phys<T> P, con
                 key_out[s] = newkey;
                 if constexpr (D == 2)
                     if (by_tile && k < kTileRow) nd.tile_key[at.tile * kTileRow + k] = newkey;
-                if constexpr (D == 3)
-                    if ((newkey >> 6) != at.tile) {
-                        // into a neighbouring tile: tell it where from
-                        int nt[3];
-                        tile_coords(g, newkey >> 6, nt);
-                        const int dx = tc[0] - nt[0], dy = tc[1] - nt[1], dz = tc[2] - nt[2];
-                        if (abs(dx) <= 1 && abs(dy) <= 1 && abs(dz) <= 1)
-                            atomicOr(&moved[newkey >> 6], 1 << ((dz + 1) * 9 + (dy + 1) * 3 + dx + 1));
+                if ((D == 3 || by_tile) && (newkey >> 6) != at.tile) {
+                    // into another tile: a neighbouring one is told where from
+                    // (2-D: it looks at all its neighbours)
+                    int nt[3];
+                    tile_coords(g, newkey >> 6, nt);
+                    const int dx = tc[0] - nt[0], dy = tc[1] - nt[1], dz = tc[2] - nt[2];
+                    if (abs(dx) <= 1 && abs(dy) <= 1 && abs(dz) <= 1) {
+                        if constexpr (D == 3) atomicOr(&moved[newkey >> 6], 1 << ((dz + 1) * 9 + (dy + 1) * 3 + dx + 1));
+                    } else {
+                        far.push(newkey >> 6, (int)s);
+                        if constexpr (D == 3) atomicOr(&moved[newkey >> 6], kFarBit);
                     }
+                }
             }
             int head, len, rank;
             wave_runs(valid ? (newkey >> 6) : -1, valid, head, len, rank);
@@ -2288,10 +2395,11 @@ struct Solver {
     }
 
     static int* key_count(const mpm_ctx* c) { return c->count[D == 2 ? c->turn : 0]; }
-    // The tiles' counts to zero; no step has laid out the state that follows.
+    // No step has laid out the state that follows.
     static void clear_keys(mpm_ctx* c)
     {
-        k_fill<int><<<std::min<long long>(nblocks(c->geo.ntiles), 4096), kBlock, 0, c->stream>>>(key_count(c), c->geo.ntiles, 0);
+        k_clear_keys<0><<<std::min<long long>(nblocks(c->geo.ntiles), 4096), kBlock, 0, c->stream>>>(
+            key_count(c), D == 3 ? c->moved : nullptr, c->far_head, c->geo.ntiles);
         c->ranges_known = false;
     }
 
@@ -2317,10 +2425,8 @@ struct Solver {
         k_fill<int><<<1, kBlock, 0, st>>>(c->status + 1, 3, 0x7fffffff);
         if (c->geo.ntiles > 0)
             k_fill<int><<<std::min<long long>(nblocks(c->geo.ntiles), 4096), kBlock, 0, st>>>(c->tile_slot, c->geo.ntiles, -1);
-        if (D == 3) {
-            k_fill<int><<<std::min<long long>(nblocks(c->geo.ntiles), 4096), kBlock, 0, st>>>(c->moved, c->geo.ntiles, 0);
-            k_fill<int><<<1, kBlock, 0, st>>>(c->meta, 64, 0);
-        }
+        if (D == 3) k_fill<int><<<1, kBlock, 0, st>>>(c->meta, 64, 0);
+        clear_keys(c);
         return launch_err(c, "clear grid");
     }
 
@@ -2370,14 +2476,14 @@ struct Solver {
         } else {
         const int o = c->turn, n = 1 - o;
         int* count = c->count[0];
-        const Ranges r{count, nullptr, c->range[o], c->range[n], c->moved, c->key, nullptr, nullptr, (long long)c->N};
+        const Ranges r{count, nullptr, c->range[o], c->range[n], c->moved, {c->far_head, c->far_next}, c->key, nullptr, nullptr, (long long)c->N};
         scan_tiles(c, nsb, count, b, c->range[n], nullptr);
         const unsigned swgs = tile_wgs(c, kSortBlock);
         if (know_ranges(c, seq) && c->N < (1ll << 30)) {   // key positions plus a batch stay in int32
             k_sort_gather<0><<<swgs, kSortBlock, 0, st>>>(g, r, b.meta, c->meta + kHaloSum, b.active, c->tmp, c->tmpk, b.perm, c->cell_cnt);
         } else {
             bucket(c, count);
-            k_sort<0><<<swgs, kSortBlock, 0, st>>>(b.meta, c->meta + kHaloSum, b.active, c->tmp, c->tmpk, b.perm, c->cell_cnt);
+            k_sort<0><<<swgs, kSortBlock, 0, st>>>(r, b.meta, c->meta + kHaloSum, b.active, c->tmp, c->tmpk, b.perm, c->cell_cnt);
         }
         prof_mark(c, MPM_PROF_BUCKET);
         if (!FL && p2g_hint(c))
@@ -2392,7 +2498,7 @@ struct Solver {
         prof_mark(c, MPM_PROF_GRID);
         if (advance) {
             k_g2p<T, D, MAT, XF><<<tile_wgs(c, kG2PBlock<T, D>), kG2PBlock<T, D>, 0, st>>>(g, P, b.meta, b.active, b.perm, cur, nxt, (const T*)b.gv,
-                                                          (const T*)b.gvo, c->key, count, c->status, b.eps_in, b.eps_out, Nodes2<T>{}, c->moved);
+                                                          (const T*)b.gvo, c->key, count, c->status, b.eps_in, b.eps_out, Nodes2<T>{}, c->moved, r.far);
             prof_mark(c, MPM_PROF_G2P);
         }
         c->turn = n;
@@ -2446,7 +2552,7 @@ struct Solver {
         const bool small = g.ntiles <= kSmallTiles;
         const int o = c->turn, n = small ? 1 - o : o;
         const unsigned wgs = small ? (unsigned)((g.ntiles + 7) / 8 * 8) : (unsigned)kTileWGs;
-        const Ranges r{c->count[o], c->count[n], c->range[o], c->range[n], nullptr, c->key, c->tile_key,
+        const Ranges r{c->count[o], c->count[n], c->range[o], c->range[n], nullptr, {c->far_head, c->far_next}, c->key, c->tile_key,
                           small ? c->tile_perm : nullptr, (long long)c->N};
         if (small && know_ranges(c, seq) && c->N < (1ll << 30)) {   // key positions plus a batch stay in int32
             k_sort_p2g2<T, PM, FL, true, 256><<<wgs, 256, 0, st>>>(g, P, r, b.meta, b.active, b.tile_slot, c->tmp, c->tmpk,
@@ -2465,7 +2571,7 @@ struct Solver {
         prof_mark(c, MPM_PROF_P2G);
         const Nodes2<T> nd{(const T*)c->part_grid, b.tile_slot, small ? c->range[n] : nullptr, c->tile_perm, c->tile_key, b.gv, b.gmass, b.gvt, b.gvo};
         k_g2p<T, D, MAT, XF><<<wgs, kG2PBlock<T, D>, 0, st>>>(g, P, b.meta, b.active, b.perm, cur, nxt, nullptr, nullptr, c->key,
-                                                              c->count[n], c->status, b.eps_in, b.eps_out, nd, nullptr);
+                                                              c->count[n], c->status, b.eps_in, b.eps_out, nd, nullptr, r.far);
         prof_mark(c, MPM_PROF_G2P);
         c->turn = n;
         c->ranges_known = small;

@@ -66,6 +66,8 @@ struct mpm_ctx {
     int32_t* count[2] = {nullptr, nullptr};  // particles per tile; 2-D steps alternate, 3-D uses the first
     int2* range[2] = {nullptr, nullptr};     // first slot and number of each tile's particles, by turn
     int32_t* moved = nullptr;      // 3-D: per tile, the neighbours that particles came from in the last step
+    int32_t* far_head = nullptr;   // chains of those that came from further away (not 2-D of many tiles)
+    int32_t* far_next = nullptr;
     int32_t* tile_perm = nullptr;  // 2-D, few tiles: row per tile of the first entries of perm
     int32_t* tile_key = nullptr;   // and of the keys after the step, else null
     int turn = 0;                  // buffer that describes the current state

@@ -42,3 +42,46 @@ def test_crowded_cells_keep_their_order(dim, n, width):
         perm = s.mpm_read_sort()[0].cpu().numpy()
         assert np.array_equal(perm, expected_perm(key)), k
     s.close()
+
+
+# blobs 20 to 24 cells around a centre thrown onto it in one step: one far
+# particle each, batches of 64, more; and a centre so crowded that it goes
+# through all keys
+@pytest.mark.parametrize("dim", [2, 3])
+@pytest.mark.parametrize("centre,each", [(0, 1), (40, 1), (300, 13), (300, 64), (700, 400), (6000, 30)])
+def test_particles_from_far_away_are_in_order(dim, centre, each):
+    import torch
+    from paper_2507_04192_amd.native import Solver
+    print(f"[case] far moves {dim}-D {centre} {each}", flush=True)
+    cells = (70, 66, 1) if dim == 2 else (70, 66, 24)
+    cfg = _config(dim, cells)
+    rng = np.random.default_rng(dim * 1000 + centre + each)
+    mid = np.array([[0.34], [0.33], [0.12]])[:dim]
+    off = 0.01 * np.array([[24, 0, 0], [-24, 0, 0], [0, 22, 0], [0, -21, 0], [20, 20, 0], [-20, 20, 0]])[:, :dim]
+    xs = [mid + rng.uniform(-0.025, 0.025, size=(dim, centre))]
+    vs = [rng.normal(0.0, 2.0, size=(dim, centre))]          # some of them into neighbouring tiles
+    for o in off:
+        xs.append(mid + o[:, None] + rng.uniform(-0.025, 0.025, size=(dim, each)))
+        vs.append(np.repeat(-o[:, None] / cfg.dt, each, axis=1))
+    x, v = np.concatenate(xs, axis=1), np.concatenate(vs, axis=1)
+    mix = rng.permutation(x.shape[1])
+    x, v = x[:, mix], v[:, mix]
+    a, b = (Solver(cfg, "f64", capacity=x.shape[1]) for _ in range(2))
+    for s in (a, b):
+        s.mpm_init_particles(x, np.zeros_like(v))
+        s.mpm_step(1)
+        s.mpm_write_state("v", v, "pid")
+        s.mpm_step(1)
+    assert a.mpm_sync_status()[0] == -5      # reported
+    for k in range(3):
+        for s in (a, b):
+            s.mpm_write_state("v", v * (0.0, 1.0, -1.0)[k], "pid")
+        key = a.read_keys().cpu().numpy()
+        b.mpm_write_state("x", b.mpm_read_state("x"))        # by keys alone
+        for s in (a, b):
+            s.mpm_step(1)
+        perm = a.mpm_read_sort()[0]
+        assert np.array_equal(perm.cpu().numpy(), expected_perm(key)), k
+        assert torch.equal(perm, b.mpm_read_sort()[0]), k
+    for s in (a, b):
+        s.close()
