@@ -27,6 +27,21 @@ namespace mpm {
 // threads of the reverse per-tile kernels (2-D: a tile's particles at once)
 template <int D> constexpr int kAdjBlock = D == 2 ? 256 : 128;
 
+// Waves per SIMD of the reverse G2P.  The materials without F take two, in 3-D
+// binary64 at the price of a few spilled registers (fluid 20, viscous 36,
+// hypoelastic 0 bytes a lane; with FLIP 180, 188, 72).  That pays where the
+// tiles fill two: a tile is two waves, the chip 1024 SIMDs, so up to 512 tiles
+// one wave each with all registers is as fast or faster.  Binary64, one wave and
+// two, 97,336 particles: fluid 43 and 49 us, viscous 45 and 52, hypoelastic 56 and
+// 56, with FLIP 67 and 82, 69 and 82, 72 and 85; 216,000: 67 and 57, 69 and 60, 63
+// and 64, with FLIP 98 and 99, 100 and 99, 107 and 97; 381,216: 93 and 74, 96 and
+// 80, 82 and 84, with FLIP 144 and 136, 146 and 139, 152 and 128.
+template <int MAT> constexpr int kAdjWaves = mat_has_F(MAT) ? 1 : 2;
+// The tiles with particles are not known to the host: at eight particles per
+// cell, as most bodies are started, a full tile holds 512, and those at the
+// border less; 131,072 fill 256, and reach about 400.
+inline bool adj_few_tiles(const mpm_ctx* c) { return c->geo.ntiles <= 512 || c->N <= 131072; }
+
 // Per-slot intermediate of the reverse sweep (mid), component-major with
 // stride cap, written by k_g2p_adj and read by k_p2g_adj:
 //   [0, D)              position adjoint
@@ -167,14 +182,14 @@ __device__ __forceinline__ T axis_dx(const T dwd[3], T inv2, T p, T q, const T R
 // written after the first in the tile's partial block), its weights pass
 // an adjoint to the position, and alpha times the adjoint of v' goes to mid
 // as the direct adjoint of v_p.
-// What bounds it: binary32 the LDS atomics (81 per particle, half of its time)
-// beside the arithmetic, binary64 the registers.  3-D dam-break, 1,843,200
-// particles, by lines along x -> by axis sums: binary32 153 -> 133 us, binary64
-// 333 -> 221 at two waves per SIMD, which the materials without F fit (sand
-// would spill: 114 -> 190 us on the half cylinder, where by axis sums alone it
-// went 125 -> 114).
-template <class T, int D, int MAT, bool FL>
-__global__ __launch_bounds__((kAdjBlock<D>)) __attribute__((amdgpu_waves_per_eu(mat_has_F(MAT) ? 1 : 2))) void k_g2p_adj(Geo g, Phys<T> P, const int* __restrict__ meta,
+// What bounds it: binary32 the LDS atomics (81 per particle) and the arithmetic,
+// binary64 the registers.  3-D dam-break, 1,843,200 particles, by lines along x ->
+// by axis sums: binary32 153 -> 133 us, binary64 333 -> 221 at two waves per SIMD
+// (sand would spill: 114 -> 190 us on the half cylinder, where by axis sums alone
+// it went 125 -> 114).
+// WV: waves per SIMD asked for, see kAdjWaves.
+template <class T, int D, int MAT, bool FL, int WV>
+__global__ __launch_bounds__((kAdjBlock<D>)) __attribute__((amdgpu_waves_per_eu(WV))) void k_g2p_adj(Geo g, Phys<T> P, const int* __restrict__ meta,
                                                     const ActiveTile* __restrict__ active,
                                                     const int* __restrict__ perm, PView<T> st, PView<T> aout,
                                                     const T* __restrict__ gv, const T* __restrict__ gvo,
@@ -969,14 +984,15 @@ struct Adjoint {
         const Geo& g = c->geo;
         prof_mark(c, -1);
         const bool flip = c->xfer == XF_FLIP;
-        if (flip)
-            k_g2p_adj<T, D, MAT, true><<<tile_wgs(c, kAdjBlock<D>), kAdjBlock<D>, 0, st>>>(
-                g, P, rb.meta, rb.active, rb.perm, st_in, aout, (const T*)rb.gv, (const T*)rb.gvo, (T*)c->part_grid,
-                (T*)c->mid);
-        else
-            k_g2p_adj<T, D, MAT, false><<<tile_wgs(c, kAdjBlock<D>), kAdjBlock<D>, 0, st>>>(
-                g, P, rb.meta, rb.active, rb.perm, st_in, aout, (const T*)rb.gv, nullptr, (T*)c->part_grid,
-                (T*)c->mid);
+        auto g2p_adj = [&](auto fl) {
+            constexpr bool FL = decltype(fl)::value;
+            constexpr int WV = kAdjWaves<MAT>, WF = sizeof(T) == 8 && D == 3 ? 1 : WV;
+            auto* kernel = adj_few_tiles(c) ? k_g2p_adj<T, D, MAT, FL, WF> : k_g2p_adj<T, D, MAT, FL, WV>;
+            kernel<<<tile_wgs(c, kAdjBlock<D>), kAdjBlock<D>, 0, st>>>(g, P, rb.meta, rb.active, rb.perm, st_in, aout, (const T*)rb.gv,
+                                                                      FL ? (const T*)rb.gvo : nullptr, (T*)c->part_grid, (T*)c->mid);
+        };
+        if (flip) g2p_adj(std::true_type{});
+        else g2p_adj(std::false_type{});
         prof_mark(c, MPM_PROF_G2P_ADJ);
         double* amu = c->floor_mu ? c->amu : nullptr;
         NodesAdj2<T> nd{};
