@@ -57,6 +57,7 @@ constexpr int kSortCap = 1024;   // particles per tile sorted in LDS (larger: in
 template <bool FL> constexpr int kP2GBlock = FL ? 256 : 128;
 // threads of a G2P workgroup (3-D binary64: smaller groups, measured faster)
 template <class T, int D> constexpr int kG2PBlock = sizeof(T) == 8 && D == 3 ? 128 : 256;
+template <class T> constexpr int kG2PNarrow2 = sizeof(T) == 8 ? 128 : 256;   // 2-D, see kSortNarrow2
 // G2P loads the next tile's node block while it works on the current one
 // (binary64: measured faster; binary32: slower)
 template <class T> constexpr bool kG2PPrefetch = sizeof(T) == 8;
@@ -1192,9 +1193,15 @@ __global__ __launch_bounds__((kP2GBlock<FL>)) __attribute__((amdgpu_waves_per_eu
 // ---------------------------------------------------------------------------
 
 // Threads per tile where tiles are many and waves, not latency, are short
-// (524,288 particles, binary64: 256 threads 74.7 us a step, 128 68.8, 64 68.7;
-// 131,072: 37.8, 36.1, 38.6).
+// (kSortMany2: binary64, 131,072 particles, 256 threads 37.8 us a step, 128 36.1,
+// 64 38.6), and fewer still in binary64 past kNarrow2 particles, here and in G2P
+// (kG2PNarrow2): the registers leave two to three waves per SIMD, and those of
+// one tile wait for each other.  A step of fluid, sand and sand with FLIP, wide
+// and narrow: 122,500 particles 32 and 40, 40 and 52, 43 and 57 us; 494,900 67 and
+// 59, 83 and 77, 91 and 84; 3.96 M 366 and 317, 476 and 421, 546 and 472.
 constexpr int kSortMany2 = 128;
+template <class T> constexpr int kSortNarrow2 = sizeof(T) == 8 ? 64 : kSortMany2;
+constexpr long long kNarrow2 = 262144;
 
 // Tile of a workgroup when there is one per tile: a contiguous chunk of tiles
 // on each XCD (workgroup b runs on XCD b % 8).  -1 past the end.
@@ -1397,7 +1404,7 @@ __global__ __launch_bounds__(NT) void k_sort_p2g2(Geo g, Phys<T> P, Ranges rg, i
             }
         tile_sort_finish<NT>(ts, in_lds, at.cnt, perm + at.off, tmp + at.off);
         const int* sorted = in_lds ? ts.sorted : (perm + at.off);
-        if (rg.tile_perm && tid < at.cnt) rg.tile_perm[at.tile * kTileRow + tid] = sorted[tid];   // NT = a row
+        if (NT == kTileRow && rg.tile_perm && tid < at.cnt) rg.tile_perm[at.tile * kTileRow + tid] = sorted[tid];
         int tc[3];
         tile_coords(g, at.tile, tc);
         // opaque to the compiler for this tile, so that what is derived from the
@@ -1741,9 +1748,9 @@ template <class T>
 struct Nodes2 {
     const T* part;          // partial block of each tile (indexed by tile)
     const int* tile_slot;
-    const int2* range;      // one workgroup per tile where given, else over the active list
-    const int* tile_perm;   // with range: the first kTileRow entries of each tile's perm
-    int* tile_key;          // with range: the same of the new keys
+    const int2* range;      // one workgroup per tile: each tile's particles,
+    const int* tile_perm;   // the first kTileRow entries of its perm
+    int* tile_key;          // and of the new keys
     T *gv, *gmass, *gvt, *gvo;
 };
 
@@ -1824,7 +1831,7 @@ __device__ __forceinline__ void node_block2(const Geo& g, const Phys<T>& P, cons
         if constexpr (FL) {
             const T vo = m > T(0) ? sum[1 + D + a] / m : T(0);
             s_vo[a][tid] = vo;
-            if (keep) nd.gvo[a * g.NN + node] = vo;
+            if (keep && nd.gvo) nd.gvo[a * g.NN + node] = vo;
         }
     }
     if (keep && P.keep_grid) nd.gmass[node] = m;
@@ -1834,8 +1841,10 @@ __device__ __forceinline__ void node_block2(const Geo& g, const Phys<T>& P, cons
 // APIC C = (4/h^2) sum phi v_i (x_i - x_p)^T, TPIC C = the velocity gradient,
 // PIC and FLIP C = 0; FLIP (FL) also gathers the grid velocity before the
 // update, gvo, and blends: v' = sum phi v_i + alpha (v_p - sum phi v_i^n).
-template <class T, int D, int MAT, int XF>
-__global__ __launch_bounds__((kG2PBlock<T, D>)) void k_g2p(Geo g, Phys<T> P, const int* __restrict__ meta,
+// BYTILE (2-D grids of few tiles): one workgroup per tile, else over the active
+// list.
+template <class T, int D, int MAT, int XF, bool BYTILE, int NT = kG2PBlock<T, D>>
+__global__ __launch_bounds__(NT) void k_g2p(Geo g, Phys<T> P, const int* __restrict__ meta,
                                                 const ActiveTile* __restrict__ active, const int* __restrict__ perm,
                                                 PView<T> cur, PView<T> nxt, const T* __restrict__ gv,
                                                 const T* __restrict__ gvo,
@@ -1845,12 +1854,12 @@ __global__ __launch_bounds__((kG2PBlock<T, D>)) void k_g2p(Geo g, Phys<T> P, con
 {
     constexpr int TE = TileShape<D>::TE, BE = TileShape<D>::BE, NB = TileShape<D>::NB;
     constexpr int NS = D * (D + 1) / 2;
-    constexpr int NPT = (NB + kG2PBlock<T, D> - 1) / kG2PBlock<T, D>;   // block nodes per thread
+    constexpr int NPT = (NB + NT - 1) / NT;   // block nodes per thread
     constexpr bool FL = XF == XF_FLIP;
     __shared__ T s_v[D][NB];
     __shared__ T s_vo[FL ? D : 1][FL ? NB : 1];
-    const bool by_tile = D == 2 && nd.range;
-    const int n_active = by_tile ? 0 : meta[0];
+    static_assert(!BYTILE || (D == 2 && NT == kTileRow), "a thread holds one entry of its tile's row");
+    const int n_active = BYTILE ? 0 : meta[0];
     const int tid = threadIdx.x;
     const long long cap = cur.cap;
     // With kG2PPrefetch, the next tile's node velocities are loaded into
@@ -1858,11 +1867,11 @@ __global__ __launch_bounds__((kG2PBlock<T, D>)) void k_g2p(Geo g, Phys<T> P, con
     // active-list entry one tile earlier still); otherwise each tile loads its
     // own block at its top.
     constexpr bool PF = kG2PPrefetch<T> && !FL && D == 3;
-    int e = __builtin_amdgcn_readfirstlane(by_tile ? tile_of_block(g.ntiles) : tile_entry(0, n_active));
+    int e = __builtin_amdgcn_readfirstlane(BYTILE ? tile_of_block(g.ntiles) : tile_entry(0, n_active));
     if (e < 0) return;
     ActiveTile at;
     int j_row = 0;
-    if (by_tile) {
+    if constexpr (BYTILE) {
         const int2 r = nd.range[e];
         j_row = nd.tile_perm[e * kTileRow + tid];
         at.tile = e;
@@ -1873,8 +1882,8 @@ __global__ __launch_bounds__((kG2PBlock<T, D>)) void k_g2p(Geo g, Phys<T> P, con
         at = active[e];
     }
     T pre[D][NPT];
-    if (PF) g2p_block_load<T, D, NPT, kG2PBlock<T, D>>(g, gv, at.tile, tid, pre);
-    int en = by_tile ? -1 : __builtin_amdgcn_readfirstlane(tile_entry(1, n_active));
+    if (PF) g2p_block_load<T, D, NPT, NT>(g, gv, at.tile, tid, pre);
+    int en = BYTILE ? -1 : __builtin_amdgcn_readfirstlane(tile_entry(1, n_active));
     int next_tile = (PF && en >= 0) ? active[en].tile : 0;
     for (int it = 0; e >= 0; ++it) {
         // 2-D: a thread's first particle is on its way while the nodes are formed
@@ -1883,7 +1892,7 @@ __global__ __launch_bounds__((kG2PBlock<T, D>)) void k_g2p(Geo g, Phys<T> P, con
         T x_first[D], g_first[NG];
         if constexpr (D == 2) {
             if (tid < at.cnt) {
-                j_first = by_tile ? j_row : ld_once(&perm[at.off + tid]);
+                j_first = BYTILE ? j_row : ld_once(&perm[at.off + tid]);
 #pragma unroll
                 for (int a = 0; a < D; ++a) x_first[a] = ld_once(&cur.x[a * cap + j_first]);
 #pragma unroll
@@ -1892,13 +1901,13 @@ __global__ __launch_bounds__((kG2PBlock<T, D>)) void k_g2p(Geo g, Phys<T> P, con
             }
             node_block2<T, FL>(g, P, nd, at.tile, tid, s_v, s_vo);
         }
-        if (!PF && D == 3) g2p_block_load<T, D, NPT, kG2PBlock<T, D>>(g, gv, at.tile, tid, pre);
+        if (!PF && D == 3) g2p_block_load<T, D, NPT, NT>(g, gv, at.tile, tid, pre);
         if constexpr (FL && D == 3) {
             T preo[D][NPT];
-            g2p_block_load<T, D, NPT, kG2PBlock<T, D>>(g, gvo, at.tile, tid, preo);
+            g2p_block_load<T, D, NPT, NT>(g, gvo, at.tile, tid, preo);
 #pragma unroll
             for (int p = 0; p < NPT; ++p) {
-                const int i = tid + p * kG2PBlock<T, D>;
+                const int i = tid + p * NT;
                 if (i < NB)
 #pragma unroll
                     for (int a = 0; a < D; ++a) s_vo[a][i] = preo[a][p];
@@ -1907,7 +1916,7 @@ __global__ __launch_bounds__((kG2PBlock<T, D>)) void k_g2p(Geo g, Phys<T> P, con
         if constexpr (D == 3)
 #pragma unroll
         for (int p = 0; p < NPT; ++p) {
-            const int i = tid + p * kG2PBlock<T, D>;
+            const int i = tid + p * NT;
             if (i < NB)
 #pragma unroll
                 for (int a = 0; a < D; ++a) s_v[a][i] = pre[a][p];
@@ -1915,15 +1924,15 @@ __global__ __launch_bounds__((kG2PBlock<T, D>)) void k_g2p(Geo g, Phys<T> P, con
         __syncthreads();
         int enn = -1, next2_tile = 0;
         if (!PF) {
-            enn = by_tile ? -1 : __builtin_amdgcn_readfirstlane(tile_entry(it + 2, n_active));
+            enn = BYTILE ? -1 : __builtin_amdgcn_readfirstlane(tile_entry(it + 2, n_active));
         } else if (en >= 0) {
-            g2p_block_load<T, D, NPT, kG2PBlock<T, D>>(g, gv, next_tile, tid, pre);
+            g2p_block_load<T, D, NPT, NT>(g, gv, next_tile, tid, pre);
             enn = __builtin_amdgcn_readfirstlane(tile_entry(it + 2, n_active));
             if (enn >= 0) next2_tile = active[enn].tile;
         }
         int tc[3];
         tile_coords(g, at.tile, tc);
-        for (int k0 = 0; k0 < at.cnt; k0 += kG2PBlock<T, D>) {
+        for (int k0 = 0; k0 < at.cnt; k0 += NT) {
             int k = k0 + tid;
             bool valid = k < at.cnt;
             int newkey = 0;
@@ -2051,9 +2060,9 @@ __global__ __launch_bounds__((kG2PBlock<T, D>)) void k_g2p(Geo g, Phys<T> P, con
                 }
                 newkey = cell_key<T, D>(g, xn, P.inv);
                 key_out[s] = newkey;
-                if constexpr (D == 2)
-                    if (by_tile && k < kTileRow) nd.tile_key[at.tile * kTileRow + k] = newkey;
-                if ((D == 3 || by_tile) && (newkey >> 6) != at.tile) {
+                if constexpr (BYTILE)
+                    if (k < kTileRow) nd.tile_key[at.tile * kTileRow + k] = newkey;
+                if ((D == 3 || BYTILE) && (newkey >> 6) != at.tile) {
                     // into another tile: a neighbouring one is told where from
                     // (2-D: it looks at all its neighbours)
                     int nt[3];
@@ -2447,7 +2456,8 @@ struct Solver {
     };
     static StepBufs ctx_bufs(mpm_ctx* c)
     {
-        return {c->perm, c->tile_slot, c->active, c->meta, (T*)c->gv, (T*)c->gmass, nullptr, (T*)c->gvo};
+        // in 2-D G2P forms the velocity before the update itself: only the reverse sweep reads it
+        return {c->perm, c->tile_slot, c->active, c->meta, (T*)c->gv, (T*)c->gmass, nullptr, D == 2 ? nullptr : (T*)c->gvo};
     }
 
     // One step from state view cur into state view nxt with the transfer XF
@@ -2497,7 +2507,7 @@ struct Solver {
                                                   b.gv, b.gmass, b.gvt, b.gvo);
         prof_mark(c, MPM_PROF_GRID);
         if (advance) {
-            k_g2p<T, D, MAT, XF><<<tile_wgs(c, kG2PBlock<T, D>), kG2PBlock<T, D>, 0, st>>>(g, P, b.meta, b.active, b.perm, cur, nxt, (const T*)b.gv,
+            k_g2p<T, D, MAT, XF, false><<<tile_wgs(c, kG2PBlock<T, D>), kG2PBlock<T, D>, 0, st>>>(g, P, b.meta, b.active, b.perm, cur, nxt, (const T*)b.gv,
                                                           (const T*)b.gvo, c->key, count, c->status, b.eps_in, b.eps_out, Nodes2<T>{}, c->moved, r.far);
             prof_mark(c, MPM_PROF_G2P);
         }
@@ -2549,7 +2559,7 @@ struct Solver {
         constexpr int PM = mat_iso_stress(MAT) ? MAT_FLUID : MAT_SAND;
         hipStream_t st = c->stream;
         const Geo& g = c->geo;
-        const bool small = g.ntiles <= kSmallTiles;
+        const bool small = g.ntiles <= kSmallTiles, narrow = sizeof(T) == 8 && c->N > kNarrow2;
         const int o = c->turn, n = small ? 1 - o : o;
         const unsigned wgs = small ? (unsigned)((g.ntiles + 7) / 8 * 8) : (unsigned)kTileWGs;
         const Ranges r{c->count[o], c->count[n], c->range[o], c->range[n], nullptr, {c->far_head, c->far_next}, c->key, c->tile_key,
@@ -2564,14 +2574,22 @@ struct Solver {
             if (small)
                 k_sort_p2g2<T, PM, FL, false, 256><<<wgs, 256, 0, st>>>(g, P, r, b.meta, b.active, b.tile_slot, c->tmp,
                                                                         c->tmpk, cur, b.perm, (T*)c->part_grid);
+            else if (narrow)
+                k_sort_p2g2<T, PM, FL, false, kSortNarrow2<T>><<<tile_wgs(c, kSortNarrow2<T>), kSortNarrow2<T>, 0, st>>>(
+                    g, P, r, b.meta, b.active, b.tile_slot, c->tmp, c->tmpk, cur, b.perm, (T*)c->part_grid);
             else
                 k_sort_p2g2<T, PM, FL, false, kSortMany2><<<tile_wgs(c, kSortMany2), kSortMany2, 0, st>>>(
                     g, P, r, b.meta, b.active, b.tile_slot, c->tmp, c->tmpk, cur, b.perm, (T*)c->part_grid);
         }
         prof_mark(c, MPM_PROF_P2G);
         const Nodes2<T> nd{(const T*)c->part_grid, b.tile_slot, small ? c->range[n] : nullptr, c->tile_perm, c->tile_key, b.gv, b.gmass, b.gvt, b.gvo};
-        k_g2p<T, D, MAT, XF><<<wgs, kG2PBlock<T, D>, 0, st>>>(g, P, b.meta, b.active, b.perm, cur, nxt, nullptr, nullptr, c->key,
-                                                              c->count[n], c->status, b.eps_in, b.eps_out, nd, nullptr, r.far);
+        auto g2p = [&](auto* kernel, unsigned grid, int block) {
+            kernel<<<grid, block, 0, st>>>(g, P, b.meta, b.active, b.perm, cur, nxt, nullptr, nullptr, c->key, c->count[n], c->status,
+                                           b.eps_in, b.eps_out, nd, nullptr, r.far);
+        };
+        if (small) g2p(k_g2p<T, D, MAT, XF, true>, wgs, kG2PBlock<T, D>);
+        else if (narrow) g2p(k_g2p<T, D, MAT, XF, false, kG2PNarrow2<T>>, tile_wgs(c, kG2PNarrow2<T>), kG2PNarrow2<T>);
+        else g2p(k_g2p<T, D, MAT, XF, false>, wgs, kG2PBlock<T, D>);
         prof_mark(c, MPM_PROF_G2P);
         c->turn = n;
         c->ranges_known = small;
