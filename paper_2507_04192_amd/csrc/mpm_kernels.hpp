@@ -2362,8 +2362,12 @@ inline unsigned tile_wgs(const mpm_ctx* c, int block)
 // that the grid update and G2P need: the step 265.4 and 263.2 us at 334 MB, 328
 // and 314 at 396 MB (binary64), 484 and 463 at 667 MB.  With FLIP four waves
 // read them and plain is better at every size (617 and 616 us at 667 MB, 332
-// and 336 at 334 MB, 142 and 154 at 112 MB).
-inline bool p2g_hint(const mpm_ctx* c) { return (double)c->nsc * (double)c->cap * c->elem > 200e6; }
+// and 336 at 334 MB, 142 and 154 at 112 MB).  Where no step has laid out the
+// particles, those of a tile lie apart and share their lines with many other
+// tiles': hinted, each of them fetches the line again.  2.94 M particles from a
+// lattice, first step, P2G hinted and plain: sand binary32 977 and 573 us, binary64
+// 1256 and 699, fluid binary64 954 and 449.
+inline bool p2g_hint(const mpm_ctx* c, bool laid_out) { return laid_out && (double)c->nsc * (double)c->cap * c->elem > 200e6; }
 
 template <class T, int D>
 struct Solver {
@@ -2489,14 +2493,15 @@ struct Solver {
         const Ranges r{count, nullptr, c->range[o], c->range[n], c->moved, {c->far_head, c->far_next}, c->key, nullptr, nullptr, (long long)c->N};
         scan_tiles(c, nsb, count, b, c->range[n], nullptr);
         const unsigned swgs = tile_wgs(c, kSortBlock);
-        if (know_ranges(c, seq) && c->N < (1ll << 30)) {   // key positions plus a batch stay in int32
+        const bool gather = know_ranges(c, seq) && c->N < (1ll << 30);   // key positions plus a batch stay in int32
+        if (gather) {
             k_sort_gather<0><<<swgs, kSortBlock, 0, st>>>(g, r, b.meta, c->meta + kHaloSum, b.active, c->tmp, c->tmpk, b.perm, c->cell_cnt);
         } else {
             bucket(c, count);
             k_sort<0><<<swgs, kSortBlock, 0, st>>>(r, b.meta, c->meta + kHaloSum, b.active, c->tmp, c->tmpk, b.perm, c->cell_cnt);
         }
         prof_mark(c, MPM_PROF_BUCKET);
-        if (!FL && p2g_hint(c))
+        if (!FL && p2g_hint(c, gather))
             k_p2g<T, D, PM, FL, !FL><<<tile_wgs(c, kP2GBlock<FL>), kP2GBlock<FL>, 0, st>>>(g, P, b.meta, b.active, c->cell_cnt,
                                                                                         cur, b.perm, (T*)c->part_grid);
         else

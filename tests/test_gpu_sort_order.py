@@ -85,3 +85,26 @@ def test_particles_from_far_away_are_in_order(dim, centre, each):
         assert torch.equal(perm, b.mpm_read_sort()[0]), k
     for s in (a, b):
         s.close()
+
+
+def test_large_state_read_with_and_without_the_hint():
+    """A state past 200 MB: its first step, and those after new keys, read the
+    particles as ordinary loads, the others with the non-temporal hint."""
+    import torch
+    from paper_2507_04192_amd.native import Solver
+    cfg = _config(3, (64, 60, 60)).replace(material=W.SAND, youngs=1e5)
+    n = 1_700_000          # 30 binary32 scalars each: 204 MB
+    rng = np.random.default_rng(3)
+    x = rng.uniform(0.0, 0.6, size=(3, n))
+    v = rng.normal(0.0, 1.0, size=(3, n))
+    a, b = (Solver(cfg, "f32", capacity=n) for _ in range(2))
+    for s in (a, b):
+        s.mpm_init_particles(x, v)
+    for k in range(3):
+        a.mpm_step(1)
+        b.mpm_write_state("x", b.mpm_read_state("x"))
+        b.mpm_step(1)
+        for f in ("x", "v", "C", "stress", "pid"):
+            assert torch.equal(a.mpm_read_state(f), b.mpm_read_state(f)), (k, f)
+    for s in (a, b):
+        s.close()
