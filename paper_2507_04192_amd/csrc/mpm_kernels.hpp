@@ -2246,13 +2246,23 @@ __global__ void k_read_grid(Geo g, const T* __restrict__ src, int ncomp, const i
 // Host side
 // ---------------------------------------------------------------------------
 
-// Values (particles times components) from which a read in pid order gathers.
-// Below, the second launch costs more than the scattered lines, which then
-// stay in cache: lattice order, 9 components, scatter against gather 6.8 and
-// 10.2 us at 110,592 particles, 10.9 and 10.9 at 262,144, 34.6 and 22.1 at
-// 884,736; 3 components 12.9 and 14.1 at 884,736, 28.0 and 26.3 at 2,097,152
-// (binary32; binary64 crosses at the same sizes).
-constexpr long long kGatherMin = 2500000;
+// Whether a read in pid order gathers (two launches), or scatters the
+// components of each slot.  3-D matrices gather from 2.5 M values on: below, the
+// second launch costs more than the scattered lines, which then stay in cache
+// (lattice order, 9 components, scatter and gather 6.8 and 10.2 us at 110,592
+// particles, 10.9 and 10.9 at 262,144, 161 and 115 at 2,935,296).  3-D vectors
+// are scattered as fast while they fit the cache, and again far past it: binary32
+// 45.9 and 49.9 us at 35 MB, 77 and 84 at 64 MB, 329 and 235 at 129 MB; binary64
+// 20.3 and 21.8 at 20 MB, 37.6 and 36.6 at 42 MB, 59 and 57 at 70 MB, 205 and 145 at
+// 127 MB, 310 and 323 at 258 MB.  In 2-D a
+// tile's rows are eight cells long and the scatter is the faster at every size
+// (binary32, 2.5 M particles, vectors 18.6 and 26.3 us, matrices 31.2 and 39.1;
+// 6.0 M binary64, 56 and 60, 152 and 156).
+inline bool read_gathers(int dim, long long N, int ncomp, int elem)
+{
+    const long long values = N * ncomp, bytes = values * elem;
+    return dim == 3 && (ncomp == 9 ? values >= 2500000 : ncomp == 3 && bytes > (elem == 8 ? 40000000 : 100000000) && bytes < 200000000);
+}
 
 inline unsigned nblocks(long long n) { return (unsigned)((n + kBlock - 1) / kBlock); }
 
@@ -2692,7 +2702,7 @@ struct Solver {
         int ncomp, conv;
         int rc = field_desc(c, field, &src, &ncomp, &conv);
         if (rc) return rc;
-        if (N > 0 && order == MPM_ORDER_PID && ncomp > 1 && N * ncomp >= kGatherMin) {
+        if (order == MPM_ORDER_PID && read_gathers(D, N, ncomp, (int)sizeof(T))) {
             k_inverse_pid<0><<<nblocks(N), kBlock, 0, st>>>(s.pid, N, c->inv);
             k_gather_field<T, D><<<dim3((nblocks(N) + 8 * kGatherPer - 1) / (8 * kGatherPer) * 8, ncomp), kBlock, 0, st>>>(src, c->cap, c->inv, N, conv,
                                                                                           (T*)dst);
