@@ -364,11 +364,11 @@ int mpm_extract(mpm_ctx* ctx, void* lag_q, void* eul_q);
  * class, the summed event time in milliseconds and the number of launches
  * since the last read, then resets.  Arrays hold MPM_PROF_N entries (host
  * memory).  In the backward sweep the recomputed forward kernels count in
- * their own classes (the key pass of a recomputed step counts as SCAN), the
- * reverse kernels in the *_ADJ classes.  BUCKET is the 3-D step's sort.  A 2-D
- * step of up to 2048 tiles sorts in P2G and updates the grid in G2P (its reverse
- * in P2G_ADJ), so SCAN and BUCKET appear only where its keys are new, and GRID
- * and GRID_ADJ never. */
+ * their own classes (the key pass at the start of a recomputed segment counts
+ * as SCAN), the reverse kernels in the *_ADJ classes.  BUCKET is the 3-D step's
+ * sort, in 2-D the scatter before it.  A 2-D step sorts in P2G and updates the
+ * grid in G2P (its reverse in P2G_ADJ), so GRID and GRID_ADJ never appear, and
+ * up to 2048 tiles SCAN and BUCKET only where its keys are new. */
 enum { MPM_PROF_SCAN = 0, MPM_PROF_BUCKET = 1, MPM_PROF_P2G = 2, MPM_PROF_GRID = 3, MPM_PROF_G2P = 4,
        MPM_PROF_G2P_ADJ = 5, MPM_PROF_GRID_ADJ = 6, MPM_PROF_P2G_ADJ = 7, MPM_PROF_N = 8 };
 int mpm_profile_enable(mpm_ctx* ctx, int on);

@@ -1162,7 +1162,9 @@ struct Adjoint {
             const bool on_tape = seg >= first;
             const int q = on_tape ? seg - first : 0;
             if (!on_tape) {
+                prof_mark(c, -1);
                 S::new_keys(c, ckpt(c, seg));
+                prof_mark(c, MPM_PROF_SCAN);
                 // a segment's last step ends at the next checkpoint: only its
                 // sort and grid are needed (but the rollout's end has none)
                 for (int t = t0; t < t1; ++t)
