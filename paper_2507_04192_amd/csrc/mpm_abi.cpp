@@ -135,7 +135,7 @@ Geo make_geo(const mpm_config& c)
 }
 
 struct Layout {
-    size_t st[2], pid[2], eps[2], key, perm, tmp, tmpk, count[2], range[2], moved, far_head, far_next, tile_perm, tile_key, tile_off, tile_slot, active, cell_cnt, part, meta, status;
+    size_t st[2], pid[2], eps[2], key, perm, tmp, tmpk, count[2], range[2], moved, tile_perm, tile_key, tile_off, tile_slot, active, cell_cnt, part, meta, status;
     size_t part_grid, gv, gmass, gvo;
     size_t inv, loss, box_sum, box_cnt, box_coef;
     size_t ckpt, ckpt_pid, tape, tape_pid, adj[2], mid, gtape, amu;
@@ -175,10 +175,8 @@ Layout make_layout(const mpm_config& c, const Geo& g, int64_t cap, int tape_step
     // steps alternate between two sets of the tiles' ranges, in 2-D of counts too
     for (int b = 0; b < 2; ++b) L.count[b] = (b == 0 || c.dim == 2) ? take((size_t)g.ntiles * 4) : 0;
     for (int b = 0; b < 2; ++b) L.range[b] = take((size_t)g.ntiles * 8);
-    L.moved = c.dim == 3 ? take((size_t)g.ntiles * 4) : 0;
     const bool rows = c.dim == 2 && g.ntiles <= kSmallTiles;
-    L.far_head = c.dim == 3 || rows ? take((size_t)g.ntiles * 4) : 0;
-    L.far_next = c.dim == 3 || rows ? take(ucap * 4) : 0;
+    L.moved = c.dim == 3 || rows ? take((2 * (size_t)g.ntiles + ucap) * 4) : 0;
     L.tile_perm = rows ? take((size_t)g.ntiles * kTileRow * 4) : 0;
     L.tile_key = rows ? take((size_t)g.ntiles * kTileRow * 4) : 0;
     L.tile_off = take((size_t)g.ntiles * 4);
@@ -354,9 +352,7 @@ int mpm_bind_workspace(mpm_ctx* c, void* dev_ptr, size_t bytes, int64_t n_partic
     const bool rows = c->cfg.dim == 2 && c->geo.ntiles <= kSmallTiles;
     c->tile_perm = rows ? (int32_t*)(b + L.tile_perm) : nullptr;
     c->tile_key = rows ? (int32_t*)(b + L.tile_key) : nullptr;
-    c->moved = (int32_t*)(b + L.moved);
-    c->far_head = c->cfg.dim == 3 || rows ? (int32_t*)(b + L.far_head) : nullptr;
-    c->far_next = c->cfg.dim == 3 || rows ? (int32_t*)(b + L.far_next) : nullptr;
+    c->moved = c->cfg.dim == 3 || rows ? (int32_t*)(b + L.moved) : nullptr;
     c->turn = 0;
     c->ranges_known = false;
     c->tile_off = (int32_t*)(b + L.tile_off);

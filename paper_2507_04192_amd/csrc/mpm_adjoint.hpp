@@ -182,11 +182,12 @@ __device__ __forceinline__ T axis_dx(const T dwd[3], T inv2, T p, T q, const T R
 // written after the first in the tile's partial block), its weights pass
 // an adjoint to the position, and alpha times the adjoint of v' goes to mid
 // as the direct adjoint of v_p.
-// What bounds it: binary32 the LDS atomics (81 per particle) and the arithmetic,
-// binary64 the registers.  3-D dam-break, 1,843,200 particles, by lines along x ->
-// by axis sums: binary32 153 -> 133 us, binary64 333 -> 221 at two waves per SIMD
-// (sand would spill: 114 -> 190 us on the half cylinder, where by axis sums alone
-// it went 125 -> 114).
+// What bounds it: the arithmetic, at the waves that its registers leave.  The LDS
+// atomics (81 per particle) cost nothing measurable: with plain adds in their
+// place the dam-break takes 137 us (136) in binary32 and 225 (215) in binary64.
+// 3-D dam-break, 1,843,200 particles, by lines along x -> by axis sums: binary32
+// 153 -> 133 us, binary64 333 -> 221 at two waves per SIMD (sand would spill: 114 ->
+// 190 us on the half cylinder, where by axis sums alone it went 125 -> 114).
 // WV: waves per SIMD asked for, see kAdjWaves.
 template <class T, int D, int MAT, bool FL, int WV>
 __global__ __launch_bounds__((kAdjBlock<D>)) __attribute__((amdgpu_waves_per_eu(WV))) void k_g2p_adj(Geo g, Phys<T> P, const int* __restrict__ meta,
@@ -199,8 +200,8 @@ __global__ __launch_bounds__((kAdjBlock<D>)) __attribute__((amdgpu_waves_per_eu(
     constexpr int NS = D * (D + 1) / 2;
     constexpr int NVA = FL ? 2 * D + 1 : D + 1;   // partial block values per node
     using ML = MidLayout<D>;
-    // binary32: the node adjoints' LDS atomics are a third faster on the padded
-    // block (3-D dam-break 147 -> 134 us); binary64 221 -> 227
+    // binary32 is faster on the padded block (3-D dam-break 147 -> 134 us);
+    // binary64 is not (221 -> 227)
     using B = std::conditional_t<D == 3 && sizeof(T) == 4, PaddedBlock, DenseBlock<D>>;
     constexpr int LY = B::LY, LZ = B::LZ, LN = B::LN;
     constexpr int stride[3] = {1, LY, LZ};

@@ -1,23 +1,27 @@
 // Forward MPM step kernels for gfx950 and their host launchers.
 //
-// One step (Sec. 2.2, update-stress-last):
-//   1. scan_reduce / scan_down  tile histogram -> tile offsets, active tiles
-//   2. bucket                   particles scattered into their tile's range
-//   3. p2g                      one tile per workgroup: cell-level stable sort
-//                               in LDS, then P2G (eq:update_m, momentum with the
-//                               APIC affine term of App. B, internal force from
-//                               the stress cache) into the tile's LDS node
-//                               block, written out as the tile's partial block
-//   4. grid                     sums the partial blocks covering each node in
-//                               a fixed order; v = P/m + dt g, walls (Sec. 5.3
-//                               friction law).  No floating-point atomics: the
-//                               step is deterministic.
-//   5. g2p                      per active tile: LDS node block, velocity,
-//                               APIC C, velocity gradient, position, then the
-//                               constitutive update; writes the state in the
-//                               new sorted order and counts the next keys
-// In 2-D, 1 to 3 are one kernel (sort_p2g2) wherever the previous step's
-// layout is known and the grid is small, and 4 is done by g2p.
+// One step (Sec. 2.2, update-stress-last), 3-D:
+//   1. scan_once       tile counts -> tile offsets, active tiles; beside it the
+//                      halo tiles, empty ones that particles' nodes reach (past
+//                      131,072 tiles scan_reduce and scan_down)
+//   2. sort_gather     each tile's particles found where the last step left them,
+//                      ranked by cell and previous slot: the permutation and the
+//                      cells' counts.  Where no step has laid out the state:
+//                      bucket (scatter by tile) and sort
+//   3. p2g             one tile per workgroup, lane = cell: P2G (eq:update_m,
+//                      momentum with the APIC affine term of App. B, internal
+//                      force from the stress cache) summed in registers, written
+//                      out as the tile's partial block
+//   4. grid            over active and halo tiles: sums the partial blocks
+//                      covering each node in a fixed order; v = P/m + dt g, walls
+//                      (Sec. 5.3 friction law).  No floating-point atomics: the
+//                      step is deterministic
+//   5. g2p             per active tile: LDS node block, velocity, APIC C, velocity
+//                      gradient, position, then the constitutive update; writes
+//                      the state in the new sorted order, counts the next keys
+//                      and marks where particles change their tile
+// In 2-D, 2 and 3 are one kernel (sort_p2g2), which up to 2048 tiles does 1 as
+// well where a step has laid out the state, and 4 is done by g2p.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -204,6 +208,24 @@ __device__ __forceinline__ void halo_take(int* __restrict__ n, int* __restrict__
     *n = 0;
 }
 
+// Particles that left their tile's neighbourhood in a step (beyond the CFL
+// limit), which the next step's sort does not meet in the ranges around their new
+// tile: chained per new tile by G2P, in no order, through their slots.  One array:
+// the marks of the neighbours, `moved`, each tile's first slot or -1, and per slot
+// the next.
+struct Far {
+    int* moved;
+    int ntiles;
+    __device__ __forceinline__ int& head(int tile) const { return moved[(long long)ntiles + tile]; }
+    __device__ __forceinline__ int& next(int slot) const { return moved[2ll * ntiles + slot]; }
+    __device__ __forceinline__ void push(int tile, int slot) const { next(slot) = atomicExch(&head(tile), slot); }
+};
+constexpr int kFarBit = 1 << 27;   // of `moved` (3-D): the tile has such a chain
+// A tile of more particles than this goes through all keys instead of its chain,
+// which is a serial walk, and ranked by counting: at most 4096 tiles are.
+constexpr int kFarCrowd = 4096;
+__device__ __forceinline__ bool far_scans_all(int cnt, long long N) { return cnt > kFarCrowd && cnt > N / 4096; }
+
 // What the scan leaves for tile t with c particles from `off` on; slot: its
 // place in the active list.
 __device__ __forceinline__ void scan_put(int t, int c, int off, int& slot, int* __restrict__ tile_off,
@@ -364,7 +386,7 @@ __global__ __launch_bounds__(kBlock) void k_scan_down(const int* __restrict__ co
 }
 
 // Scatter every particle into its tile's range (order inside a tile is
-// arbitrary here; the P2G kernel sorts it).  Leaves count[] at zero.  A
+// arbitrary here; k_sort, in 2-D k_sort_p2g2, ranks them).  Leaves count[] at zero.  A
 // thread takes kBucketPer particles, kBlock apart, whose loads, range
 // reservations and stores are each issued together.
 constexpr int kBucketPer = 4;
@@ -438,12 +460,14 @@ __global__ __launch_bounds__(kBlock) void k_init(Geo g, Phys<T> P, const T* __re
 
 // The tiles' counts and the marks of the last step's moves to none.
 template <int Unused = 0>
-__global__ __launch_bounds__(kBlock) void k_clear_keys(int* __restrict__ count, int* __restrict__ moved, int* __restrict__ head, int ntiles)
+__global__ __launch_bounds__(kBlock) void k_clear_keys(int* __restrict__ count, Far far, int ntiles)
 {
     for (int t = blockIdx.x * kBlock + threadIdx.x; t < ntiles; t += gridDim.x * kBlock) {
         count[t] = 0;
-        if (moved) moved[t] = 0;
-        if (head) head[t] = -1;
+        if (far.moved) {
+            far.moved[t] = 0;
+            far.head(t) = -1;
+        }
     }
 }
 
@@ -754,28 +778,14 @@ __device__ __forceinline__ void tile_sort_finish(TileSort& s, bool in_lds, int c
     }
 }
 
-// Particles that left their tile's neighbourhood in a step (beyond the CFL
-// limit), which the next step's sort does not meet in the ranges around their new
-// tile: chained per new tile by G2P, in no order, through their slots.
-struct Far {
-    int* head;   // per tile: a slot, -1 none
-    int* next;   // per slot of a chained particle
-    __device__ __forceinline__ void push(int tile, int slot) const { next[slot] = atomicExch(&head[tile], slot); }
-};
-constexpr int kFarBit = 1 << 27;   // of `moved` (3-D): the tile has such a chain
-// A tile of more particles than this goes through all keys instead of its chain,
-// which is a serial walk, and ranked by counting: at most 4096 tiles are.
-constexpr int kFarCrowd = 4096;
-__device__ __forceinline__ bool far_scans_all(int cnt, long long N) { return cnt > kFarCrowd && cnt > N / 4096; }
-
 // The previous step's layout and this step's, for kernels that gather.
 struct Ranges {
     int* count;              // particles per tile, by the current keys
     int* count_next;         // 2-D: cleared for this step's G2P (3-D: count itself is)
     const int2* range;       // previous sort: first slot and number of each tile's particles
     int2* range_next;        // this sort
-    int* moved;              // 3-D: bit per neighbour that particles came from, kFarBit (cleared for this step's G2P)
-    Far far;                 // chains of the last step (left empty for this step's G2P)
+    int* moved;              // 3-D: bit per neighbour that particles came from, kFarBit (cleared for this step's G2P);
+                             // the chains of the last step behind it (see Far; left empty for this step's G2P)
     const int* key;
     const int* tile_key;     // 2-D: the first kTileRow keys of every tile's range, a row per tile
     int* tile_perm;          // 2-D: the same of perm (null: not kept)
@@ -809,16 +819,17 @@ constexpr int kOwnBatches = 8;   // batches of a tile's own range held in regist
 
 // One wave: takes a tile's chain and leaves its slots, ascending, in the end of
 // the tile's range of tmp; their number (0 also for a crowded tile).
-__device__ __forceinline__ int far_sorted(const Ranges& rg, const ActiveTile& at, int* __restrict__ tmp, int* __restrict__ scratch)
+__device__ __forceinline__ int far_sorted(const Far& far, long long N, const ActiveTile& at, int* __restrict__ tmp,
+                                          int* __restrict__ scratch)
 {
     const int lane = threadIdx.x & 63;
-    int j = __builtin_amdgcn_readfirstlane(rg.far.head[at.tile]), n = 0;
-    if (far_scans_all(at.cnt, rg.N)) j = -1;
+    int j = __builtin_amdgcn_readfirstlane(far.head(at.tile)), n = 0;
+    if (far_scans_all(at.cnt, N)) j = -1;
     for (; j >= 0 && n < at.cnt; ++n) {
         if (lane == 0) scratch[n] = j;
-        j = __builtin_amdgcn_readfirstlane(rg.far.next[j]);
+        j = __builtin_amdgcn_readfirstlane(far.next(j));
     }
-    if (lane == 0) rg.far.head[at.tile] = -1;
+    if (lane == 0) far.head(at.tile) = -1;
     __threadfence_block();
     for (int u = lane; u < n; u += 64) {
         const int f = scratch[u];
@@ -850,7 +861,7 @@ __global__ __launch_bounds__(kSortBlock) __attribute__((amdgpu_waves_per_eu(8)))
     for (int e = xcd * chunk + (int)(blockIdx.x / 8) * NW + w; e < end; e += per) {
         const ActiveTile at = active[e];
         const int2 own = rg.range[at.tile];
-        const unsigned from = (unsigned)rg.moved[at.tile];
+        const unsigned from = (unsigned)__builtin_amdgcn_readfirstlane(rg.moved[at.tile]);   // the wave's one tile
         int tc[3];
         tile_coords(g, at.tile, tc);
         // lane q: the range of neighbour q where particles came from
@@ -860,6 +871,7 @@ __global__ __launch_bounds__(kSortBlock) __attribute__((amdgpu_waves_per_eu(8)))
             if (lane < 27 && ((from >> lane) & 1) && tx >= 0 && ty >= 0 && tz >= 0 && tx < g.ntile[0] && ty < g.ntile[1] &&
                 tz < g.ntile[2])
                 nb = rg.range[(tz * g.ntile[1] + ty) * g.ntile[0] + tx];
+            if (lane == 13) nb = own;
         }
         int ck[kOwnBatches];   // keys of the own range, then cell | rank << 6, or -1
 #pragma unroll
@@ -907,7 +919,7 @@ __global__ __launch_bounds__(kSortBlock) __attribute__((amdgpu_waves_per_eu(8)))
         };
         // the far ones wait in the end of that range, which the list reaches
         // only after it has taken as many of them
-        const int n_far = from & kFarBit ? far_sorted(rg, at, tmp, perm + at.off) : 0;
+        const int n_far = from & kFarBit ? far_sorted(Far{rg.moved, g.ntiles}, rg.N, at, tmp, perm + at.off) : 0;
         int far_at = 0;
         auto far_before = [&](int slot) {
             while (far_at < n_far) {
@@ -919,30 +931,29 @@ __global__ __launch_bounds__(kSortBlock) __attribute__((amdgpu_waves_per_eu(8)))
             }
         };
         bool held = own.y <= kOwnBatches * 64;   // the own range's particles stay in ck
-        for (unsigned b = from & 0x1fffu; b; b &= b - 1) {
-            const int q = __ffs((int)b) - 1;
-            far_before(__shfl(nb.x, q));
-            list(__shfl(nb.x, q), __shfl(nb.y, q));
-        }
-        far_before(own.x);
-        if (held) {
+        bool all = false;
+        // the neighbours' ranges marked and, as 13, the own one
+        for (unsigned todo = (from & 0x7ffffffu) | 1u << 13;; todo = 1) {
+            for (; todo; todo &= todo - 1) {
+                const int q = __ffs((int)todo) - 1;
+                const int first = __shfl(nb.x, q), num = __shfl(nb.y, q);
+                if (n_far > far_at) far_before(first);
+                if (q == 13 && held) {
 #pragma unroll
-            for (int q = 0; q < kOwnBatches; ++q) ck[q] = count(ck[q]);
-        } else {
-            list(own.x, own.y);
-        }
-        for (unsigned b = from & 0x7ffc000u; b; b &= b - 1) {
-            const int q = __ffs((int)b) - 1;
-            far_before(__shfl(nb.x, q));
-            list(__shfl(nb.x, q), __shfl(nb.y, q));
-        }
-        far_before(0x7fffffff);
-        if (found != at.cnt) {   // a crowded tile whose chain was not taken
+                    for (int i = 0; i < kOwnBatches; ++i) ck[i] = count(ck[i]);
+                } else {
+                    list(first, num);
+                }
+            }
+            if (n_far > far_at) far_before(0x7fffffff);
+            if (found == at.cnt || all) break;
+            // a crowded tile whose chain was not taken: all keys
+            all = true;
             cnt[lane] = 0;
             wave_sync();
             found = listed = 0;
             held = false;
-            list(0, (int)rg.N);
+            nb = make_int2(0, (int)rg.N);
         }
         if (lane == 0) {
             rg.moved[at.tile] = 0;
@@ -980,7 +991,7 @@ __global__ __launch_bounds__(kSortBlock) __attribute__((amdgpu_waves_per_eu(8)))
 // The same from the bucketed entries of each tile, which come in no order: by
 // placement into the cells and counting, in LDS.
 template <int Unused = 0>
-__global__ __launch_bounds__(kSortBlock) void k_sort(Ranges rg, int* __restrict__ meta, int* __restrict__ n_halo,
+__global__ __launch_bounds__(kSortBlock) void k_sort(Far far, int* __restrict__ meta, int* __restrict__ n_halo,
                                                      const ActiveTile* __restrict__ active, int* __restrict__ tmp, const int* __restrict__ tmpk,
                                                      int* __restrict__ perm, int* __restrict__ cell_cnt)
 {
@@ -998,8 +1009,8 @@ __global__ __launch_bounds__(kSortBlock) void k_sort(Ranges rg, int* __restrict_
             s.cur[tid] = 0;
         }
         if (tid == 0) {   // what the last step marked is not used here
-            rg.moved[at.tile] = 0;
-            rg.far.head[at.tile] = -1;
+            far.moved[at.tile] = 0;
+            far.head(at.tile) = -1;
         }
         const bool in_lds = at.cnt <= kSortCap;
         // a tile that fits LDS keeps its entries in registers: one batch of loads
@@ -1307,7 +1318,7 @@ __global__ __launch_bounds__(NT) void k_sort_p2g2(Geo g, Phys<T> P, Ranges rg, i
             const int e = tile_entry(it, n_active);
             if (e < 0) break;
             at = active[e];
-            if (rg.far.head && tid == 0) rg.far.head[at.tile] = -1;   // not used here
+            if (rg.moved && tid == 0) Far{rg.moved, g.ntiles}.head(at.tile) = -1;   // not used here
             __syncthreads();
         }
         const bool in_lds = at.cnt <= kSortCap;
@@ -1358,17 +1369,18 @@ __global__ __launch_bounds__(NT) void k_sort_p2g2(Geo g, Phys<T> P, Ranges rg, i
             if (!GATHER || all || ts.found == at.cnt) break;
             if (w == 0) {
                 // some came from further away: along their chain, one by one
-                int j = __builtin_amdgcn_readfirstlane(rg.far.head[at.tile]), n = 0;
+                const Far far{rg.moved, g.ntiles};
+                int j = __builtin_amdgcn_readfirstlane(far.head(at.tile)), n = 0;
                 if (far_scans_all(at.cnt, rg.N)) j = -1;
                 for (; j >= 0 && n < at.cnt; ++n) {
                     if (lane == 0) {
                         tmp[at.off + n] = j;
                         atomicAdd(&ts.cnt[rg.key[j] & 63], 1);
                     }
-                    j = __builtin_amdgcn_readfirstlane(rg.far.next[j]);
+                    j = __builtin_amdgcn_readfirstlane(far.next(j));
                 }
                 if (lane == 0) {
-                    rg.far.head[at.tile] = -1;
+                    far.head(at.tile) = -1;
                     s_far = n;
                 }
                 wave_sync();
@@ -1755,10 +1767,10 @@ struct Nodes2 {
 };
 
 // Sum of NV values over the partial blocks (one per tile, stride NS values per
-// node) that cover node `tid` of a tile's block, in the order of node_blocks:
-// own tile first.  I: the node; returns its owner, the first active tile that
-// covers it.  Blocks are loaded before it is known which tiles are active: one
-// round trip.
+// node) that cover node `tid` of a tile's block, own tile first, then the tile
+// below along x, y and both.  I: the node; returns its owner, the first active
+// tile that covers it.  Blocks are loaded before it is known which tiles are
+// active: one round trip.
 template <class T, int NV, int NS>
 __device__ __forceinline__ int block_sum2(const Geo& g, const int* __restrict__ tile_slot, const T* __restrict__ part, int tile,
                                           int tid, int I[3], T sum[NV])
@@ -1850,7 +1862,7 @@ __global__ __launch_bounds__(NT) void k_g2p(Geo g, Phys<T> P, const int* __restr
                                                 const T* __restrict__ gvo,
                                                 int* __restrict__ key_out, int* __restrict__ count,
                                                 int* __restrict__ status, const T* __restrict__ eps_in,
-                                                T* __restrict__ eps_out, Nodes2<T> nd, int* __restrict__ moved, Far far)
+                                                T* __restrict__ eps_out, Nodes2<T> nd, int* __restrict__ moved)
 {
     constexpr int TE = TileShape<D>::TE, BE = TileShape<D>::BE, NB = TileShape<D>::NB;
     constexpr int NS = D * (D + 1) / 2;
@@ -1936,6 +1948,7 @@ __global__ __launch_bounds__(NT) void k_g2p(Geo g, Phys<T> P, const int* __restr
             int k = k0 + tid;
             bool valid = k < at.cnt;
             int newkey = 0;
+            bool far = false;   // beyond the neighbouring tiles
             if (valid) {
                 long long s = at.off + k;
                 const bool mine_first = D == 2 && k0 == 0;
@@ -2068,17 +2081,17 @@ __global__ __launch_bounds__(NT) void k_g2p(Geo g, Phys<T> P, const int* __restr
                     int nt[3];
                     tile_coords(g, newkey >> 6, nt);
                     const int dx = tc[0] - nt[0], dy = tc[1] - nt[1], dz = tc[2] - nt[2];
-                    if (abs(dx) <= 1 && abs(dy) <= 1 && abs(dz) <= 1) {
-                        if constexpr (D == 3) atomicOr(&moved[newkey >> 6], 1 << ((dz + 1) * 9 + (dy + 1) * 3 + dx + 1));
-                    } else {
-                        far.push(newkey >> 6, (int)s);
-                        if constexpr (D == 3) atomicOr(&moved[newkey >> 6], kFarBit);
-                    }
+                    far = abs(dx) > 1 || abs(dy) > 1 || abs(dz) > 1;
+                    if constexpr (D == 3)
+                        atomicOr(&moved[newkey >> 6], far ? kFarBit : 1 << ((dz + 1) * 9 + (dy + 1) * 3 + dx + 1));
                 }
             }
             int head, len, rank;
             wave_runs(valid ? (newkey >> 6) : -1, valid, head, len, rank);
             if (valid && rank == 0) atomicAdd(&count[newkey >> 6], len);
+            // here, past the particle: inside it the exchange cost registers, and
+            // G2P of the viscous fluid 75 us for 73
+            if (far) Far{moved, g.ntiles}.push(newkey >> 6, at.off + k);
         }
         __syncthreads();
         e = en;
@@ -2422,7 +2435,7 @@ struct Solver {
     static void clear_keys(mpm_ctx* c)
     {
         k_clear_keys<0><<<std::min<long long>(nblocks(c->geo.ntiles), 4096), kBlock, 0, c->stream>>>(
-            key_count(c), D == 3 ? c->moved : nullptr, c->far_head, c->geo.ntiles);
+            key_count(c), Far{c->moved, c->geo.ntiles}, c->geo.ntiles);
         c->ranges_known = false;
     }
 
@@ -2500,7 +2513,7 @@ struct Solver {
         } else {
         const int o = c->turn, n = 1 - o;
         int* count = c->count[0];
-        const Ranges r{count, nullptr, c->range[o], c->range[n], c->moved, {c->far_head, c->far_next}, c->key, nullptr, nullptr, (long long)c->N};
+        const Ranges r{count, nullptr, c->range[o], c->range[n], c->moved, c->key, nullptr, nullptr, (long long)c->N};
         scan_tiles(c, nsb, count, b, c->range[n], nullptr);
         const unsigned swgs = tile_wgs(c, kSortBlock);
         const bool gather = know_ranges(c, seq) && c->N < (1ll << 30);   // key positions plus a batch stay in int32
@@ -2508,7 +2521,7 @@ struct Solver {
             k_sort_gather<0><<<swgs, kSortBlock, 0, st>>>(g, r, b.meta, c->meta + kHaloSum, b.active, c->tmp, c->tmpk, b.perm, c->cell_cnt);
         } else {
             bucket(c, count);
-            k_sort<0><<<swgs, kSortBlock, 0, st>>>(r, b.meta, c->meta + kHaloSum, b.active, c->tmp, c->tmpk, b.perm, c->cell_cnt);
+            k_sort<0><<<swgs, kSortBlock, 0, st>>>(Far{c->moved, g.ntiles}, b.meta, c->meta + kHaloSum, b.active, c->tmp, c->tmpk, b.perm, c->cell_cnt);
         }
         prof_mark(c, MPM_PROF_BUCKET);
         if (!FL && p2g_hint(c, gather))
@@ -2523,7 +2536,7 @@ struct Solver {
         prof_mark(c, MPM_PROF_GRID);
         if (advance) {
             k_g2p<T, D, MAT, XF, false><<<tile_wgs(c, kG2PBlock<T, D>), kG2PBlock<T, D>, 0, st>>>(g, P, b.meta, b.active, b.perm, cur, nxt, (const T*)b.gv,
-                                                          (const T*)b.gvo, c->key, count, c->status, b.eps_in, b.eps_out, Nodes2<T>{}, c->moved, r.far);
+                                                          (const T*)b.gvo, c->key, count, c->status, b.eps_in, b.eps_out, Nodes2<T>{}, c->moved);
             prof_mark(c, MPM_PROF_G2P);
         }
         c->turn = n;
@@ -2577,7 +2590,7 @@ struct Solver {
         const bool small = g.ntiles <= kSmallTiles, narrow = sizeof(T) == 8 && c->N > kNarrow2;
         const int o = c->turn, n = small ? 1 - o : o;
         const unsigned wgs = small ? (unsigned)((g.ntiles + 7) / 8 * 8) : (unsigned)kTileWGs;
-        const Ranges r{c->count[o], c->count[n], c->range[o], c->range[n], nullptr, {c->far_head, c->far_next}, c->key, c->tile_key,
+        const Ranges r{c->count[o], c->count[n], c->range[o], c->range[n], c->moved, c->key, c->tile_key,
                           small ? c->tile_perm : nullptr, (long long)c->N};
         if (small && know_ranges(c, seq) && c->N < (1ll << 30)) {   // key positions plus a batch stay in int32
             k_sort_p2g2<T, PM, FL, true, 256><<<wgs, 256, 0, st>>>(g, P, r, b.meta, b.active, b.tile_slot, c->tmp, c->tmpk,
@@ -2600,7 +2613,7 @@ struct Solver {
         const Nodes2<T> nd{(const T*)c->part_grid, b.tile_slot, small ? c->range[n] : nullptr, c->tile_perm, c->tile_key, b.gv, b.gmass, b.gvt, b.gvo};
         auto g2p = [&](auto* kernel, unsigned grid, int block) {
             kernel<<<grid, block, 0, st>>>(g, P, b.meta, b.active, b.perm, cur, nxt, nullptr, nullptr, c->key, c->count[n], c->status,
-                                           b.eps_in, b.eps_out, nd, nullptr, r.far);
+                                           b.eps_in, b.eps_out, nd, c->moved);
         };
         if (small) g2p(k_g2p<T, D, MAT, XF, true>, wgs, kG2PBlock<T, D>);
         else if (narrow) g2p(k_g2p<T, D, MAT, XF, false, kG2PNarrow2<T>>, tile_wgs(c, kG2PNarrow2<T>), kG2PNarrow2<T>);

@@ -65,9 +65,8 @@ struct mpm_ctx {
     int32_t* tmpk = nullptr;       // key of each bucketed particle
     int32_t* count[2] = {nullptr, nullptr};  // particles per tile; 2-D steps alternate, 3-D uses the first
     int2* range[2] = {nullptr, nullptr};     // first slot and number of each tile's particles, by turn
-    int32_t* moved = nullptr;      // 3-D: per tile, the neighbours that particles came from in the last step
-    int32_t* far_head = nullptr;   // chains of those that came from further away (not 2-D of many tiles)
-    int32_t* far_next = nullptr;
+    int32_t* moved = nullptr;      // 3-D: per tile, the neighbours that particles came from in the last step;
+                                   // behind it the chains of those from further away (2-D of many tiles: none)
     int32_t* tile_perm = nullptr;  // 2-D, few tiles: row per tile of the first entries of perm
     int32_t* tile_key = nullptr;   // and of the keys after the step, else null
     int turn = 0;                  // buffer that describes the current state
@@ -78,7 +77,10 @@ struct mpm_ctx {
     mpm::ActiveTile* active = nullptr;
     int32_t* cell_cnt = nullptr;   // 3-D: particles per cell of each active tile
     int32_t* part = nullptr;
-    int32_t* meta = nullptr;       // [0] active tiles, [1] particles sorted
+    // [0] active tiles, [1] particles sorted; 3-D: [kHaloAt] halo tiles of the step,
+    // whose number gathers in [kHaloSum] of the context's own and is taken, and
+    // cleared, by the step's sort
+    int32_t* meta = nullptr;
     int32_t* status = nullptr;     // [0] flags, [1] smallest bad pid
     void* part_grid = nullptr;     // per active tile: P2G node block, mass + momentum
     void* gv = nullptr;            // nodal velocity after the grid update [dim]
