@@ -233,11 +233,12 @@ TRAFFIC_FILE = os.path.join(ROOT, "profiles", "hbm_traffic_cylinder.txt")
 
 def traffic_kernels(cls, elem):
     """The 3-D sand kernels behind a timed class (template arguments:
-    precision, dimension, material, then FLIP and the non-temporal hint for P2G
-    and the transfer for G2P)."""
-    t = "float" if elem == 4 else "double"
-    names = {"p2g": f"k_p2g<{t}, 3, 1, false, true>", "g2p": f"k_g2p<{t}, 3, 1, 0>",
-             "g2p_adj": f"k_g2p_adj<{t}, 3, 1, false>", "p2g_adj": f"k_p2g_adj<{t}, 3, 1, false>"}
+    precision, dimension, material, then FLIP and the non-temporal hint for P2G;
+    the transfer, 2-D's way through the tiles and the threads per tile for G2P;
+    FLIP, and the waves per SIMD of the reverse G2P)."""
+    t, block = ("float", 256) if elem == 4 else ("double", 128)
+    names = {"p2g": f"k_p2g<{t}, 3, 1, false, true>", "g2p": f"k_g2p<{t}, 3, 1, 0, false, {block}>",
+             "g2p_adj": f"k_g2p_adj<{t}, 3, 1, false, 1>", "p2g_adj": f"k_p2g_adj<{t}, 3, 1, false>"}
     return [names.get(cls, cls)]
 
 

@@ -810,10 +810,12 @@ struct Ranges {
 // such a step costs each particle a few trips to memory, too: with all of 2.65 M
 // particles moved 20 cells the step after takes 0.89 ms (0.26 without), where
 // every tile went through all keys 5.9, and more with every tile and particle.
-// Cylinder, 2,780,000 particles: 15 us, where the scatter took 13 and the sort,
-// by LDS placement inside P2G at its three waves per SIMD, about 25 of P2G's 94
-// (binary32; 19 in a kernel of its own).  It waits for its four dependent round
-// trips, one more for each two ranges marked.
+// Cylinder, 2,780,000 particles: 20 us between events, where the scatter took 13
+// and the sort, by LDS placement inside P2G at its three waves per SIMD, about 25
+// of P2G's 94 (binary32; 19 in a kernel of its own); 29 once the sand moves and
+// tiles hold more than 512.  A wave is one chain: four dependent trips to memory
+// and one more for each range marked, the counting of eight batches, the rank
+// table and the placement.
 constexpr int kSortBlock = 256;
 constexpr int kOwnBatches = 8;   // batches of a tile's own range held in registers (512 particles, 8 per cell)
 
@@ -1230,9 +1232,10 @@ __device__ __forceinline__ int tile_of_block(int ntiles)
 // wave's own copy of the tile's node block, lanes on distinct nodes per offset;
 // the copies are summed in a fixed order.  With four particles per cell a wave
 // of four has one round, where one wave (binary64, LDS atomics) had four.
-// A step of the 2-D dam-break, 8,192 / 32,768 / 73,728 particles: binary32
-// 24.1 / 25.6 / 28.5 -> 13.8 / 17.6 / 18.6 us, binary64 28.8 / 31.0 / 35.1 ->
-// 15.1 / 20.2 / 22.6.  This kernel takes 7.7 us of it at 8,192 particles and
+// A step of the 2-D dam-break before the water moves, 8,192 / 32,768 / 73,728
+// particles: binary32 24.1 / 25.6 / 28.5 -> 13.8 / 17.6 / 18.6 us, binary64 28.8 /
+// 31.0 / 35.1 -> 15.1 / 20.2 / 22.6; over 1000 steps of 8,192 26.2 -> 16.7 and 32.1 ->
+// 17.8.  This kernel takes 7.7 us of it at 8,192 particles and
 // G2P 6.2; what bounds both is the chain of launch, two memory round trips,
 // LDS phases and the drain of the stores.
 template <class T, int MAT, bool FL, bool GATHER, int NT>
