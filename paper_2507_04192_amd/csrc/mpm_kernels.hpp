@@ -1370,6 +1370,7 @@ __global__ __launch_bounds__(NT) void k_sort_p2g2(Geo g, Phys<T> P, Ranges rg, i
             if (w == 0) tile_sort_scan(ts, lane);
             __syncthreads();
             if (!GATHER || all || ts.found == at.cnt) break;
+            __syncthreads();   // all waves have read ts.found, which the first forms anew
             if (w == 0) {
                 // some came from further away: along their chain, one by one
                 const Far far{rg.moved, g.ntiles};
